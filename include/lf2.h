@@ -107,9 +107,11 @@ typedef struct lf2_plan_s *lf2_plan;
  * (LF2_ERR_UNSUPPORTED otherwise); r2c needs an even N0.  Line lengths
  * (N0/2 for r2c along x) with compiled kernels: 2^a, 3 2^a and 5 2^a up to
  * 1024 along x with ncomp 1, 2, 3 or 6, and up to 2048 along y and z; every
- * other 2^a 3^b 5^c line up to 8192 points (and any ncomp) runs kernels
- * with a run-time radix schedule (lf2_plan_get_schedule), as long as a tile
- * of one line fits the device's LDS.  The plan is bound to the current HIP
+ * other 2^a 3^b 5^c line up to 8192 points (and any ncomp) takes a run-time
+ * radix schedule (lf2_plan_get_schedule), as long as a tile of one line fits
+ * the device's LDS.  Of these, lines up to 1024 points (along x with those
+ * ncomp) run kernels compiled for their length until a schedule is set.
+ * The plan is bound to the current HIP
  * device; its twiddles (generated in FP64 on the device, rounded once to
  * FP32) stay resident until lf2_plan_destroy.  Synchronises the device once.
  */
@@ -171,8 +173,9 @@ lf2_status lf2_plan_set_tuning(lf2_plan p, int32_t axis, int32_t variant, int32_
  * product is the line length) of the passes along `axis` (0 = x, 1 = y,
  * 2 = z).  Line lengths with compiled kernels use a schedule fixed at
  * compile time; any other 2^a 3^b 5^c length, and any pass for which a
- * schedule is set, runs kernels that take the schedule at run time (*runtime
- * = 1).  LF2_PLAN_AUTOTUNE times the candidate schedules of every such axis,
+ * schedule is set, takes its schedule at run time (*runtime = 1; up to 1024
+ * points the default schedule's stages are compiled, forward bit for bit the
+ * same).  LF2_PLAN_AUTOTUNE times the candidate schedules of every such axis,
  * and of the y and z passes against their compiled kernels, and keeps the
  * fastest.  get: radices[0 .. *nstages - 1] (the rest 0); any output may be
  * NULL.  set: each radix 2, 3, 4, 5, 8 or 16 with product the line length;

@@ -31,9 +31,9 @@ COMMON = [
 
 # (source, extra flags, object name)
 UNITS = [
-    ("lf2_kx.hip", ["-DLF2_KX_PART=0"], "kx_r2c.o"),
-    ("lf2_kx.hip", ["-DLF2_KX_PART=1"], "kx_c2r.o"),
-    ("lf2_kx.hip", ["-DLF2_KX_PART=2"], "kx_c2c.o"),
+    *(("lf2_kx.hip", [f"-DLF2_KX_PART={p}", f"-DLF2_KX_SET={t}"], f"kx_{nm}{t}.o")
+      for t in (0, 2, 1) for p, nm in ((2, "c2c"), (0, "r2c"), (1, "c2r"))),
+    *(("lf2_kragged.hip", [f"-DLF2_KR_PART={p}"], f"kragged{p}.o") for p in (0, 1)),
     ("lf2_ks.hip", [], "ks.o"),
     ("lf2_kreg.hip", [], "kreg.o"),
     ("lf2_kmisc.hip", [], "kmisc.o"),

@@ -200,7 +200,7 @@ size_t spectrum_bytes(const lf2_plan_s *p)
 
 int x_grid_blocks(const lf2_plan_s *p)
 {
-    const int rb = p->gen[0] ? p->gen_rb : x_rows_per_block(p->len[0], p->nc);
+    const int rb = p->gen[0] && !p->nat[0] ? p->gen_rb : x_rows_per_block(p->len[0], p->nc);
     return (int)((p->n[1] * p->n[2] + rb - 1) / rb);
 }
 
@@ -505,9 +505,9 @@ lf2_status run_strided(const lf2_plan_s *p, int axis, int sign, const SArgs &a, 
     const double sb = (double)spectrum_bytes(p);
     const bool epi = (a.epi & (EPI_PK | EPI_PK_AFTER | EPI_POISSON)) != 0;
     const bool tr = (a.epi & (EPI_TSTORE | EPI_TLOAD)) != 0;
-    // run-time schedule: lengths without compiled kernels, and plain passes
-    // whose tuned schedule beat the compiled kernels
-    if (p->gen_only[axis] || (p->gen[axis] && !epi)) {
+    // run-time schedule: lengths without compiled kernels (or with a schedule
+    // set), and plain passes whose tuned schedule beat the compiled kernels
+    if (!p->nat[axis] && (p->gen_only[axis] || (p->gen[axis] && !epi))) {
         if (tr)
             return fail(LF2_ERR_UNSUPPORTED, "no transposing pass for line length %d", p->len[axis]);
         const bool pk = (a.epi & (EPI_PK | EPI_PK_AFTER)) != 0;
@@ -566,7 +566,7 @@ lf2_status run_x(const lf2_plan_s *p, int which, int sign, const XArgs &a, hipSt
     };
     const std::string shape = kname(" %lldx%lldx%lld/%d", (long long)p->n[0], (long long)p->n[1],
                                     (long long)p->n[2], p->nc);
-    if (p->gen[0]) {
+    if (p->gen[0] && !p->nat[0]) {
         static const char *const kModes[] = {"r2c", "c2r", "c2c"};
         const int mode = which == 0 ? 1 : which == 1 ? 2 : 0;
         t = prof::begin(kname("k_gx<%s>", kModes[which]) + shape, which == 2 ? 2 * sb : rb + sb, s);
@@ -770,6 +770,12 @@ lf2_status autotune(lf2_plan p)
             a.out_plane = c1 * p->n[1];
             const int mode = p->kind == LF2_R2C ? 1 : 0;
             double best = -1.0;
+            if (p->nat[0]) {  // the compiled tiles first: the default
+                best = p->tune_us[0][0] = time_it([&] {
+                    return mode == 1 ? launch_x_r2c(p->len[0], p->nc, a, s)
+                                     : launch_x_c2c(p->len[0], p->nc, -1, a, s);
+                });
+            }
             for (const GSched &sc : sched_candidates(p->len[0])) {
                 if (st != LF2_OK) break;
                 const double us = time_it([&] {
@@ -779,6 +785,7 @@ lf2_status autotune(lf2_plan p)
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
                     best = us;
                     p->sched[0] = sc;
+                    p->nat[0] = false;
                 }
             }
             p->tune_us[0][1] = best;
@@ -811,7 +818,7 @@ lf2_status autotune(lf2_plan p)
             const bool reg = !p->gen_only[axis] && s_reg_supported(p->len[axis]);
             const SArgs a = s_args(p, axis, w, w, EPI_STORE);
             double best = -1.0;
-            if (!p->gen_only[axis]) {
+            if (!p->gen_only[axis] || p->nat[axis]) {
                 // two sweeps over the settings, each setting keeping its
                 // faster time: a setting timed while the chip's clocks or
                 // memory state drift is timed again in the other sweep
@@ -862,6 +869,7 @@ lf2_status autotune(lf2_plan p)
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
                     best = us;
                     p->gen[axis] = true;
+                    p->nat[axis] = false;
                     p->sched[axis] = sc;
                 }
             }
@@ -932,6 +940,8 @@ lf2_status lf2_fft_plan(lf2_plan *out, const lf2_lattice *lat, int32_t ncomp, lf
     for (int i = 0; i < 3; ++i) {
         p->gen_only[i] = gen_only[i];
         p->gen[i] = gen_only[i];
+        p->nat[i] = gen_only[i] && ragged_supported(lens[i]) &&
+                    (i > 0 || ncomp == 1 || ncomp == 2 || ncomp == 3 || ncomp == 6);
         const std::vector<GSched> cand = sched_candidates(lens[i]);
         if (!cand.empty()) p->sched[i] = cand[0];
     }
@@ -1044,9 +1054,10 @@ lf2_status lf2_plan_get_schedule(lf2_plan p, int32_t axis, int32_t radices[15], 
         n = p->sched[axis].n;
         for (int i = 0; i < n; ++i) r[i] = p->sched[axis].r[i];
     } else {
-        // the compiled kernels' schedule (lf2_device.hpp)
-        n = lf2::nstages(p->len[axis]);
-        for (int i = 0; i < n && i < kGenMaxStages; ++i) r[i] = lf2::radix_at(p->len[axis], i);
+        // the factors of the compiled kernels' stages (lf2_device.hpp)
+        const lf2::RadixPlan rp = lf2::radix_plan(p->len[axis]);
+        n = rp.nf;
+        for (int i = 0; i < n && i < kGenMaxStages; ++i) r[i] = rp.f[i];
     }
     if (nst) *nst = n;
     if (runtime) *runtime = p->gen[axis] ? 1 : 0;
@@ -1074,6 +1085,7 @@ lf2_status lf2_plan_set_schedule(lf2_plan p, int32_t axis, const int32_t *radice
         return fail(LF2_ERR_UNSUPPORTED, "line length %d does not fit a tile", p->len[axis]);
     p->sched[axis] = sc;
     p->gen[axis] = true;
+    p->nat[axis] = false;
     return LF2_OK;
 }
 

@@ -216,32 +216,74 @@ struct Dft<32, S> {
 };
 
 // ---------------------------------------------------------------- radix plan
-// Radices for a line of length L = 2^a * 3^b * 5^c: the power-of-two part in
-// ceil(a/4) stages of 2..16 with the bits spread evenly (512 -> 8,8,8;
-// 256 -> 16,16; 128 -> 16,8), then the factors 3 and 5.
+// Factors for a line of length L = 2^a * 3^b * 5^c: the power-of-two part in
+// ceil(a/4) factors of 2..16 with the bits spread evenly (512 -> 8,8,8;
+// 256 -> 16,16; 128 -> 16,8), then the factors 3 and 5.  A stage takes one
+// factor, or, where 3s and 5s are more than one, two adjacent ones
+// (r = r1 r2) in the same registers: each stage is an exchange through LDS
+// with two barriers, and the pair does what its two stages would, value by
+// value, without the exchange between them.  Pairs of at most 25 points
+// (registers) are joined so that the stages are fewest, and of those so that
+// the largest stage is smallest (360 -> 8*3,3*5; 900 -> 4*3,3*5,5).  A single
+// 3 or 5 stays a stage of its own: joining it (192 as 8,8*3) made those
+// passes 0 to 14 % slower (320^3 forward: 163 -> 179 us), the longer
+// butterflies leaving too few per tile for its threads.
+constexpr int kMaxFactors = 12;
+constexpr int kMaxPair = 25;
 
-__host__ __device__ constexpr int ilog2c(int n) { return n <= 1 ? 0 : 1 + ilog2c(n / 2); }
-__host__ __device__ constexpr int pow2part(int n) { return (n % 2 == 0) ? 2 * pow2part(n / 2) : 1; }
-__host__ __device__ constexpr int nstages_pow2(int L) { return (ilog2c(pow2part(L)) + 3) / 4; }
-__host__ __device__ constexpr int count_factor(int n, int p) { return (n % p == 0 && n > 1) ? 1 + count_factor(n / p, p) : 0; }
-__host__ __device__ constexpr int nstages(int L)
+struct RadixPlan {
+    int n;                 // stages
+    int r[kMaxFactors];    // radix of each stage
+    int r1[kMaxFactors];   // its first factor (r1 = r: a single one)
+    int nf;                // factors
+    int f[kMaxFactors];
+    int nodd;              // factors of 3 and 5
+};
+
+// Fewest stages from factor i on with stages of at most m points.
+__host__ __device__ constexpr int fewest_stages(const RadixPlan &p, int i, int m)
 {
-    return nstages_pow2(L) + count_factor(L, 3) + count_factor(L, 5);
+    if (i >= p.nf) return 0;
+    if (p.f[i] > m) return 1 << 20;
+    int best = 1 + fewest_stages(p, i + 1, m);
+    if (i + 1 < p.nf && p.f[i] * p.f[i + 1] <= m && p.f[i] * p.f[i + 1] <= kMaxPair) {
+        const int two = 1 + fewest_stages(p, i + 2, m);
+        if (two < best) best = two;
+    }
+    return best;
 }
-__host__ __device__ constexpr int radix_at(int L, int st)
+__host__ __device__ constexpr RadixPlan radix_plan(int L)
 {
-    // power-of-two stages first
-    return st < nstages_pow2(L)
-               ? (1 << (ilog2c(pow2part(L)) / nstages_pow2(L) +
-                        (st < ilog2c(pow2part(L)) % nstages_pow2(L) ? 1 : 0)))
-               : (st < nstages_pow2(L) + count_factor(L, 3) ? 3 : 5);
+    RadixPlan p{};
+    int a = 0;
+    while (L % 2 == 0) {
+        L /= 2;
+        ++a;
+    }
+    const int ns2 = (a + 3) / 4;
+    for (int st = 0; st < ns2; ++st) p.f[p.nf++] = 1 << (a / ns2 + (st < a % ns2 ? 1 : 0));
+    for (; L % 3 == 0; L /= 3) p.f[p.nf++] = 3;
+    for (; L % 5 == 0; L /= 5) p.f[p.nf++] = 5;
+    p.nodd = p.nf - ns2;
+    if (p.nodd <= 1) {
+        for (; p.n < p.nf; ++p.n) p.r[p.n] = p.r1[p.n] = p.f[p.n];
+        return p;
+    }
+    const int ns = fewest_stages(p, 0, kMaxPair);
+    int m = 2;
+    while (m < kMaxPair && fewest_stages(p, 0, m) > ns) ++m;
+    for (int i = 0; i < p.nf;) {
+        const bool pair = i + 1 < p.nf && p.f[i] * p.f[i + 1] <= m &&
+                          p.n + 1 + fewest_stages(p, i + 2, m) == ns;
+        p.r1[p.n] = p.f[i];
+        p.r[p.n++] = pair ? p.f[i] * p.f[i + 1] : p.f[i];
+        i += pair ? 2 : 1;
+    }
+    return p;
 }
-__host__ __device__ constexpr int max_radix(int L, int st = 0)
-{
-    return st >= nstages(L) ? 1
-                            : (radix_at(L, st) > max_radix(L, st + 1) ? radix_at(L, st)
-                                                                      : max_radix(L, st + 1));
-}
+// Evaluated once per length and translation unit.
+template <int L>
+inline constexpr RadixPlan kPlan = radix_plan(L);
 
 // ------------------------------------------------------------ column engine
 // NL interleaved lines (columns of a strided pass), element (line l, point p)
@@ -311,7 +353,134 @@ __device__ __forceinline__ void gstore_pts(const c32 (&v)[R], c32 *p, int64_t qs
     }
 }
 
-template <int L, int R, int NS, int S, int NL, int NT, bool SRC_G, bool DST_G, bool NTM = false>
+// A line whose stages may be pairs (kPlan: more than one factor of 3 or 5).
+template <int L>
+inline constexpr bool kPaired = kPlan<L>.nodd > 1;
+
+// a w with the rounding of the run-time-schedule stages (lf2_kgen.hip), which
+// these lines also run: which product of a sum the compiler folds into the
+// fused multiply-add is left to it elsewhere, and is spelled out here, so
+// that a line gives the same bits either way.
+__device__ __forceinline__ c32 twiddle_mul(c32 a, c32 w)
+{
+    return c32{fmaf(a.x, w.x, -(a.y * w.y)), fmaf(a.y, w.x, a.x * w.y)};
+}
+
+// Dft<R, S>, the sums of two products in the 5- and 16-point ones spelled out
+// in the same way.
+template <int R, int S>
+__device__ __forceinline__ void dft_fixed(c32 *v)
+{
+    if constexpr (R == 5) {
+        const float c1 = 0.30901699437494742410f;   // cos(2 pi / 5)
+        const float c2 = -0.80901699437494742410f;  // cos(4 pi / 5)
+        const float s1 = 0.95105651629515357212f;   // sin(2 pi / 5)
+        const float s2 = 0.58778525229247312917f;   // sin(4 pi / 5)
+        const c32 t1 = add(v[1], v[4]), t2 = add(v[2], v[3]);
+        const c32 t3 = sub(v[1], v[4]), t4 = sub(v[2], v[3]);
+        const c32 a0 = v[0];
+        const c32 m1 = c32{fmaf(c2, t2.x, fmaf(c1, t1.x, a0.x)), fmaf(c2, t2.y, fmaf(c1, t1.y, a0.y))};
+        const c32 m2 = c32{fmaf(c1, t2.x, fmaf(c2, t1.x, a0.x)), fmaf(c1, t2.y, fmaf(c2, t1.y, a0.y))};
+        const c32 n1 = muli<S>(c32{fmaf(s2, t4.x, s1 * t3.x), fmaf(s2, t4.y, s1 * t3.y)});
+        const c32 n2 = muli<S>(c32{fmaf(s2, t3.x, -(s1 * t4.x)), fmaf(s2, t3.y, -(s1 * t4.y))});
+        v[0] = add(a0, add(t1, t2));
+        v[1] = add(m1, n1);
+        v[4] = sub(m1, n1);
+        v[2] = add(m2, n2);
+        v[3] = sub(m2, n2);
+    } else if constexpr (R == 16) {
+        const float c1 = 0.92387953251128675613f;  // cos(pi/8)
+        const float s1 = 0.38268343236508977173f;  // sin(pi/8)
+        const float r2 = 0.70710678118654752440f;
+        c32 t[4][4];
+#pragma unroll
+        for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+            for (int n1 = 0; n1 < 4; ++n1) t[n2][n1] = v[4 * n1 + n2];
+            Dft<4, S>::run(t[n2]);
+        }
+        auto m = [](c32 a, c32 w) {
+            return c32{fmaf(-a.y, w.y, a.x * w.x), fmaf(a.y, w.x, a.x * w.y)};
+        };
+        const c32 w11 = c32{c1, S * s1}, w12 = c32{r2, S * r2}, w13 = c32{s1, S * c1};
+        const c32 w23 = c32{-r2, S * r2}, w33 = c32{-c1, -S * s1};
+        t[1][1] = m(t[1][1], w11);
+        t[1][2] = m(t[1][2], w12);
+        t[1][3] = m(t[1][3], w13);
+        t[2][1] = m(t[2][1], w12);
+        t[2][2] = muli<S>(t[2][2]);
+        t[2][3] = m(t[2][3], w23);
+        t[3][1] = m(t[3][1], w13);
+        t[3][2] = m(t[3][2], w23);
+        const c32 a = t[3][3];
+        t[3][3] = c32{fmaf(a.x, w33.x, -(a.y * w33.y)), fmaf(a.x, w33.y, a.y * w33.x)};
+#pragma unroll
+        for (int k1 = 0; k1 < 4; ++k1) {
+            c32 u[4] = {t[0][k1], t[1][k1], t[2][k1], t[3][k1]};
+            Dft<4, S>::run(u);
+#pragma unroll
+            for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = u[k2];
+        }
+    } else {
+        Dft<R, S>::run(v);
+    }
+}
+
+// The stage twiddles and the radix-R butterfly of the thread's values v
+// (points j + r L/R, k = j mod NS) of a kPaired line.  R = R1 R2: the R2
+// butterflies of radix R1 over the points r2 + R2 r1 (twiddles
+// W_{NS R1}^{r1 k}), then, where R2 > 1, the R1 butterflies of radix R2 that
+// the next stage would do on their outputs (k + r1 NS there: twiddles
+// W_{NS R}^{r2 (k + r1 NS)}); output r1 + R1 r2 of the pair is output r of a
+// radix-R stage.
+template <int L, int R, int R1, int NS, int S>
+__device__ __forceinline__ void butterfly(c32 (&v)[R], int k, const c32 *tw)
+{
+    constexpr int R2 = R / R1;
+    static_assert(R1 * R2 == R, "two factors at most");
+    c32 t[R2][R1];
+#pragma unroll
+    for (int r2 = 0; r2 < R2; ++r2) {
+#pragma unroll
+        for (int r1 = 0; r1 < R1; ++r1) {
+            t[r2][r1] = v[r2 + R2 * r1];
+            if (NS > 1 && r1 > 0) {
+                c32 w = tw[tw_index<L / (NS * R1)>(r1, k)];
+                if (S > 0) w = conjg(w);
+                t[r2][r1] = twiddle_mul(t[r2][r1], w);
+            }
+        }
+        dft_fixed<R1, S>(t[r2]);
+    }
+#pragma unroll
+    for (int r1 = 0; r1 < R1; ++r1) {
+        c32 u[R2];
+#pragma unroll
+        for (int r2 = 0; r2 < R2; ++r2) {
+            u[r2] = t[r2][r1];
+            if (r2 > 0 && (NS > 1 || r1 > 0)) {
+                c32 w = tw[tw_index<L / (NS * R)>(r2, k + r1 * NS)];
+                if (S > 0) w = conjg(w);
+                u[r2] = twiddle_mul(u[r2], w);
+            }
+        }
+        if constexpr (R2 > 1) dft_fixed<R2, S>(u);
+#pragma unroll
+        for (int r2 = 0; r2 < R2; ++r2) v[r1 + R1 * r2] = u[r2];
+    }
+}
+
+// The butterfly of a first stage (no twiddles before it).
+template <int L, int R, int R1, int S>
+__device__ __forceinline__ void dft_first(c32 (&v)[R], const c32 *tw)
+{
+    if constexpr (kPaired<L>)
+        butterfly<L, R, R1, 1, S>(v, 0, tw);
+    else
+        Dft<R, S>::run(v);
+}
+
+template <int L, int R, int R1, int NS, int S, int NL, int NT, bool SRC_G, bool DST_G, bool NTM = false>
 __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, int64_t gs,
                                           bool gv, const c32 *tw, int tid)
 {
@@ -341,15 +510,19 @@ __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, i
         const int j = j0 + i * JS;
         if (Q % JS == 0 || j < Q) {
             const int k = j % NS;
-            if (NS > 1) {
+            if constexpr (kPaired<L>) {
+                butterfly<L, R, R1, NS, S>(v[i], k, tw);
+            } else {
+                if (NS > 1) {
 #pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    c32 w = tw[tw_index<L / (NS * R)>(r, k)];
-                    if (S > 0) w = conjg(w);
-                    v[i][r] = mul(v[i][r], w);
+                    for (int r = 1; r < R; ++r) {
+                        c32 w = tw[tw_index<L / (NS * R)>(r, k)];
+                        if (S > 0) w = conjg(w);
+                        v[i][r] = mul(v[i][r], w);
+                    }
                 }
+                Dft<R, S>::run(v[i]);
             }
-            Dft<R, S>::run(v[i]);
             if (DST_G) {
                 if (gv) gstore_pts<R, NTM>(v[i], gout + (int64_t)j * gs, (int64_t)Q * gs);
             } else {
@@ -401,7 +574,7 @@ __device__ __forceinline__ void gstoref(float *p, float v)
         *p = v;
 }
 
-template <int L, int R, int NS, int S, int RB, int NC, int LP, int NT, bool SRC_G, bool DST_G,
+template <int L, int R, int R1, int NS, int S, int RB, int NC, int LP, int NT, bool SRC_G, bool DST_G,
           bool NTM = false, bool PACK = false>
 __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
                                           const int64_t *rowoff_in, const int64_t *rowoff_out,
@@ -448,15 +621,19 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
             const int j = t % Q, q = t / Q;
             const int l = q * NC + c;
             const int k = j % NS;
-            if (NS > 1) {
+            if constexpr (kPaired<L>) {
+                butterfly<L, R, R1, NS, S>(v[i], k, tw);
+            } else {
+                if (NS > 1) {
 #pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    c32 w = tw[tw_index<L / (NS * R)>(r, k)];
-                    if (S > 0) w = conjg(w);
-                    v[i][r] = mul(v[i][r], w);
+                    for (int r = 1; r < R; ++r) {
+                        c32 w = tw[tw_index<L / (NS * R)>(r, k)];
+                        if (S > 0) w = conjg(w);
+                        v[i][r] = mul(v[i][r], w);
+                    }
                 }
+                Dft<R, S>::run(v[i]);
             }
-            Dft<R, S>::run(v[i]);
             if (DST_G && PACK) {
                 if (q < nvalid) {
 #pragma unroll
@@ -514,9 +691,9 @@ __device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout,
         }
         __syncthreads();
     } else if constexpr (NS < L) {
-        constexpr int R = radix_at(L, ST);
+        constexpr int R = kPlan<L>.r[ST], R1 = kPlan<L>.r1[ST];
         constexpr bool first = ST == 0, last = NS * R == L;
-        row_stage<L, R, NS, S, RB, NC, LP, NT, first && SRC_G, last && DST_G, NTM, PACK>(
+        row_stage<L, R, R1, NS, S, RB, NC, LP, NT, first && SRC_G, last && DST_G, NTM, PACK>(
             buf, gin, gout, rowoff_in, rowoff_out, nvalid, tw, tid, ssq);
         row_fft<L, S, RB, NC, LP, NT, SRC_G, DST_G, ST + 1, NS * R, NTM, PACK>(
             buf, gin, gout, rowoff_in, rowoff_out, nvalid, tw, tid, ssq);
@@ -527,9 +704,15 @@ __device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout,
 // order of the factors gives the same DFT; the reverse order lets a
 // transform start with the radix another one ended with (register hand-off
 // in the fused Poisson pass).
-__host__ __device__ constexpr int radix_sel(int L, int st, bool rev)
+template <int L>
+__host__ __device__ constexpr int radix_sel(int st, bool rev)
 {
-    return rev ? radix_at(L, nstages(L) - 1 - st) : radix_at(L, st);
+    return kPlan<L>.r[rev ? kPlan<L>.n - 1 - st : st];
+}
+template <int L>
+__host__ __device__ constexpr int radix1_sel(int st, bool rev)
+{
+    return kPlan<L>.r1[rev ? kPlan<L>.n - 1 - st : st];
 }
 
 // Butterflies per thread of a column stage with Q = L / R butterflies per
@@ -544,7 +727,7 @@ __host__ __device__ constexpr int col_nb(int L, int R, int NL, int NT)
 // of each butterfly j in v (they belong at points j + r Q when this is the
 // last stage).  After LDS reads the block waits at a barrier, so LDS may be
 // rewritten afterwards.
-template <int L, int R, int NS, int S, int NL, int NT, bool SRC_G, bool NTM = false>
+template <int L, int R, int R1, int NS, int S, int NL, int NT, bool SRC_G, bool NTM = false>
 __device__ __forceinline__ void col_stage_in(const c32 *buf, const c32 *gin, int64_t gs, bool gv,
                                              const c32 *tw, int tid,
                                              c32 (&v)[col_nb(L, R, NL, NT)][R])
@@ -574,15 +757,19 @@ __device__ __forceinline__ void col_stage_in(const c32 *buf, const c32 *gin, int
     for (int i = 0; i < NB; ++i) {
         const int j = j0 + i * JS;
         const int k = j % NS;
-        if (NS > 1) {
+        if constexpr (kPaired<L>) {
+            butterfly<L, R, R1, NS, S>(v[i], k, tw);
+        } else {
+            if (NS > 1) {
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                c32 w = tw[tw_index<L / (NS * R)>(r, k)];
-                if (S > 0) w = conjg(w);
-                v[i][r] = mul(v[i][r], w);
+                for (int r = 1; r < R; ++r) {
+                    c32 w = tw[tw_index<L / (NS * R)>(r, k)];
+                    if (S > 0) w = conjg(w);
+                    v[i][r] = mul(v[i][r], w);
+                }
             }
+            Dft<R, S>::run(v[i]);
         }
-        Dft<R, S>::run(v[i]);
     }
 }
 
@@ -637,10 +824,10 @@ __device__ __forceinline__ void col_fft(c32 *buf, const c32 *gin, c32 *gout, int
         }
         __syncthreads();
     } else if constexpr (NS < L) {
-        constexpr int R = radix_sel(L, ST, REV);
+        constexpr int R = radix_sel<L>(ST, REV), R1 = radix1_sel<L>(ST, REV);
         constexpr bool first = ST == 0, last = NS * R == L;
         if constexpr (!(last && SKIP_LAST)) {
-            col_stage<L, R, NS, S, NL, NT, first && SRC_G, last && DST_G, NTM>(buf, gin, gout, gs,
+            col_stage<L, R, R1, NS, S, NL, NT, first && SRC_G, last && DST_G, NTM>(buf, gin, gout, gs,
                                                                                gv, tw, tid);
             col_fft<L, S, NL, NT, SRC_G, DST_G, ST + 1, NS * R, NTM, REV, SKIP_LAST>(buf, gin, gout,
                                                                                     gs, gv, tw, tid);

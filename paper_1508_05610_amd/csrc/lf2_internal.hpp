@@ -112,7 +112,25 @@ hipError_t launch_strided_reg(int len, int sign, const SArgs &a, int grid_cap, h
 // LDS histogram copies of a fused last-axis tile of length len binning into
 // nbins bins, when the block's LDS is `budget` bytes: one per wave if they
 // fit with the tile, else one.  0 if len has no compiled fused tile.
-int epi_hist_copies(int len, int nbins, size_t budget);
+// persistent: the persistent batch kernel's blocks of 512 threads (the others
+// have s_nt<len>).
+int epi_hist_copies(int len, int nbins, size_t budget, bool persistent = false);
+
+// Kernels of the lengths of LF2_RAGGED_LENGTHS (lf2_kx.hip, lf2_kragged.hip):
+// the x tiles, and the narrow strided tile with its fused epilogue.  The
+// launchers above call them for those lengths.
+bool ragged_supported(int len);
+hipError_t ragged_x_r2c_a(int m, int nc, const XArgs &a, hipStream_t s);
+hipError_t ragged_x_r2c_b(int m, int nc, const XArgs &a, hipStream_t s);
+hipError_t ragged_x_c2r_a(int m, int nc, const XArgs &a, hipStream_t s);
+hipError_t ragged_x_c2r_b(int m, int nc, const XArgs &a, hipStream_t s);
+hipError_t ragged_x_c2c_a(int len, int nc, int sign, const XArgs &a, hipStream_t s);
+hipError_t ragged_x_c2c_b(int len, int nc, int sign, const XArgs &a, hipStream_t s);
+// plain pass (shm 0) or the fused last-axis pass (a.epi, forward sign only)
+hipError_t ragged_strided_a(int len, int sign, const SArgs &a, int grid, size_t shm, bool ntm,
+                            hipStream_t s);
+hipError_t ragged_strided_b(int len, int sign, const SArgs &a, int grid, size_t shm, bool ntm,
+                            hipStream_t s);
 
 // Run-time-schedule kernels (lf2_kgen.hip): LDS bytes of an x tile of RB
 // rows and of a strided tile of B columns (nbins > 0: with the binning

@@ -46,7 +46,49 @@ __host__ __device__ constexpr int s_b(int L)
     return L <= 128 ? 64 : L <= 256 ? 32 : L <= 512 ? 16 : L <= 1024 ? 8 : 4;
 }
 
+
+// Threads of a strided tile of lines of L points.  Each thread takes every
+// JS-th of the L / R butterflies of a stage, JS = threads / columns, so a
+// stage costs ceil((L / R) / JS) JS R points of work: of the whole-wave
+// counts up to 512 whose butterflies fit 32 registers of values, the one
+// with the least work over the stages, the larger one of equals.  Lines with
+// at most one factor of 3 or 5 take 512: powers of two divide evenly over
+// them, and the others (320, 384, ...) measured no faster with fewer.
+__host__ __device__ constexpr int s_work(int L, const RadixPlan &p, int nt)
+{
+    const int js = nt / s_b(L);
+    int w = 0;
+    for (int st = 0; st < p.n; ++st) {
+        const int nb = (L / p.r[st] + js - 1) / js;
+        if (nb * p.r[st] > 32) return 1 << 30;
+        w += nb * js * p.r[st];
+    }
+    return w;
+}
+__host__ __device__ constexpr int s_threads(int L)
+{
+    const RadixPlan p = radix_plan(L);
+    if (L < 16 || p.nodd <= 1) return kSThreads;
+    int best = kSThreads, work = s_work(L, p, best);
+    for (int nt = kSThreads - 64; nt >= 128; nt -= 64) {
+        const int w = nt % s_b(L) == 0 ? s_work(L, p, nt) : work;
+        if (w < work) {
+            best = nt;
+            work = w;
+        }
+    }
+    return best;
+}
+template <int L>
+inline constexpr int s_nt = s_threads(L);
+
 __host__ __device__ constexpr size_t al16(size_t b) { return (b + 15) & ~(size_t)15; }
+
+// LDS bytes of a narrow strided tile: its columns and the twiddle table.
+__host__ __device__ constexpr size_t s_bytes(int L)
+{
+    return al16(al16(sizeof(c32) * L * s_b(L)) + sizeof(c32) * L);
+}
 
 // Row base offsets of the RB rows of tile `blk`, in LDS.
 template <int RB, int NT>
@@ -271,11 +313,11 @@ struct XC2RGen {
             const c32 d = mul(conjg(twp[k]), sub(xk, xmc));
             return c32{sm_.x - d.y, sm_.y + d.x};  // s + i d
         };
-        if constexpr (nstages(M) >= 2) {
+        if constexpr (kPlan<M>.n >= 2) {
             // the first inverse stage forms its inputs Z[k] from the bins in
             // LDS as it reads them (butterfly b: component b % NC, then j,
             // then row, as in the row engine), then the remaining stages
-            constexpr int R = radix_at(M, 0), Q = M / R;
+            constexpr int R = kPlan<M>.r[0], Q = M / R;
             constexpr int NBF = NL * Q, NB = (NBF + NT - 1) / NT;
             c32 v[NB][R];
 #pragma unroll
@@ -296,7 +338,7 @@ struct XC2RGen {
                 if (NBF % NT == 0 || b < NBF) {
                     const int c = b % NC, t = b / NC;
                     const int j = t % Q, q = t / Q;
-                    Dft<R, +1>::run(v[i]);
+                    dft_first<M, R, kPlan<M>.r1[0], +1>(v[i], tw);
                     c32 *dst = buf + (q * NC + c) * LP;
 #pragma unroll
                     for (int r = 0; r < R; ++r) dst[lpad(j * R + r)] = v[i][r];
@@ -540,11 +582,11 @@ struct XC2RV {
             }
         }
         __syncthreads();
-        if constexpr (nstages(M) >= 2) {
+        if constexpr (kPlan<M>.n >= 2) {
             // The first inverse stage forms its inputs Z[k] from the bins
             // X[k], X[M-k] in LDS as it reads them (every read before the
             // barrier, every write after it), then the remaining stages.
-            constexpr int R = radix_at(M, 0), Q = M / R;
+            constexpr int R = kPlan<M>.r[0], Q = M / R;
             constexpr int NBF = RB * Q, NB = (NBF + NT - 1) / NT;
             c32 v[NB][R];
 #pragma unroll
@@ -573,7 +615,7 @@ struct XC2RV {
                 const int b = tid + i * NT;
                 if (NBF % NT == 0 || b < NBF) {
                     const int j = b % Q, q = b / Q;
-                    Dft<R, +1>::run(v[i]);
+                    dft_first<M, R, kPlan<M>.r1[0], +1>(v[i], tw);
                     c32 *dst = buf + q * LP;
 #pragma unroll
                     for (int r = 0; r < R; ++r) dst[lpad(j * R + r)] = v[i][r];
@@ -759,8 +801,7 @@ template <int L, int S, bool EPI, int NT, bool NTM = false, int K2 = 0>
 struct STile {
     static constexpr int B = s_b(L);
     static constexpr int RPT = NT / B;  // row groups in the epilogue
-    static constexpr size_t O_BUF = 0, O_TW = al16(sizeof(c32) * L * B),
-                            BYTES = al16(O_TW + sizeof(c32) * L);
+    static constexpr size_t O_BUF = 0, O_TW = al16(sizeof(c32) * L * B), BYTES = s_bytes(L);
     static __device__ void tables(const SArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, L, tid, NT);
@@ -769,7 +810,8 @@ struct STile {
     // j + r L/R0 of the thread's column (radix R0), all loads issued before
     // any of them is used (a column past the end loads column 0 and is
     // zeroed).
-    static constexpr int R0 = nstages(L) == 0 ? 1 : radix_sel(L, 0, false);
+    static constexpr int R0 = kPlan<L>.n == 0 ? 1 : kPlan<L>.r[0];
+    static constexpr int R01 = kPlan<L>.n == 0 ? 1 : kPlan<L>.r1[0];
     static constexpr int NB0 = col_nb(L, R0, B, NT);
     struct In {
         c32 v[NB0][R0];
@@ -856,14 +898,15 @@ struct STile {
                                                     bool valid, bool store, c32 *gout,
                                                     double *hist, const BinEdge *edges, In &in)
     {
-        constexpr int NST = nstages(L);
-        constexpr int RL = NST == 0 ? 1 : radix_at(L, NST - 1);
+        constexpr int NST = kPlan<L>.n;
+        constexpr int RL = NST == 0 ? 1 : kPlan<L>.r[NST - 1];
+        constexpr int RL1 = NST == 0 ? 1 : kPlan<L>.r1[NST - 1];
         constexpr int QL = L / RL;
         constexpr int NB = col_nb(L, RL, B, NT);
         const int j0 = tid / B;
         // first forward stage (no twiddles) on the loaded inputs
 #pragma unroll
-        for (int i = 0; i < NB0; ++i) Dft<R0, S>::run(in.v[i]);
+        for (int i = 0; i < NB0; ++i) dft_first<L, R0, R01, S>(in.v[i], tw);
         c32 v[NB][RL];
         if constexpr (NST <= 1) {
             static_assert(NB0 == NB && R0 == RL, "one stage: its inputs are its butterflies");
@@ -875,7 +918,7 @@ struct STile {
             col_stage_out<L, R0, 1, B, NT, false>(buf, nullptr, 0, false, tid, in.v);
             col_fft<L, S, B, NT, false, false, 1, R0, NTM, false, true>(buf, nullptr, nullptr, 0,
                                                                       false, tw, tid);
-            col_stage_in<L, RL, QL, S, B, NT, false>(buf, nullptr, 0, false, tw, tid, v);
+            col_stage_in<L, RL, RL1, QL, S, B, NT, false>(buf, nullptr, 0, false, tw, tid, v);
         }
         // column f = ky nxk + kx of the (kx, ky) plane (fewer than 2^31 columns)
         const int kx = valid ? (int)f % a.mt.nxk : 0;
@@ -914,7 +957,7 @@ struct STile {
                 // backward transform: first stage (radix RL, no twiddles) from
                 // the registers, the rest through LDS in reverse radix order
 #pragma unroll
-                for (int i = 0; i < NB; ++i) Dft<RL, +1>::run(v[i]);
+                for (int i = 0; i < NB; ++i) dft_first<L, RL, RL1, +1>(v[i], tw);
                 if constexpr (NST <= 1) {
                     col_stage_out<L, RL, 1, B, NT, true, NTM>(buf, gout, a.stride, valid && store,
                                                               tid, v);
@@ -1165,11 +1208,11 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2c_v(XArgs a)
 // fused pass's LDS tables leave room for one block (lines of 1024 points and
 // more), where two waves per SIMD are all it can reach.
 template <int L, int S, bool EPI, bool NTM = false, int K2 = 0>
-__global__ __launch_bounds__(kSThreads)
+__global__ __launch_bounds__(s_nt<L>)
     __attribute__((amdgpu_waves_per_eu(EPI && L >= 1024 ? 2 : 4))) void k_strided(SArgs a)
 {
-    using T = STile<L, S, EPI, kSThreads, NTM, K2>;
-    constexpr int NT = kSThreads;
+    constexpr int NT = s_nt<L>;
+    using T = STile<L, S, EPI, NT, NTM, K2>;
     constexpr int B = T::B;
     __shared__ __align__(16) char sm[T::BYTES];
     extern __shared__ double dyn[];  // hist[hcopies][nbins + 1], edges[nbins + 1]

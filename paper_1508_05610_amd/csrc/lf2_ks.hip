@@ -18,16 +18,29 @@ bool s_supported(int len)
 
 int s_cols_per_block(int len) { return s_b(len); }
 
-int epi_hist_copies(int len, int nbins, size_t budget)
+bool ragged_supported(int len)
 {
-    constexpr int kWaves = kSThreads / 64;
+    switch (len) {
+#define LF2_CASE(L) case L:
+        LF2_RAGGED_LENGTHS(LF2_CASE)
+#undef LF2_CASE
+        return true;
+    default:
+        return false;
+    }
+}
+
+int epi_hist_copies(int len, int nbins, size_t budget, bool persistent)
+{
     switch (len) {
 #define LF2_CASE(L)                                                                          \
     case L: {                                                                                \
-        const size_t tile = STile<L, -1, true, kSThreads, true>::BYTES;                      \
-        return tile + (size_t)(nbins + 1) * 8 * (kWaves + 1) <= budget ? kWaves : 1;         \
+        const int waves = (persistent ? kSThreads : s_nt<L>) / 64;                           \
+        const size_t tile = s_bytes(L);                                                      \
+        return tile + (size_t)(nbins + 1) * 8 * (waves + 1) <= budget ? waves : 1;           \
     }
         LF2_S_LENGTHS(LF2_CASE)
+        LF2_RAGGED_LENGTHS(LF2_CASE)
 #undef LF2_CASE
     default:
         return 0;
@@ -63,9 +76,9 @@ template <int L, bool NTM>
 static void narrow_k(int sign, int g, const SArgs &a, hipStream_t s)
 {
     if (sign < 0)
-        hipLaunchKernelGGL((k_strided<L, -1, false, NTM>), dim3(g), dim3(kSThreads), 0, s, a);
+        hipLaunchKernelGGL((k_strided<L, -1, false, NTM>), dim3(g), dim3(s_nt<L>), 0, s, a);
     else
-        hipLaunchKernelGGL((k_strided<L, 1, false, NTM>), dim3(g), dim3(kSThreads), 0, s, a);
+        hipLaunchKernelGGL((k_strided<L, 1, false, NTM>), dim3(g), dim3(s_nt<L>), 0, s, a);
 }
 
 static hipError_t launch_wide(int len, int sign, const SArgs &a, int grid_cap, hipStream_t s,
@@ -149,6 +162,14 @@ hipError_t launch_strided(int len, int sign, const SArgs &a_in, int grid_cap, hi
         return launch_wide(len, sign, a, grid_cap, s, grid_used, kChunk, ntm);
     }
     if (epi && ntm) return hipErrorInvalidValue;
+    if (ragged_supported(len)) {
+        const int b = s_b(len);
+        const int64_t ntiles = (a.ncols + b - 1) / b;
+        const int64_t span = (ntiles + 8 * kChunk - 1) / (8 * kChunk) * (8 * kChunk);
+        const int g = (int)(span < grid_cap ? span : grid_cap);
+        if (grid_used) *grid_used = g;
+        return (len <= 270 ? ragged_strided_a : ragged_strided_b)(len, sign, a, g, shm, ntm, s);
+    }
 #define LF2_CASE(L)                                                                          \
     case L: {                                                                                \
         int64_t ntiles = (a.ncols + s_b(L) - 1) / s_b(L);                                    \
@@ -156,10 +177,10 @@ hipError_t launch_strided(int len, int sign, const SArgs &a_in, int grid_cap, hi
         int g = (int)(span < grid_cap ? span : grid_cap);                                    \
         if (grid_used) *grid_used = g;                                                       \
         if (epi && sign < 0 && a.mt.k2z_unit > 0.0)                                          \
-            hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(g), dim3(kSThreads), shm, \
+            hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(g), dim3(s_nt<L>), shm,  \
                                s, a);                                                        \
         else if (epi && sign < 0)                                                            \
-            hipLaunchKernelGGL((k_strided<L, -1, true, true, 2>), dim3(g), dim3(kSThreads), shm, \
+            hipLaunchKernelGGL((k_strided<L, -1, true, true, 2>), dim3(g), dim3(s_nt<L>), shm,  \
                                s, a);                                                        \
         else if (epi)                                                                        \
             return hipErrorInvalidValue;                                                     \

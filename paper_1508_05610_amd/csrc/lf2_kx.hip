@@ -1,6 +1,8 @@
 // lf2_kx.hip -- instantiations and launchers of the x-pass kernels.
 // LF2_KX_PART selects the family compiled by this translation unit
-// (0: r2c, 1: c2r, 2: c2c) so that the families build in parallel.
+// (0: r2c, 1: c2r, 2: c2c) and LF2_KX_SET the line lengths (0: LF2_LENGTHS,
+// 1 and 2: the two lists of LF2_RAGGED_LENGTHS) so that they build in
+// parallel; a length outside its list is passed on to the next set.
 // One-component rows with 8-byte aligned element offsets take the fast
 // kernels (complex loads/stores straight into/out of the Stockham stages);
 // everything else (components interleaved, odd halo offsets) takes the
@@ -16,6 +18,28 @@ namespace lf2 {
 #ifndef LF2_KX_PART
 #define LF2_KX_PART 0
 #endif
+#ifndef LF2_KX_SET
+#define LF2_KX_SET 0
+#endif
+#if LF2_KX_SET == 0
+#define LF2_KX_LENGTHS LF2_LENGTHS
+#define LF2_KX_FN(f) launch_##f
+#define LF2_KX_NEXT(f) ragged_##f##_a
+#elif LF2_KX_SET == 1
+#define LF2_KX_LENGTHS LF2_RAGGED_LENGTHS_A
+#define LF2_KX_FN(f) ragged_##f##_a
+#define LF2_KX_NEXT(f) ragged_##f##_b
+#else
+#define LF2_KX_LENGTHS LF2_RAGGED_LENGTHS_B
+#define LF2_KX_FN(f) ragged_##f##_b
+#define LF2_KX_NEXT(f) no_length
+// past the last list
+template <class... A>
+static hipError_t no_length(A &&...)
+{
+    return hipErrorInvalidValue;
+}
+#endif
 
 static inline unsigned x_grid(int64_t nrows, int rb) { return (unsigned)((nrows + rb - 1) / rb); }
 
@@ -27,6 +51,7 @@ static inline bool pairs_aligned(const void *p, int64_t off, int64_t row, int64_
 }
 
 #if LF2_KX_PART == 0
+#if LF2_KX_SET == 0
 bool x_supported(int len, int nc)
 {
     if (nc != 1 && nc != 2 && nc != 3 && nc != 6) return false;
@@ -41,6 +66,7 @@ bool x_supported(int len, int nc)
 }
 
 int x_rows_per_block(int len, int nc) { return x_rb(len, nc); }
+#endif
 
 template <int L, int NC>
 static void r2c_nc(const XArgs &a, hipStream_t s)
@@ -49,7 +75,7 @@ static void r2c_nc(const XArgs &a, hipStream_t s)
                        a);
 }
 
-hipError_t launch_x_r2c(int m, int nc, const XArgs &a, hipStream_t s)
+hipError_t LF2_KX_FN(x_r2c)(int m, int nc, const XArgs &a, hipStream_t s)
 {
     const bool vec = nc == 1 && pairs_aligned(a.in, a.in_off, a.in_row, a.in_plane);
 #define LF2_CASE(L)                                                                          \
@@ -69,9 +95,9 @@ hipError_t launch_x_r2c(int m, int nc, const XArgs &a, hipStream_t s)
             return hipErrorInvalidValue;                                                     \
         return hipGetLastError();
     switch (m) {
-        LF2_LENGTHS(LF2_CASE)
+        LF2_KX_LENGTHS(LF2_CASE)
     default:
-        return hipErrorInvalidValue;
+        return LF2_KX_NEXT(x_r2c)(m, nc, a, s);
     }
 #undef LF2_CASE
 }
@@ -85,7 +111,7 @@ static void c2r_nc(const XArgs &a, hipStream_t s)
                        a);
 }
 
-hipError_t launch_x_c2r(int m, int nc, const XArgs &a, hipStream_t s)
+hipError_t LF2_KX_FN(x_c2r)(int m, int nc, const XArgs &a, hipStream_t s)
 {
     const bool vec = nc == 1 && pairs_aligned(a.out, a.out_off, a.out_row, a.out_plane);
 #define LF2_CASE(L)                                                                          \
@@ -105,9 +131,9 @@ hipError_t launch_x_c2r(int m, int nc, const XArgs &a, hipStream_t s)
             return hipErrorInvalidValue;                                                     \
         return hipGetLastError();
     switch (m) {
-        LF2_LENGTHS(LF2_CASE)
+        LF2_KX_LENGTHS(LF2_CASE)
     default:
-        return hipErrorInvalidValue;
+        return LF2_KX_NEXT(x_c2r)(m, nc, a, s);
     }
 #undef LF2_CASE
 }
@@ -125,6 +151,7 @@ static void c2c_nc(int sign, const XArgs &a, hipStream_t s)
                            dim3(kXThreads), 0, s, a);
 }
 
+#if LF2_KX_SET == 0
 // Lane j ^ M's value of v, for lanes in groups of eight (M = 1, 2, 4).
 // DPP: data-parallel moves of the VALU (quad permutes for M = 1 and 2; for
 // M = 4 a shift by four lanes either way within each row of sixteen lanes,
@@ -229,8 +256,9 @@ hipError_t launch_x_c2c_shfl(int sign, bool dpp, const XArgs &a, hipStream_t s)
         hipLaunchKernelGGL((k_x_c2c_s64<1, false>), dim3(g), dim3(256), 0, s, a);
     return hipGetLastError();
 }
+#endif
 
-hipError_t launch_x_c2c(int len, int nc, int sign, const XArgs &a, hipStream_t s)
+hipError_t LF2_KX_FN(x_c2c)(int len, int nc, int sign, const XArgs &a, hipStream_t s)
 {
 #define LF2_CASE(L)                                                                          \
     case L:                                                                                  \
@@ -246,9 +274,9 @@ hipError_t launch_x_c2c(int len, int nc, int sign, const XArgs &a, hipStream_t s
             return hipErrorInvalidValue;                                                     \
         return hipGetLastError();
     switch (len) {
-        LF2_LENGTHS(LF2_CASE)
+        LF2_KX_LENGTHS(LF2_CASE)
     default:
-        return hipErrorInvalidValue;
+        return LF2_KX_NEXT(x_c2c)(len, nc, sign, a, s);
     }
 #undef LF2_CASE
 }

@@ -56,6 +56,10 @@ struct lf2_plan_s {
     bool gen_only[3] = {false, false, false};
     bool gen[3] = {false, false, false};
     lf2::GSched sched[3] = {};
+    // a run-time-schedule axis whose length has compiled narrow tiles all the
+    // same (ragged_supported): its passes run them until a schedule is set
+    // or the tuner finds one faster
+    bool nat[3] = {false, false, false};
     int gen_rb = 1;          // x tile rows of the run-time x kernels
     size_t lds_max = 65536;  // LDS bytes a block may use on the plan's device
     void *tw[3] = {nullptr, nullptr, nullptr};
