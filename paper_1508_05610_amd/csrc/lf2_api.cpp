@@ -17,6 +17,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -98,7 +99,7 @@ struct Agg {
     double ms = 0.0, bytes = 0.0;
 };
 std::mutex mu;
-bool on = false;
+std::atomic<bool> on{false};
 std::vector<std::string> names;
 std::vector<Agg> agg;
 std::vector<Rec> recs;
@@ -119,6 +120,10 @@ hipEvent_t take()
 // Set while a call that must not allocate runs on this thread: its launches
 // are not recorded (recording may create events).
 thread_local bool t_quiet = false;
+
+// Whether launches on this thread are recorded (their names need not be
+// made otherwise: about 1 us of a call's host time per pass).
+bool active() { return on.load(std::memory_order_relaxed) && !t_quiet; }
 
 // Returns a record index, or -1 when timing is off.
 int begin(const std::string &name, double bytes, hipStream_t s)
@@ -204,7 +209,9 @@ int x_grid_blocks(const lf2_plan_s *p)
     return (int)((p->n[1] * p->n[2] + rb - 1) / rb);
 }
 
-// Workspace layout: [W spectrum][pk partials][bin sums][sumsq partials][sumsq]
+// Workspace layout: [W spectrum][pk partials][sums][sumsq partials][sumsq];
+// the results of the two reductions go straight to the caller's arrays, and
+// their places stay so that the size a caller planned for does not change.
 struct WsLayout {
     size_t w, part, sums, sq, sqt, total;
 };
@@ -515,12 +522,13 @@ lf2_status run_strided(const lf2_plan_s *p, int axis, int sign, const SArgs &a, 
         if (b < 1)
             return fail(LF2_ERR_UNSUPPORTED, "line length %d with %d bins does not fit a tile",
                         p->len[axis], pk ? a.mt.nbins : 0);
-        const int t = prof::begin(kname("k_gs<%d,%d> %s%s%s %lldx%lldx%lld/%d", sign, epi ? 1 : 0,
-                                        axis == 1 ? "y" : "z",
-                                        (a.epi & EPI_POISSON) ? "+poisson" : "", pk ? "+pk" : "",
-                                        (long long)p->n[0], (long long)p->n[1], (long long)p->n[2],
-                                        p->nc),
-                                  (a.epi & EPI_STORE) ? 2 * sb : sb, s);
+        int t = -1;
+        if (prof::active())
+            t = prof::begin(kname("k_gs<%d,%d> %s%s%s %lldx%lldx%lld/%d", sign, epi ? 1 : 0,
+                                  axis == 1 ? "y" : "z", (a.epi & EPI_POISSON) ? "+poisson" : "",
+                                  pk ? "+pk" : "", (long long)p->n[0], (long long)p->n[1],
+                                  (long long)p->n[2], p->nc),
+                            (a.epi & EPI_STORE) ? 2 * sb : sb, s);
         hipError_t e = launch_gs(sign, a, p->sched[axis], p->len[axis], b, grid_cap, s, grid_used);
         prof::end(t, s);
         if (e != hipSuccess)
@@ -533,18 +541,21 @@ lf2_status run_strided(const lf2_plan_s *p, int axis, int sign, const SArgs &a, 
                       fused_reg_fits(p->len[axis], (a.epi & (EPI_PK | EPI_PK_AFTER)) ? a.mt.nbins : 0);
     const int variant = tr ? 0 : epi ? (freg ? 8 : 0) : p->svar[axis];
     const int ntm = ((variant & 2) || epi) ? 1 : 0;  // the fused pass always streams
-    // "<kernel symbol> <pass>": the symbol part matches the profiler's name
-    const std::string sym = tr ? kname("k_strided_t<%d,%d>", p->len[axis], sign)
-                            : freg ? kname("k_fused_r<%d,%d>", p->len[axis], a.mt.k2z_unit > 0.0 ? 1 : 2)
-                            : (variant & 1) ? kname("k_strided_w<%d,%d,%d>", p->len[axis], sign, ntm)
-                            : (variant & 4) ? kname("k_strided_r<%d,%d,%d>", p->len[axis], sign, ntm)
-                                            : kname("k_strided<%d,%d,%d,%d>", p->len[axis], sign,
-                                                    epi ? 1 : 0, ntm);
-    const int t = prof::begin(sym + kname(" %s%s%s %lldx%lldx%lld/%d", axis == 1 ? "y" : "z",
+    int t = -1;
+    if (prof::active()) {
+        // "<kernel symbol> <pass>": the symbol part matches the profiler's name
+        const std::string sym = tr ? kname("k_strided_t<%d,%d>", p->len[axis], sign)
+                                : freg ? kname("k_fused_r<%d,%d>", p->len[axis], a.mt.k2z_unit > 0.0 ? 1 : 2)
+                                : (variant & 1) ? kname("k_strided_w<%d,%d,%d>", p->len[axis], sign, ntm)
+                                : (variant & 4) ? kname("k_strided_r<%d,%d,%d>", p->len[axis], sign, ntm)
+                                                : kname("k_strided<%d,%d,%d,%d>", p->len[axis], sign,
+                                                        epi ? 1 : 0, ntm);
+        t = prof::begin(sym + kname(" %s%s%s %lldx%lldx%lld/%d", axis == 1 ? "y" : "z",
                                     (a.epi & EPI_POISSON) ? "+poisson" : "",
                                     (a.epi & (EPI_PK | EPI_PK_AFTER)) ? "+pk" : "",
                                     (long long)p->n[0], (long long)p->n[1], (long long)p->n[2], p->nc),
-                              (a.epi & EPI_STORE) ? 2 * sb : sb, s);
+                        (a.epi & EPI_STORE) ? 2 * sb : sb, s);
+    }
     hipError_t e = launch_strided(p->len[axis], sign, a, grid_cap, s, grid_used, variant,
                                   epi ? 16 : p->schunk[axis]);
     prof::end(t, s);
@@ -557,65 +568,73 @@ lf2_status run_strided(const lf2_plan_s *p, int axis, int sign, const SArgs &a, 
 lf2_status run_x(const lf2_plan_s *p, int which, int sign, const XArgs &a, hipStream_t s)
 {
     hipError_t e;
-    const double rb = (double)p->ntot * p->nc * 4.0;  // real field
-    const double sb = (double)spectrum_bytes(p);
-    int t;
-    // the same layout test the launchers apply to pick the paired fast kernels
-    auto paired = [](const void *q, int64_t off, int64_t row, int64_t plane) {
-        return ((uintptr_t)q % 8) == 0 && off % 2 == 0 && row % 2 == 0 && plane % 2 == 0;
-    };
-    const std::string shape = kname(" %lldx%lldx%lld/%d", (long long)p->n[0], (long long)p->n[1],
-                                    (long long)p->n[2], p->nc);
-    if (p->gen[0] && !p->nat[0]) {
+    const bool gen = p->gen[0] && !p->nat[0];
+    int t = -1;
+    if (prof::active()) {
+        const double rb = (double)p->ntot * p->nc * 4.0;  // real field
+        const double sb = (double)spectrum_bytes(p);
+        // the same layout test the launchers apply to pick the paired fast kernels
+        auto paired = [](const void *q, int64_t off, int64_t row, int64_t plane) {
+            return ((uintptr_t)q % 8) == 0 && off % 2 == 0 && row % 2 == 0 && plane % 2 == 0;
+        };
         static const char *const kModes[] = {"r2c", "c2r", "c2c"};
-        const int mode = which == 0 ? 1 : which == 1 ? 2 : 0;
-        t = prof::begin(kname("k_gx<%s>", kModes[which]) + shape, which == 2 ? 2 * sb : rb + sb, s);
-        e = launch_gx(mode, sign, a, p->sched[0], p->len[0], p->nc, p->gen_rb, s);
-        prof::end(t, s);
-        if (e != hipSuccess)
-            return fail(LF2_ERR_DEVICE, "x pass (L=%d) launch: %s", p->len[0], hipGetErrorString(e));
-        return LF2_OK;
+        const bool v = which == 0 ? paired(a.in, a.in_off, a.in_row, a.in_plane)
+                                  : paired(a.out, a.out_off, a.out_row, a.out_plane);
+        std::string sym;
+        if (gen)
+            sym = kname("k_gx<%s>", kModes[which]);
+        else if (which == 2 && p->xx)
+            sym = kname("k_x_c2c_s64<%s,%d>", p->xx == 2 ? "dpp" : "bpermute", sign);
+        else if (which == 2)
+            sym = kname("k_x_c2c_v<%d,%d,%d>", p->len[0], p->nc, sign);
+        else if (p->nc == 1 && v)
+            sym = kname("k_x_%s_v<%d>", kModes[which], p->len[0]);
+        else
+            sym = kname("k_x_%s<%d,%d>", kModes[which], p->len[0], p->nc);
+        t = prof::begin(sym + kname(" %lldx%lldx%lld/%d", (long long)p->n[0], (long long)p->n[1],
+                                    (long long)p->n[2], p->nc),
+                        which == 2 ? 2 * sb : rb + sb, s);
     }
-    if (which == 0) {
-        const bool v = p->nc == 1 && paired(a.in, a.in_off, a.in_row, a.in_plane);
-        t = prof::begin((v ? kname("k_x_r2c_v<%d>", p->len[0]) : kname("k_x_r2c<%d,%d>", p->len[0], p->nc)) + shape,
-                        rb + sb, s);
+    if (gen)
+        e = launch_gx(which == 0 ? 1 : which == 1 ? 2 : 0, sign, a, p->sched[0], p->len[0], p->nc,
+                      p->gen_rb, s);
+    else if (which == 0)
         e = launch_x_r2c(p->len[0], p->nc, a, s);
-    } else if (which == 1) {
-        const bool v = p->nc == 1 && paired(a.out, a.out_off, a.out_row, a.out_plane);
-        t = prof::begin((v ? kname("k_x_c2r_v<%d>", p->len[0]) : kname("k_x_c2r<%d,%d>", p->len[0], p->nc)) + shape,
-                        rb + sb, s);
+    else if (which == 1)
         e = launch_x_c2r(p->len[0], p->nc, a, s);
-    } else if (p->xx) {
-        t = prof::begin(kname("k_x_c2c_s64<%s,%d>", p->xx == 2 ? "dpp" : "bpermute", sign) + shape,
-                        2 * sb, s);
+    else if (p->xx)
         e = launch_x_c2c_shfl(sign, p->xx == 2, a, s);
-    } else {
-        t = prof::begin(kname("k_x_c2c_v<%d,%d,%d>", p->len[0], p->nc, sign) + shape, 2 * sb, s);
+    else
         e = launch_x_c2c(p->len[0], p->nc, sign, a, s);
-    }
     prof::end(t, s);
     if (e != hipSuccess)
         return fail(LF2_ERR_DEVICE, "x pass (L=%d) launch: %s", p->len[0], hipGetErrorString(e));
     return LF2_OK;
 }
 
-// Binning tail: reduce partials, finalize into the caller's arrays.
-// sq_part (nullable): sq_rows per-block sums of squares of the real field,
-// reduced into *sq_total in the same launch as the bin partials.
-lf2_status pk_tail(lf2_plan p, const ShellEntry &sh, double *part, int grid, double *sums,
-                   double dx, double vscale, double *d_pk, double *d_kmean, double *d_count,
-                   double *d_parseval, const double *sq_part, int64_t sq_rows, double *sq_total,
-                   hipStream_t s)
+// Binning tail: reduce the partials into the caller's arrays.  sq_part
+// (with d_parseval): sq_rows per-block sums of squares of the real field.
+lf2_status pk_tail(lf2_plan p, const ShellEntry &sh, const double *part, int grid, double dx,
+                   double vscale, double *d_pk, double *d_kmean, double *d_count,
+                   double *d_parseval, const double *sq_part, int64_t sq_rows, hipStream_t s)
 {
-    const int nb = sh.nbins;
-    LF2_HIP(launch_reduce_cols2(part, grid, nb + 1, sums, sq_part, sq_rows, sq_part ? 1 : 0,
-                                sq_total, s));
-    const double *sumsq_total = sq_part ? sq_total : nullptr;
-    const double norm = dx * dx * dx / (double)p->ntot;
-    const double kscale = 6.283185307179586476925286766559 / ((double)p->lcm * dx);
-    LF2_HIP(launch_pk_finalize(sums, nb, sh.count, sh.sumk, norm, vscale, kscale, d_pk, d_kmean,
-                               d_count, d_parseval, sumsq_total, 1.0 / (double)p->ntot, s));
+    PkTail a{};
+    a.partial = part;
+    a.rows = grid;
+    a.nbins = sh.nbins;
+    a.count = sh.count;
+    a.sumk = sh.sumk;
+    a.norm = dx * dx * dx / (double)p->ntot;
+    a.vscale = vscale;
+    a.kscale = 6.283185307179586476925286766559 / ((double)p->lcm * dx);
+    a.inv_n = 1.0 / (double)p->ntot;
+    a.pk = d_pk;
+    a.kmean = d_kmean;
+    a.count_out = d_count;
+    a.parseval = d_parseval;
+    a.sq_part = sq_part;
+    a.sq_rows = sq_rows;
+    LF2_HIP(launch_pk_tail(a, s));
     return LF2_OK;
 }
 
@@ -1329,12 +1348,11 @@ lf2_status poisson_impl(lf2_plan p, const float *rho, float *phi, double dx, uin
     if (nb > 0) {
         const double vscale = (flags & LF2_PK_OF_PHI) ? (double)p->ntot * (double)p->ntot : 1.0;
         const bool user_bins = nbins > 0;
-        if ((st = pk_tail(p, sh, (double *)(ws + L.part), grid, (double *)(ws + L.sums), dx, vscale,
+        if ((st = pk_tail(p, sh, (const double *)(ws + L.part), grid, dx, vscale,
                           user_bins ? d_pk : nullptr, user_bins ? d_kmean : nullptr,
                           user_bins ? d_count : nullptr, d_parseval,
                           parseval ? (const double *)(ws + L.sq) : nullptr,
-                          parseval ? x_grid_blocks(p) : 0,
-                          parseval ? (double *)(ws + L.sqt) : nullptr, s)))
+                          parseval ? x_grid_blocks(p) : 0, s)))
             return st;
     }
     return LF2_OK;
@@ -1446,8 +1464,7 @@ lf2_status lf2_power_spectrum(lf2_plan p, const void *field, int32_t field_is_ks
         za.partial = part;
         if ((st = run_strided(p, 2, -1, za, kPkGrid, s, &grid))) return st;
     }
-    return pk_tail(p, sh, part, grid, (double *)(ws + L.sums), dx, 1.0, d_pk, d_kmean, d_count,
-                   nullptr, nullptr, 0, nullptr, s);
+    return pk_tail(p, sh, part, grid, dx, 1.0, d_pk, d_kmean, d_count, nullptr, nullptr, 0, s);
 }
 
 }  // extern "C"

@@ -160,16 +160,22 @@ hipError_t launch_shell_partials(const ModeTables &mt, int n1, int n2, double ls
 // out[b] = sum_g partial[g * width + b] in a fixed order, b < width.
 hipError_t launch_reduce_cols(const double *partial, int64_t grid, int width, double *out,
                               hipStream_t s);
-// the same for two arrays in one launch (width2 = 0: the second is unused)
-hipError_t launch_reduce_cols2(const double *partial1, int64_t grid1, int width1, double *out1,
-                               const double *partial2, int64_t grid2, int width2, double *out2,
-                               hipStream_t s);
 hipError_t launch_pk_kspace(const void *F, int n1, int n2, int64_t sx, int64_t sy, int64_t sz,
                             const ModeTables &mt, double *partial, int grid, hipStream_t s);
-hipError_t launch_pk_finalize(const double *S, int nbins, const double *count, const double *sumk,
-                              double norm, double vscale, double kscale, double *pk,
-                              double *kmean, double *count_out, double *parseval,
-                              const double *sumsq, double inv_n, hipStream_t s);
+// Results of a binning pass from its partials ([rows][nbins + 1], slot nbins
+// the row's total) and the lattice's shell table.
+struct PkTail {
+    const double *partial;
+    int64_t rows;
+    int nbins;
+    const double *count, *sumk;         // shell table
+    double norm, vscale, kscale, inv_n;
+    double *pk, *kmean, *count_out;     // nullable
+    double *parseval;                   // nullable: { sum of sq_part, k-space sum }
+    const double *sq_part;              // with parseval: sums of squares per block
+    int64_t sq_rows;
+};
+hipError_t launch_pk_tail(const PkTail &a, hipStream_t s);
 
 int x_rows_per_block(int len, int nc);
 int s_cols_per_block(int len);

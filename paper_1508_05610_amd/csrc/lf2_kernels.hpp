@@ -755,6 +755,29 @@ __device__ __forceinline__ void hist_flush(int nbins, int copies, double *hist, 
     }
 }
 
+// The flush at the end of a binning block: as hist_flush, but slot nbins of
+// the row gets the sum of all its slots (the zero mode included), bin 0
+// first over 64 strided lanes and a fixed tree, so that the k-space Parseval
+// sum is one more column of the reduction instead of a pass over its results.
+__device__ __forceinline__ void hist_flush_row(int nbins, int copies, double *hist, double *out,
+                                               int tid, int nt)
+{
+    const int w = nbins + 1;
+    for (int i = tid; i < w; i += nt) {
+        double s = hist[i];
+        for (int c = 1; c < copies; ++c) s += hist[c * w + i];
+        hist[i] = s;
+        if (i < nbins) out[i] = s;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        double t = 0.0;
+        for (int i = tid; i < w; i += 64) t += hist[i];
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
+        if (tid == 0) out[nbins] = t;
+    }
+}
+
 // 1/d for d > 0 in FP64: the hardware reciprocal refined by one Newton step,
 // which squares the estimate's relative error; the scale it feeds multiplies
 // FP32 modes in FP64 and is rounded to FP32 with the product.
@@ -1244,7 +1267,7 @@ __global__ __launch_bounds__(s_nt<L>)
     }
     if (pk) {
         __syncthreads();
-        hist_flush(nb, a.hcopies, hist, a.partial + (int64_t)blockIdx.x * (nb + 1), tid, NT);
+        hist_flush_row(nb, a.hcopies, hist, a.partial + (int64_t)blockIdx.x * (nb + 1), tid, NT);
     }
 }
 

@@ -318,8 +318,8 @@ __global__ __launch_bounds__(kGThreads) void k_gs(SArgs a, GSched sc, int L, int
         }
         __syncthreads();
     }
-    if (pk)
-        for (int i = tid; i <= nb; i += kGThreads) a.partial[(int64_t)blockIdx.x * (nb + 1) + i] = hist[i];
+    // the tile loop's last barrier has passed
+    if (pk) hist_flush_row(nb, 1, hist, a.partial + (int64_t)blockIdx.x * (nb + 1), tid, kGThreads);
 }
 
 hipError_t launch_gs(int sign, const SArgs &a, const GSched &sc, int len, int b, int grid_cap,

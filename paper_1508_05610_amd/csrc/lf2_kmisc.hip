@@ -166,23 +166,15 @@ hipError_t launch_shell_partials(const ModeTables &mt, int n1, int n2, double /*
     return hipGetLastError();
 }
 
-// Fixed-order column sums: out[b] = sum over g of partial[g * width + b].
-// One block per column (blocks width1.. serve an optional second array, so
-// that two reductions share a launch); thread t keeps four running sums
-// over the rows g = t + kRedThreads (4 i + j), j = 0..3 (four loads in
-// flight instead of a chain of dependent ones), adds them in a fixed order,
-// then a fixed tree combines the thread sums, so the result is reproducible.
+// Column b of partial ([grid][width]) summed over its rows in a fixed order
+// by the block: thread t keeps four running sums over the rows
+// g = t + kRedThreads (4 i + j), j = 0..3 (four loads in flight instead of a
+// chain of dependent ones), adds them in a fixed order, then a fixed tree
+// combines the thread sums, so the result is reproducible.  Thread 0 returns
+// the sum.
 constexpr int kRedThreads = 1024;
-__global__ __launch_bounds__(kRedThreads) void k_reduce_cols(
-    const double *partial1, int64_t grid1, int width1, double *out1, const double *partial2,
-    int64_t grid2, int width2, double *out2)
+__device__ double column_sum(const double *partial, int64_t grid, int width, int b, double *red)
 {
-    __shared__ double red[kRedThreads];
-    const bool first = (int)blockIdx.x < width1;
-    const double *partial = first ? partial1 : partial2;
-    const int64_t grid = first ? grid1 : grid2;
-    const int width = first ? width1 : width2;
-    const int b = first ? (int)blockIdx.x : (int)blockIdx.x - width1;
     const int t = threadIdx.x;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     int64_t g = t;
@@ -199,23 +191,25 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_cols(
         if (t < h) red[t] += red[t + h];
         __syncthreads();
     }
-    if (t == 0) (first ? out1 : out2)[b] = red[0];
+    return red[0];
 }
 
-hipError_t launch_reduce_cols2(const double *partial1, int64_t grid1, int width1, double *out1,
-                               const double *partial2, int64_t grid2, int width2, double *out2,
-                               hipStream_t s)
+// out[b] = sum over g of partial[g * width + b], one block per column.
+__global__ __launch_bounds__(kRedThreads) void k_reduce_cols(const double *partial, int64_t grid,
+                                                             int width, double *out)
 {
-    if (width1 + width2 <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce_cols, dim3(width1 + width2), dim3(kRedThreads), 0, s, partial1,
-                       grid1, width1, out1, partial2, grid2, width2, out2);
-    return hipGetLastError();
+    __shared__ double red[kRedThreads];
+    const double s = column_sum(partial, grid, width, blockIdx.x, red);
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 hipError_t launch_reduce_cols(const double *partial, int64_t grid, int width, double *out,
                               hipStream_t s)
 {
-    return launch_reduce_cols2(partial, grid, width, out, nullptr, 0, 0, nullptr, s);
+    if (width <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_reduce_cols, dim3(width), dim3(kRedThreads), 0, s, partial, grid, width,
+                       out);
+    return hipGetLastError();
 }
 
 // Power spectrum of a spectrum already in k space ([n2][n1][nxk], ncomp 1).
@@ -299,49 +293,40 @@ hipError_t launch_pk_kspace(const void *F, int n1, int n2, int64_t sx, int64_t s
     return hipGetLastError();
 }
 
-// From the bin sums S[0..nbins] (S[nbins] = zero mode) and the lattice
-// shell table: pk = norm * vscale * S_b / count_b, kmean = kscale * sumk_b /
-// count_b (0 for empty bins); parseval = { *sumsq, inv_n * vscale *
-// sum_b S_b including the zero mode }.
-constexpr int kFinThreads = 256;
-__global__ __launch_bounds__(kFinThreads) void k_pk_finalize(
-    const double *S, int nbins, const double *count, const double *sumk, double norm,
-    double vscale, double kscale, double *pk, double *kmean, double *count_out, double *parseval,
-    const double *sumsq, double inv_n)
+// The results of a binning pass, one launch: block b < nbins sums column b
+// of the partials (S_b) and writes pk = norm * vscale * S_b / count_b,
+// kmean = kscale * sumk_b / count_b (0 for empty bins) and count_b; with
+// parseval, block nbins sums the rows' totals (slot nbins) into
+// parseval[1] = inv_n * vscale * sum and block nbins + 1 the sums of squares
+// of the real field into parseval[0].  As two launches (column sums, then one
+// block finalizing them) the tail of a 32^3 solve took 2.9 + 4.0 us, most of
+// it launch and memory latency.
+__global__ __launch_bounds__(kRedThreads) void k_pk_tail(PkTail a)
 {
-    const int t = threadIdx.x;
-    for (int b = t; b < nbins; b += kFinThreads) {
-        const double c = count[b];
-        if (pk) pk[b] = c > 0 ? norm * vscale * S[b] / c : 0.0;
-        if (kmean) kmean[b] = c > 0 ? kscale * sumk[b] / c : 0.0;
-        if (count_out) count_out[b] = c;
+    __shared__ double red[kRedThreads];
+    const int b = blockIdx.x;
+    if (b > a.nbins) {
+        const double s = column_sum(a.sq_part, a.sq_rows, 1, 0, red);
+        if (threadIdx.x == 0) a.parseval[0] = s;
+        return;
     }
-    if (parseval) {  // uniform over the block
-        // sum of all nbins + 1 slots (the zero mode included): per-thread
-        // strided sums, then a fixed tree
-        __shared__ double red[kFinThreads];
-        double a = 0.0;
-        for (int b = t; b <= nbins; b += kFinThreads) a += S[b];
-        red[t] = a;
-        __syncthreads();
-        for (int h = kFinThreads / 2; h > 0; h >>= 1) {
-            if (t < h) red[t] += red[t + h];
-            __syncthreads();
-        }
-        if (t == 0) {
-            parseval[0] = sumsq ? *sumsq : 0.0;
-            parseval[1] = inv_n * vscale * red[0];
-        }
+    const double s = column_sum(a.partial, a.rows, a.nbins + 1, b, red);
+    if (threadIdx.x != 0) return;
+    if (b == a.nbins) {
+        a.parseval[1] = a.inv_n * a.vscale * s;
+        return;
     }
+    const double c = a.count[b];
+    if (a.pk) a.pk[b] = c > 0 ? a.norm * a.vscale * s / c : 0.0;
+    if (a.kmean) a.kmean[b] = c > 0 ? a.kscale * a.sumk[b] / c : 0.0;
+    if (a.count_out) a.count_out[b] = c;
 }
 
-hipError_t launch_pk_finalize(const double *S, int nbins, const double *count, const double *sumk,
-                              double norm, double vscale, double kscale, double *pk,
-                              double *kmean, double *count_out, double *parseval,
-                              const double *sumsq, double inv_n, hipStream_t s)
+hipError_t launch_pk_tail(const PkTail &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pk_finalize, dim3(1), dim3(kFinThreads), 0, s, S, nbins, count, sumk, norm,
-                       vscale, kscale, pk, kmean, count_out, parseval, sumsq, inv_n);
+    const int blocks = a.nbins + (a.parseval ? 2 : 0);
+    if (blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pk_tail, dim3(blocks), dim3(kRedThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -406,7 +406,7 @@ void k_fused_r(SArgs a)
             fused_walk<L>(a, pw, c, j, kx, corner, qxy, fp < a.ncols, wh, edges);
         }
         __syncthreads();
-        hist_flush(nb, a.hcopies, hist, a.partial + (int64_t)blockIdx.x * (nb + 1), tid, kFThreads);
+        hist_flush_row(nb, a.hcopies, hist, a.partial + (int64_t)blockIdx.x * (nb + 1), tid, kFThreads);
     }
 }
 
