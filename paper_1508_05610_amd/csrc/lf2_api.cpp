@@ -209,6 +209,22 @@ int x_grid_blocks(const lf2_plan_s *p)
     return (int)((p->n[1] * p->n[2] + rb - 1) / rb);
 }
 
+// Whether the plan's planes run both their axes in one block (k_plane): they
+// fit its LDS, the field is small enough to be bound by latency, and there is
+// a plane for every CU or the planes are small.  With N1 = 64 and N0 = 64 or
+// 128, real: 4.2 M sites 1.2 times faster forward and 1.1 backward, 8.4 M
+// sites equal forward and 0.9 times as fast backward.  128 x 128 planes
+// (142 KB): 256 of them 1.5 and 1.1 times faster, 128 of them 1.1 and 1.0, and
+// the Poisson solve's way back 1 us slower, half the chip being idle; 120 x
+// 120 planes (123 KB), 120 of them: 1.1 and 1.03 times faster.
+bool plane_fits(const lf2_plan_s *p)
+{
+    if (p->ntot * p->nc * (p->kind == LF2_C2C ? 2 : 1) > kPlaneFloats) return false;
+    if (!plane_axis_ok(p->len[0]) || !plane_axis_ok(p->len[1])) return false;
+    return plane_lds_bytes(p->len[0], (int)p->nxk, p->nc, p->len[1]) <=
+           (p->n[2] < 256 ? (size_t)128 * 1024 : kPlaneLds);
+}
+
 // Workspace layout: [W spectrum][pk partials][sums][sumsq partials][sumsq];
 // the results of the two reductions go straight to the caller's arrays, and
 // their places stay so that the size a caller planned for does not change.
@@ -216,7 +232,7 @@ struct WsLayout {
     size_t w, part, sums, sq, sqt, total;
 };
 
-WsLayout ws_layout(const lf2_plan_s *p, bool need_w, int nbins, bool parseval)
+WsLayout ws_layout(const lf2_plan_s *p, bool need_w, int nbins, bool parseval, bool plane = false)
 {
     WsLayout l{};
     size_t off = 0;
@@ -227,7 +243,8 @@ WsLayout ws_layout(const lf2_plan_s *p, bool need_w, int nbins, bool parseval)
     l.sums = off;
     off += nbins > 0 ? align256((size_t)(nbins + 1) * 8) : 0;
     l.sq = off;
-    off += parseval ? align256((size_t)x_grid_blocks(p) * 8) : 0;
+    const int64_t sq_rows = x_grid_blocks(p);
+    off += parseval ? align256((size_t)(plane && p->n[2] > sq_rows ? p->n[2] : sq_rows) * 8) : 0;
     l.sqt = off;
     off += parseval ? 256 : 0;
     l.total = off;
@@ -610,6 +627,43 @@ lf2_status run_x(const lf2_plan_s *p, int which, int sign, const XArgs &a, hipSt
     if (e != hipSuccess)
         return fail(LF2_ERR_DEVICE, "x pass (L=%d) launch: %s", p->len[0], hipGetErrorString(e));
     return LF2_OK;
+}
+
+// The x and y passes of every plane in one launch: which as for run_x (0 r2c
+// forward, 1 c2r backward, 2 c2c).
+lf2_status run_plane(const lf2_plan_s *p, int which, int sign, const XArgs &a, hipStream_t s)
+{
+    int t = -1;
+    if (prof::active()) {
+        static const char *const kModes[] = {"r2c", "c2r", "c2c"};
+        const double rb = (double)p->ntot * p->nc * 4.0, sb = (double)spectrum_bytes(p);
+        t = prof::begin(kname("k_plane<%s,%d> xy %lldx%lldx%lld/%d", kModes[which], sign,
+                              (long long)p->n[0], (long long)p->n[1], (long long)p->n[2], p->nc),
+                        which == 2 ? 2 * sb : rb + sb, s);
+    }
+    const hipError_t e = launch_plane(which == 0 ? 1 : which == 1 ? 2 : 0, sign, a, p->len[0],
+                                      (int)p->nxk, p->nc, (int)p->n[1], (int)p->n[2], p->tw[1], s);
+    prof::end(t, s);
+    if (e != hipSuccess)
+        return fail(LF2_ERR_DEVICE, "plane pass (%dx%d) launch: %s", p->len[0], p->len[1],
+                    hipGetErrorString(e));
+    return LF2_OK;
+}
+
+// The x pass (x) and the y pass in place on its output, forward; or the y
+// pass in place on x's input (W) and the x pass, backward.
+lf2_status run_xy(const lf2_plan_s *p, int which, int sign, const XArgs &x, void *spec, hipStream_t s,
+                  bool plane)
+{
+    if (plane) return run_plane(p, which, sign, x, s);
+    lf2_status st;
+    const SArgs y = s_args(p, 1, spec, spec, EPI_STORE);
+    if (sign < 0) {
+        if ((st = run_x(p, which, sign, x, s))) return st;
+        return run_strided(p, 1, sign, y, kStridedGridCap, s, nullptr);
+    }
+    if ((st = run_strided(p, 1, sign, y, kStridedGridCap, s, nullptr))) return st;
+    return run_x(p, which, sign, x, s);
 }
 
 // Binning tail: reduce the partials into the caller's arrays.  sq_part
@@ -999,6 +1053,9 @@ lf2_status lf2_fft_plan(lf2_plan *out, const lf2_lattice *lat, int32_t ncomp, lf
         int64_t a = (p->n[i] / 2) * (p->lcm / p->n[i]);
         p->qmax += a * a;
     }
+    p->plane = plane_fits(p);
+    p->plane_bits = p->plane && plane_axis_bits(p->len[0], kind == LF2_R2C) &&
+                    plane_axis_bits(p->len[1], false);
     hipStream_t s = nullptr;
     lf2_status st = LF2_OK;
     // the fused binning evaluates the bin rule in 32 x 32 -> 64-bit products
@@ -1105,6 +1162,7 @@ lf2_status lf2_plan_set_schedule(lf2_plan p, int32_t axis, const int32_t *radice
     p->sched[axis] = sc;
     p->gen[axis] = true;
     p->nat[axis] = false;
+    if (axis < 2) p->plane = false;  // the pass that was asked for
     return LF2_OK;
 }
 
@@ -1123,6 +1181,7 @@ lf2_status lf2_plan_set_tuning(lf2_plan p, int32_t axis, int32_t variant, int32_
                         "lane exchange needs c2c rows of 64 points and one component");
         }
         p->xx = variant;
+        p->plane = false;  // the pass that was asked for
         return LF2_OK;
     }
     if (axis == 3) {
@@ -1146,6 +1205,7 @@ lf2_status lf2_plan_set_tuning(lf2_plan p, int32_t axis, int32_t variant, int32_
     p->svar[axis] = variant;
     p->schunk[axis] = chunk;
     p->gen[axis] = false;  // the compiled kernels again
+    if (axis == 1) p->plane = false;  // the pass that was asked for
     return LF2_OK;
 }
 
@@ -1218,8 +1278,7 @@ lf2_status lf2_fft_execute(lf2_plan p, lf2_direction dir, const void *in, void *
             if ((st = run_x(p, 0, -1, x_args(p, in, W, true, false, true), s))) return st;
             if ((st = run_strided(p, 1, -1, s_args(p, 1, W, out, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
         } else {
-            if ((st = run_x(p, 0, -1, x_args(p, in, out, true, false, true), s))) return st;
-            if ((st = run_strided(p, 1, -1, s_args(p, 1, out, out, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
+            if ((st = run_xy(p, 0, -1, x_args(p, in, out, true, false, true), out, s, p->plane))) return st;
         }
         return run_strided(p, 2, -1, s_args(p, 2, out, out, EPI_STORE), kStridedGridCap, s, nullptr);
     }
@@ -1229,44 +1288,33 @@ lf2_status lf2_fft_execute(lf2_plan p, lf2_direction dir, const void *in, void *
         if ((st = get_workspace(p, L.total, &ws))) return st;
         void *W = ws + L.w;
         if ((st = run_strided(p, 2, +1, s_args(p, 2, in, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-        if ((st = run_strided(p, 1, +1, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-        return run_x(p, 1, +1, x_args(p, W, out, false, true, true), s);
+        return run_xy(p, 1, +1, x_args(p, W, out, false, true, true), W, s, p->plane);
     }
-    // c2c
+    // c2c: x and y of a plane, then z, forward; the reverse, backward.  The
+    // intermediate is out, or the workspace where out has another layout (the
+    // paper's (k_z, k_x, k_y) order: the z pass stores or loads transposed) or
+    // a halo (backward)
     const int sg = (int)dir;
-    if (p->klay == 2) {
-        // the paper's (k_z, k_x, k_y) order: natural passes in the workspace,
-        // the z pass stores (forward) or loads (backward) transposed
+    void *W = out;
+    if (p->klay == 2 || (dir == LF2_BACKWARD && p->halo != 0)) {
         WsLayout L = ws_layout(p, true, 0, false);
         char *ws;
         if ((st = get_workspace(p, L.total, &ws))) return st;
-        void *W = ws + L.w;
-        if (dir == LF2_FORWARD) {
-            if ((st = run_x(p, 2, sg, x_args(p, in, W, true, false, false), s))) return st;
-            if ((st = run_strided(p, 1, sg, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-            return run_strided(p, 2, sg, t_args(p, W, out, EPI_STORE | EPI_TSTORE), kStridedGridCap, s, nullptr);
-        }
-        if ((st = run_strided(p, 2, sg, t_args(p, in, W, EPI_STORE | EPI_TLOAD), kStridedGridCap, s, nullptr))) return st;
-        if ((st = run_strided(p, 1, sg, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-        return run_x(p, 2, sg, x_args(p, W, out, false, true, false), s);
+        W = ws + L.w;
     }
+    auto zpass = [&](const void *src, void *dst) {
+        if (p->klay == 2)
+            return run_strided(p, 2, sg,
+                               t_args(p, src, dst, EPI_STORE | (sg < 0 ? EPI_TSTORE : EPI_TLOAD)),
+                               kStridedGridCap, s, nullptr);
+        return run_strided(p, 2, sg, s_args(p, 2, src, dst, EPI_STORE), kStridedGridCap, s, nullptr);
+    };
     if (dir == LF2_FORWARD) {
-        if ((st = run_x(p, 2, sg, x_args(p, in, out, true, false, false), s))) return st;
-        if ((st = run_strided(p, 1, sg, s_args(p, 1, out, out, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-        return run_strided(p, 2, sg, s_args(p, 2, out, out, EPI_STORE), kStridedGridCap, s, nullptr);
+        if ((st = run_xy(p, 2, sg, x_args(p, in, W, true, false, false), W, s, p->plane))) return st;
+        return zpass(W, out);
     }
-    if (p->halo == 0) {
-        if ((st = run_strided(p, 2, sg, s_args(p, 2, in, out, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-        if ((st = run_strided(p, 1, sg, s_args(p, 1, out, out, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-        return run_x(p, 2, sg, x_args(p, out, out, false, true, false), s);
-    }
-    WsLayout L = ws_layout(p, true, 0, false);
-    char *ws;
-    if ((st = get_workspace(p, L.total, &ws))) return st;
-    void *W = ws + L.w;
-    if ((st = run_strided(p, 2, sg, s_args(p, 2, in, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-    if ((st = run_strided(p, 1, sg, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-    return run_x(p, 2, sg, x_args(p, W, out, false, true, false), s);
+    if ((st = zpass(in, W))) return st;
+    return run_xy(p, 2, sg, x_args(p, W, out, false, true, false), W, s, p->plane);
 }
 
 }  // extern "C"
@@ -1304,7 +1352,16 @@ lf2_status poisson_impl(lf2_plan p, const float *rho, float *phi, double dx, uin
     hipStream_t s = (hipStream_t)stream;
     const bool parseval = d_parseval != nullptr;
     const int nb = nbins > 0 ? nbins : (parseval ? 1 : 0);
-    WsLayout L = ws_layout(p, true, nb, parseval);
+    // bins and Parseval sums are FP64 sums of the forward spectrum: the plane
+    // kernel makes it where it gives the two passes' bits
+    bool plane = p->plane && (nb == 0 || p->plane_bits);
+    WsLayout L = ws_layout(p, true, nb, parseval, plane);
+    const size_t room = ws_given ? ws_given_bytes : p->own_ws ? p->own_ws_bytes : L.total;
+    if (plane && room < L.total) {
+        // a workspace sized for the two passes' sums of squares: run those
+        plane = false;
+        L = ws_layout(p, true, nb, parseval);
+    }
     char *ws;
     if (ws_given) {
         if (ws_given_bytes < L.total)
@@ -1330,8 +1387,7 @@ lf2_status poisson_impl(lf2_plan p, const float *rho, float *phi, double dx, uin
 
     XArgs xa = x_args(p, rho, W, true, false, true);
     if (parseval) xa.sumsq = (double *)(ws + L.sq);
-    if ((st = run_x(p, 0, -1, xa, s))) return st;
-    if ((st = run_strided(p, 1, -1, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
+    if ((st = run_xy(p, 0, -1, xa, W, s, plane))) return st;
     int epi = EPI_STORE | EPI_POISSON;
     if (nb > 0) epi |= (flags & LF2_PK_OF_PHI) ? EPI_PK_AFTER : EPI_PK;
     SArgs za = s_args(p, 2, W, W, epi);
@@ -1343,8 +1399,7 @@ lf2_status poisson_impl(lf2_plan p, const float *rho, float *phi, double dx, uin
         za.partial = (double *)(ws + L.part);
     }
     if ((st = run_strided(p, 2, -1, za, nb > 0 ? kPkGrid : kStridedGridCap, s, &grid))) return st;
-    if ((st = run_strided(p, 1, +1, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
-    if ((st = run_x(p, 1, +1, x_args(p, W, phi, false, true, true), s))) return st;
+    if ((st = run_xy(p, 1, +1, x_args(p, W, phi, false, true, true), W, s, p->plane))) return st;
     if (nb > 0) {
         const double vscale = (flags & LF2_PK_OF_PHI) ? (double)p->ntot * (double)p->ntot : 1.0;
         const bool user_bins = nbins > 0;
@@ -1352,7 +1407,7 @@ lf2_status poisson_impl(lf2_plan p, const float *rho, float *phi, double dx, uin
                           user_bins ? d_pk : nullptr, user_bins ? d_kmean : nullptr,
                           user_bins ? d_count : nullptr, d_parseval,
                           parseval ? (const double *)(ws + L.sq) : nullptr,
-                          parseval ? x_grid_blocks(p) : 0, s)))
+                          !parseval ? 0 : plane ? p->n[2] : x_grid_blocks(p), s)))
             return st;
     }
     return LF2_OK;
@@ -1453,12 +1508,9 @@ lf2_status lf2_power_spectrum(lf2_plan p, const void *field, int32_t field_is_ks
         LF2_HIP(e);
     } else {
         void *W = ws + L.w;
-        if (p->kind == LF2_R2C) {
-            if ((st = run_x(p, 0, -1, x_args(p, field, W, true, false, true), s))) return st;
-        } else {
-            if ((st = run_x(p, 2, -1, x_args(p, field, W, true, false, false), s))) return st;
-        }
-        if ((st = run_strided(p, 1, -1, s_args(p, 1, W, W, EPI_STORE), kStridedGridCap, s, nullptr))) return st;
+        const int which = p->kind == LF2_R2C ? 0 : 2;
+        const XArgs xa = x_args(p, field, W, true, false, which == 0);
+        if ((st = run_xy(p, which, -1, xa, W, s, p->plane_bits))) return st;
         SArgs za = s_args(p, 2, W, W, EPI_PK);
         use_shell(za.mt, sh);
         za.partial = part;

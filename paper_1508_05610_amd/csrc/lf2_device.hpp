@@ -357,18 +357,23 @@ __device__ __forceinline__ void gstore_pts(const c32 (&v)[R], c32 *p, int64_t qs
 template <int L>
 inline constexpr bool kPaired = kPlan<L>.nodd > 1;
 
-// a w with the rounding of the run-time-schedule stages (lf2_kgen.hip), which
-// these lines also run: which product of a sum the compiler folds into the
-// fused multiply-add is left to it elsewhere, and is spelled out here, so
-// that a line gives the same bits either way.
+// a w.  Which product of a sum the compiler folds into the fused
+// multiply-add is left to it in most stages, and is spelled out here and in
+// dft_fixed, so that kernels which run a stage of another kernel's line give
+// its bits.  XW: im = fma(a.x, w.y, a.y w.x), as in a compiled line's last
+// stage where that stores to memory; else fma(a.y, w.x, a.x w.y), as in its
+// other stages and in the run-time-schedule stages (lf2_kgen.hip).
+template <bool XW = false>
 __device__ __forceinline__ c32 twiddle_mul(c32 a, c32 w)
 {
-    return c32{fmaf(a.x, w.x, -(a.y * w.y)), fmaf(a.y, w.x, a.x * w.y)};
+    const float re = fmaf(a.x, w.x, -(a.y * w.y));
+    return c32{re, XW ? fmaf(a.x, w.y, a.y * w.x) : fmaf(a.y, w.x, a.x * w.y)};
 }
 
 // Dft<R, S>, the sums of two products in the 5- and 16-point ones spelled out
-// in the same way.
-template <int R, int S>
+// in the same way: as in the run-time-schedule stages, or (T32) as in the
+// compiled ones, which differ in one of the 16-point twiddles.
+template <int R, int S, bool T32 = false>
 __device__ __forceinline__ void dft_fixed(c32 *v)
 {
     if constexpr (R == 5) {
@@ -402,6 +407,9 @@ __device__ __forceinline__ void dft_fixed(c32 *v)
         auto m = [](c32 a, c32 w) {
             return c32{fmaf(-a.y, w.y, a.x * w.x), fmaf(a.y, w.x, a.x * w.y)};
         };
+        auto my = [](c32 a, c32 w) {
+            return c32{fmaf(a.x, w.x, -(a.y * w.y)), fmaf(a.x, w.y, a.y * w.x)};
+        };
         const c32 w11 = c32{c1, S * s1}, w12 = c32{r2, S * r2}, w13 = c32{s1, S * c1};
         const c32 w23 = c32{-r2, S * r2}, w33 = c32{-c1, -S * s1};
         t[1][1] = m(t[1][1], w11);
@@ -411,7 +419,7 @@ __device__ __forceinline__ void dft_fixed(c32 *v)
         t[2][2] = muli<S>(t[2][2]);
         t[2][3] = m(t[2][3], w23);
         t[3][1] = m(t[3][1], w13);
-        t[3][2] = m(t[3][2], w23);
+        t[3][2] = T32 ? my(t[3][2], w23) : m(t[3][2], w23);
         const c32 a = t[3][3];
         t[3][3] = c32{fmaf(a.x, w33.x, -(a.y * w33.y)), fmaf(a.x, w33.y, a.y * w33.x)};
 #pragma unroll

@@ -149,6 +149,17 @@ hipError_t launch_update_halo(void *field, const int64_t n[3], int64_t h, int64_
 hipError_t launch_gradient(const float *in, float *out, const int64_t n[3], int64_t h, int nc,
                            double dx, hipStream_t s);
 
+// x and y passes of whole z planes in one launch (lf2_kplane.hip): mode 0 c2c
+// (x then y for sign < 0, y then x for sign > 0), 1 r2c forward, 2 c2r
+// backward.  m: points of an x line, np: points of a k-space row, n2 planes;
+// x: the offsets and strides of the plane's rows on both sides.
+constexpr int kPlaneStages = 6;  // most factors of a line
+bool plane_axis_ok(int len);
+bool plane_axis_bits(int len, bool real_x);  // the bits of the two passes, forward
+size_t plane_lds_bytes(int m, int np, int nc, int n1);
+hipError_t launch_plane(int mode, int sign, const XArgs &x, int m, int np, int nc, int n1, int n2,
+                        const void *tw_y, hipStream_t s);
+
 // Setup and reduction kernels (FP64).
 hipError_t launch_twiddles(void *tw, int len, hipStream_t s);
 hipError_t launch_k2_table(double *dst, int n, int count, double dx, int discrete, hipStream_t s);

@@ -60,6 +60,8 @@ struct lf2_plan_s {
     // same (ragged_supported): its passes run them until a schedule is set
     // or the tuner finds one faster
     bool nat[3] = {false, false, false};
+    bool plane = false;      // x and y passes in one launch (plane_fits)
+    bool plane_bits = false; // and forward with the two passes' bits
     int gen_rb = 1;          // x tile rows of the run-time x kernels
     size_t lds_max = 65536;  // LDS bytes a block may use on the plan's device
     void *tw[3] = {nullptr, nullptr, nullptr};
@@ -78,6 +80,9 @@ namespace host {
 
 constexpr int kPkGrid = 1024;  // blocks of a binning pass (partials rows)
 constexpr int kStridedGridCap = 1 << 30;
+constexpr size_t kPlaneLds = 160 * 1024;  // most LDS of a plane kernel's block
+// Most floats of an x-space field whose planes run both axes in one launch.
+constexpr int64_t kPlaneFloats = 9 << 19;
 
 lf2_status fail(lf2_status st, const char *fmt, ...);
 
