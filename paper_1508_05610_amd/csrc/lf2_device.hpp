@@ -222,14 +222,16 @@ struct Dft<32, S> {
 // factor, or, where 3s and 5s are more than one, two adjacent ones
 // (r = r1 r2) in the same registers: each stage is an exchange through LDS
 // with two barriers, and the pair does what its two stages would, value by
-// value, without the exchange between them.  Pairs of at most 25 points
-// (registers) are joined so that the stages are fewest, and of those so that
-// the largest stage is smallest (360 -> 8*3,3*5; 900 -> 4*3,3*5,5).  A single
+// value, without the exchange between them.  Pairs are joined so that the
+// stages are fewest, and of those so that the largest stage is smallest
+// (360 -> 8*3,3*5; 900 -> 4*3,3*5,5); line_plan says how large they may be
+// (registers).  A single
 // 3 or 5 stays a stage of its own: joining it (192 as 8,8*3) made those
 // passes 0 to 14 % slower (320^3 forward: 163 -> 179 us), the longer
 // butterflies leaving too few per tile for its threads.
 constexpr int kMaxFactors = 12;
-constexpr int kMaxPair = 25;
+constexpr int kMaxPair = 25;   // largest pair (points) of a plain pass
+constexpr int kEpiPair = 16;   // and of the fused last-axis pass
 
 struct RadixPlan {
     int n;                 // stages
@@ -246,13 +248,13 @@ __host__ __device__ constexpr int fewest_stages(const RadixPlan &p, int i, int m
     if (i >= p.nf) return 0;
     if (p.f[i] > m) return 1 << 20;
     int best = 1 + fewest_stages(p, i + 1, m);
-    if (i + 1 < p.nf && p.f[i] * p.f[i + 1] <= m && p.f[i] * p.f[i + 1] <= kMaxPair) {
+    if (i + 1 < p.nf && p.f[i] * p.f[i + 1] <= m) {
         const int two = 1 + fewest_stages(p, i + 2, m);
         if (two < best) best = two;
     }
     return best;
 }
-__host__ __device__ constexpr RadixPlan radix_plan(int L)
+__host__ __device__ constexpr RadixPlan radix_plan(int L, int cap = kMaxPair)
 {
     RadixPlan p{};
     int a = 0;
@@ -269,9 +271,9 @@ __host__ __device__ constexpr RadixPlan radix_plan(int L)
         for (; p.n < p.nf; ++p.n) p.r[p.n] = p.r1[p.n] = p.f[p.n];
         return p;
     }
-    const int ns = fewest_stages(p, 0, kMaxPair);
+    const int ns = fewest_stages(p, 0, cap);
     int m = 2;
-    while (m < kMaxPair && fewest_stages(p, 0, m) > ns) ++m;
+    while (m < cap && fewest_stages(p, 0, m) > ns) ++m;
     for (int i = 0; i < p.nf;) {
         const bool pair = i + 1 < p.nf && p.f[i] * p.f[i + 1] <= m &&
                           p.n + 1 + fewest_stages(p, i + 2, m) == ns;
@@ -281,9 +283,70 @@ __host__ __device__ constexpr RadixPlan radix_plan(int L)
     }
     return p;
 }
+
+// Columns of a narrow strided tile: 64 KiB of LDS at most, >= 128-byte row
+// segments up to L = 512.
+__host__ __device__ constexpr int s_b(int L)
+{
+    return L <= 128 ? 64 : L <= 256 ? 32 : L <= 512 ? 16 : L <= 1024 ? 8 : 4;
+}
+
+constexpr int kSThreads = 512;  // most threads of a narrow strided tile
+
+// Points of work of a strided tile's line over the stages of p with nt
+// threads: each thread takes every js-th of the L / R butterflies of a stage,
+// js = nt / columns, so a stage costs ceil((L / R) / js) js R points.
+// Butterflies of more than 32 values a thread (registers) do not count.
+__host__ __device__ constexpr int s_work(int L, const RadixPlan &p, int nt)
+{
+    const int js = nt / s_b(L);
+    int w = 0;
+    for (int st = 0; st < p.n; ++st) {
+        const int nb = (L / p.r[st] + js - 1) / js;
+        if (nb * p.r[st] > 32) return 1 << 30;
+        w += nb * js * p.r[st];
+    }
+    return w;
+}
+// Threads of a strided tile: of the whole-wave counts up to 512 the one with
+// the least work over the stages, the larger one of equals.  Lines with at
+// most one factor of 3 or 5 take 512: powers of two divide evenly over them,
+// and the others (320, 384, ...) measured no faster with fewer.
+__host__ __device__ constexpr int s_threads(int L, const RadixPlan &p)
+{
+    if (L < 16 || p.nodd <= 1) return kSThreads;
+    int best = kSThreads, work = s_work(L, p, best);
+    for (int nt = kSThreads - 64; nt >= 128; nt -= 64) {
+        const int w = nt % s_b(L) == 0 ? s_work(L, p, nt) : work;
+        if (w < work) {
+            best = nt;
+            work = w;
+        }
+    }
+    return best;
+}
+
+// The plan of a line: pairs of at most CAP points, or of at most 16 where two
+// stages of larger pairs leave more than a fifth of the lanes idle (300 as
+// 12,25: 0.77 busy with its registers spilled, r2c y pass 57 us at 300^3; as
+// 12,5,5: 46).  Pairs of 24 and 25 points need 128 to 150 registers in a
+// plain pass and over 200 in the fused one, which then keeps two waves per
+// SIMD (216 as 24,9: 90 us at 360 x 300 x 216; as 8,9,3: 71): CAP is 16 there.
+template <int CAP>
+__host__ __device__ constexpr RadixPlan line_plan(int L)
+{
+    const RadixPlan p = radix_plan(L, CAP);
+    if (p.nodd <= 1 || CAP <= 16) return p;
+    return 5 * p.n * L < 4 * s_work(L, p, s_threads(L, p)) ? radix_plan(L, 16) : p;
+}
 // Evaluated once per length and translation unit.
+template <int L, int CAP = kMaxPair>
+inline constexpr RadixPlan kPlan = line_plan<CAP>(L);
+// Threads of the plain strided tile and of the fused last-axis one.
 template <int L>
-inline constexpr RadixPlan kPlan = radix_plan(L);
+inline constexpr int s_nt = s_threads(L, kPlan<L>);
+template <int L>
+inline constexpr int e_nt = s_threads(L, kPlan<L, kEpiPair>);
 
 // ------------------------------------------------------------ column engine
 // NL interleaved lines (columns of a strided pass), element (line l, point p)
@@ -712,15 +775,15 @@ __device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout,
 // order of the factors gives the same DFT; the reverse order lets a
 // transform start with the radix another one ended with (register hand-off
 // in the fused Poisson pass).
-template <int L>
+template <int L, int CAP>
 __host__ __device__ constexpr int radix_sel(int st, bool rev)
 {
-    return kPlan<L>.r[rev ? kPlan<L>.n - 1 - st : st];
+    return kPlan<L, CAP>.r[rev ? kPlan<L, CAP>.n - 1 - st : st];
 }
-template <int L>
+template <int L, int CAP>
 __host__ __device__ constexpr int radix1_sel(int st, bool rev)
 {
-    return kPlan<L>.r1[rev ? kPlan<L>.n - 1 - st : st];
+    return kPlan<L, CAP>.r1[rev ? kPlan<L, CAP>.n - 1 - st : st];
 }
 
 // Butterflies per thread of a column stage with Q = L / R butterflies per
@@ -816,7 +879,7 @@ __device__ __forceinline__ void col_stage_out(c32 *buf, c32 *gout, int64_t gs, b
 // REV runs the radices in reverse order; SKIP_LAST stops before the last
 // stage (whose inputs are then in LDS).
 template <int L, int S, int NL, int NT, bool SRC_G, bool DST_G, int ST = 0, int NS = 1,
-          bool NTM = false, bool REV = false, bool SKIP_LAST = false>
+          bool NTM = false, bool REV = false, bool SKIP_LAST = false, int CAP = kMaxPair>
 __device__ __forceinline__ void col_fft(c32 *buf, const c32 *gin, c32 *gout, int64_t gs, bool gv,
                                         const c32 *tw, int tid)
 {
@@ -832,12 +895,12 @@ __device__ __forceinline__ void col_fft(c32 *buf, const c32 *gin, c32 *gout, int
         }
         __syncthreads();
     } else if constexpr (NS < L) {
-        constexpr int R = radix_sel<L>(ST, REV), R1 = radix1_sel<L>(ST, REV);
+        constexpr int R = radix_sel<L, CAP>(ST, REV), R1 = radix1_sel<L, CAP>(ST, REV);
         constexpr bool first = ST == 0, last = NS * R == L;
         if constexpr (!(last && SKIP_LAST)) {
             col_stage<L, R, R1, NS, S, NL, NT, first && SRC_G, last && DST_G, NTM>(buf, gin, gout, gs,
                                                                                gv, tw, tid);
-            col_fft<L, S, NL, NT, SRC_G, DST_G, ST + 1, NS * R, NTM, REV, SKIP_LAST>(buf, gin, gout,
+            col_fft<L, S, NL, NT, SRC_G, DST_G, ST + 1, NS * R, NTM, REV, SKIP_LAST, CAP>(buf, gin, gout,
                                                                                     gs, gv, tw, tid);
         }
     }

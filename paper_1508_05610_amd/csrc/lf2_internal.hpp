@@ -113,7 +113,7 @@ hipError_t launch_strided_reg(int len, int sign, const SArgs &a, int grid_cap, h
 // nbins bins, when the block's LDS is `budget` bytes: one per wave if they
 // fit with the tile, else one.  0 if len has no compiled fused tile.
 // persistent: the persistent batch kernel's blocks of 512 threads (the others
-// have s_nt<len>).
+// have e_nt<len>).
 int epi_hist_copies(int len, int nbins, size_t budget, bool persistent = false);
 
 // Kernels of the lengths of LF2_RAGGED_LENGTHS (lf2_kx.hip, lf2_kragged.hip):

@@ -75,10 +75,10 @@ __global__ __launch_bounds__(s_nt<L>) __attribute__((amdgpu_waves_per_eu(4))) vo
 // z pass: forward * -1/(N k^2) * backward, with the tile's w|F|^2 bin sums
 // written to its own row of the field's partials.
 template <int L, int K2>
-__global__ __launch_bounds__(s_nt<L>) __attribute__((amdgpu_waves_per_eu(4))) void k_bz(
+__global__ __launch_bounds__(e_nt<L>) __attribute__((amdgpu_waves_per_eu(4))) void k_bz(
     const BatchField *fields, const BatchItem *items)
 {
-    using T = STile<L, -1, true, s_nt<L>, true, K2>;
+    using T = STile<L, -1, true, e_nt<L>, true, K2>;
     __shared__ __align__(16) char sm[T::BYTES];
     extern __shared__ double dyn[];  // hist[hcopies][nbins + 1], edges[nbins + 1]
     const int tid = threadIdx.x;
@@ -88,11 +88,11 @@ __global__ __launch_bounds__(s_nt<L>) __attribute__((amdgpu_waves_per_eu(4))) vo
     double *hist = dyn;
     BinEdge *edges = (BinEdge *)(dyn + F.z.hcopies * (nb + 1));
     T::tables(F.z, sm, tid);
-    if (nb > 0) hist_init(F.z.mt, F.z.hcopies, hist, edges, tid, s_nt<L>);
+    if (nb > 0) hist_init(F.z.mt, F.z.hcopies, hist, edges, tid, e_nt<L>);
     __syncthreads();
     [[clang::always_inline]] T::tile(F.z, it.tile, sm, tid, hist, edges);
     if (nb > 0)
-        hist_flush(nb, F.z.hcopies, hist, F.partial + (int64_t)it.tile * (nb + 1), tid, s_nt<L>);
+        hist_flush(nb, F.z.hcopies, hist, F.partial + (int64_t)it.tile * (nb + 1), tid, e_nt<L>);
 }
 
 // One block per field: fixed-order reduction of the z tiles' bin rows, then
@@ -442,10 +442,10 @@ hipError_t batch_group_launch(int pass, int len, const BatchField *fields,
             break;                                                                           \
         case BP_Z:                                                                           \
             if (k2cont)                                                                      \
-                hipLaunchKernelGGL((k_bz<L, 1>), dim3(nitems), dim3(s_nt<L>), zdyn, s,     \
+                hipLaunchKernelGGL((k_bz<L, 1>), dim3(nitems), dim3(e_nt<L>), zdyn, s,     \
                                    fields, items);                                           \
             else                                                                             \
-                hipLaunchKernelGGL((k_bz<L, 2>), dim3(nitems), dim3(s_nt<L>), zdyn, s,     \
+                hipLaunchKernelGGL((k_bz<L, 2>), dim3(nitems), dim3(e_nt<L>), zdyn, s,     \
                                    fields, items);                                           \
             break;                                                                           \
         case BP_YI:                                                                          \

@@ -29,7 +29,6 @@
 namespace lf2 {
 
 constexpr int kXThreads = 256;
-constexpr int kSThreads = 512;
 
 // Rows per x-pass tile: about 4096 * (NT / 256) complex values of LDS, at
 // most 256 rows.
@@ -39,49 +38,6 @@ __host__ __device__ constexpr int x_rb(int L, int NC, int NT = kXThreads)
                ? 1
                : (((4096 / L) / NC * (NT / 256)) > 256 ? 256 : ((4096 / L) / NC * (NT / 256)));
 }
-// Columns per strided tile: 64 KiB of LDS at most, >= 128-byte row segments
-// up to L = 512.
-__host__ __device__ constexpr int s_b(int L)
-{
-    return L <= 128 ? 64 : L <= 256 ? 32 : L <= 512 ? 16 : L <= 1024 ? 8 : 4;
-}
-
-
-// Threads of a strided tile of lines of L points.  Each thread takes every
-// JS-th of the L / R butterflies of a stage, JS = threads / columns, so a
-// stage costs ceil((L / R) / JS) JS R points of work: of the whole-wave
-// counts up to 512 whose butterflies fit 32 registers of values, the one
-// with the least work over the stages, the larger one of equals.  Lines with
-// at most one factor of 3 or 5 take 512: powers of two divide evenly over
-// them, and the others (320, 384, ...) measured no faster with fewer.
-__host__ __device__ constexpr int s_work(int L, const RadixPlan &p, int nt)
-{
-    const int js = nt / s_b(L);
-    int w = 0;
-    for (int st = 0; st < p.n; ++st) {
-        const int nb = (L / p.r[st] + js - 1) / js;
-        if (nb * p.r[st] > 32) return 1 << 30;
-        w += nb * js * p.r[st];
-    }
-    return w;
-}
-__host__ __device__ constexpr int s_threads(int L)
-{
-    const RadixPlan p = radix_plan(L);
-    if (L < 16 || p.nodd <= 1) return kSThreads;
-    int best = kSThreads, work = s_work(L, p, best);
-    for (int nt = kSThreads - 64; nt >= 128; nt -= 64) {
-        const int w = nt % s_b(L) == 0 ? s_work(L, p, nt) : work;
-        if (w < work) {
-            best = nt;
-            work = w;
-        }
-    }
-    return best;
-}
-template <int L>
-inline constexpr int s_nt = s_threads(L);
-
 __host__ __device__ constexpr size_t al16(size_t b) { return (b + 15) & ~(size_t)15; }
 
 // LDS bytes of a narrow strided tile: its columns and the twiddle table.
@@ -833,8 +789,9 @@ struct STile {
     // j + r L/R0 of the thread's column (radix R0), all loads issued before
     // any of them is used (a column past the end loads column 0 and is
     // zeroed).
-    static constexpr int R0 = kPlan<L>.n == 0 ? 1 : kPlan<L>.r[0];
-    static constexpr int R01 = kPlan<L>.n == 0 ? 1 : kPlan<L>.r1[0];
+    static constexpr RadixPlan PL = kPlan<L, kEpiPair>;  // of the fused pass
+    static constexpr int R0 = PL.n == 0 ? 1 : PL.r[0];
+    static constexpr int R01 = PL.n == 0 ? 1 : PL.r1[0];
     static constexpr int NB0 = col_nb(L, R0, B, NT);
     struct In {
         c32 v[NB0][R0];
@@ -921,9 +878,9 @@ struct STile {
                                                     bool valid, bool store, c32 *gout,
                                                     double *hist, const BinEdge *edges, In &in)
     {
-        constexpr int NST = kPlan<L>.n;
-        constexpr int RL = NST == 0 ? 1 : kPlan<L>.r[NST - 1];
-        constexpr int RL1 = NST == 0 ? 1 : kPlan<L>.r1[NST - 1];
+        constexpr int NST = PL.n;
+        constexpr int RL = NST == 0 ? 1 : PL.r[NST - 1];
+        constexpr int RL1 = NST == 0 ? 1 : PL.r1[NST - 1];
         constexpr int QL = L / RL;
         constexpr int NB = col_nb(L, RL, B, NT);
         const int j0 = tid / B;
@@ -939,7 +896,7 @@ struct STile {
                 for (int r = 0; r < RL; ++r) v[i][r] = in.v[i][r];
         } else {
             col_stage_out<L, R0, 1, B, NT, false>(buf, nullptr, 0, false, tid, in.v);
-            col_fft<L, S, B, NT, false, false, 1, R0, NTM, false, true>(buf, nullptr, nullptr, 0,
+            col_fft<L, S, B, NT, false, false, 1, R0, NTM, false, true, kEpiPair>(buf, nullptr, nullptr, 0,
                                                                       false, tw, tid);
             col_stage_in<L, RL, RL1, QL, S, B, NT, false>(buf, nullptr, 0, false, tw, tid, v);
         }
@@ -986,7 +943,7 @@ struct STile {
                                                               tid, v);
                 } else {
                     col_stage_out<L, RL, 1, B, NT, false>(buf, nullptr, 0, false, tid, v);
-                    col_fft<L, +1, B, NT, false, true, 1, RL, NTM, true>(
+                    col_fft<L, +1, B, NT, false, true, 1, RL, NTM, true, false, kEpiPair>(
                         buf, nullptr, gout, a.stride, valid && store, tw, tid);
                 }
                 return;
@@ -1231,10 +1188,10 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2c_v(XArgs a)
 // fused pass's LDS tables leave room for one block (lines of 1024 points and
 // more), where two waves per SIMD are all it can reach.
 template <int L, int S, bool EPI, bool NTM = false, int K2 = 0>
-__global__ __launch_bounds__(s_nt<L>)
+__global__ __launch_bounds__(EPI ? e_nt<L> : s_nt<L>)
     __attribute__((amdgpu_waves_per_eu(EPI && L >= 1024 ? 2 : 4))) void k_strided(SArgs a)
 {
-    constexpr int NT = s_nt<L>;
+    constexpr int NT = EPI ? e_nt<L> : s_nt<L>;
     using T = STile<L, S, EPI, NT, NTM, K2>;
     constexpr int B = T::B;
     __shared__ __align__(16) char sm[T::BYTES];

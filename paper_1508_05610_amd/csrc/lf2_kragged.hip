@@ -37,10 +37,10 @@ hipError_t ragged_strided_b(
 #define LF2_CASE(L)                                                                          \
     case L:                                                                                  \
         if (epi && a.mt.k2z_unit > 0.0)                                                      \
-            hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(grid), dim3(s_nt<L>), \
+            hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(grid), dim3(e_nt<L>), \
                                shm, s, a);                                                   \
         else if (epi)                                                                        \
-            hipLaunchKernelGGL((k_strided<L, -1, true, true, 2>), dim3(grid), dim3(s_nt<L>), \
+            hipLaunchKernelGGL((k_strided<L, -1, true, true, 2>), dim3(grid), dim3(e_nt<L>), \
                                shm, s, a);                                                   \
         else if (ntm)                                                                        \
             plain<L, true>(sign, grid, a, s);                                                \

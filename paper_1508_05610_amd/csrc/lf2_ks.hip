@@ -35,7 +35,7 @@ int epi_hist_copies(int len, int nbins, size_t budget, bool persistent)
     switch (len) {
 #define LF2_CASE(L)                                                                          \
     case L: {                                                                                \
-        const int waves = (persistent ? kSThreads : s_nt<L>) / 64;                           \
+        const int waves = (persistent ? kSThreads : e_nt<L>) / 64;                           \
         const size_t tile = s_bytes(L);                                                      \
         return tile + (size_t)(nbins + 1) * 8 * (waves + 1) <= budget ? waves : 1;           \
     }
@@ -177,10 +177,10 @@ hipError_t launch_strided(int len, int sign, const SArgs &a_in, int grid_cap, hi
         int g = (int)(span < grid_cap ? span : grid_cap);                                    \
         if (grid_used) *grid_used = g;                                                       \
         if (epi && sign < 0 && a.mt.k2z_unit > 0.0)                                          \
-            hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(g), dim3(s_nt<L>), shm,  \
+            hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(g), dim3(e_nt<L>), shm,  \
                                s, a);                                                        \
         else if (epi && sign < 0)                                                            \
-            hipLaunchKernelGGL((k_strided<L, -1, true, true, 2>), dim3(g), dim3(s_nt<L>), shm,  \
+            hipLaunchKernelGGL((k_strided<L, -1, true, true, 2>), dim3(g), dim3(e_nt<L>), shm,  \
                                s, a);                                                        \
         else if (epi)                                                                        \
             return hipErrorInvalidValue;                                                     \

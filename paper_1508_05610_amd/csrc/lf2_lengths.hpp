@@ -5,8 +5,8 @@
 // then it runs the compiled narrow tiles of these lengths, whose divisions,
 // twiddle strides and unrolled stages are constants and whose first and last
 // stages load and store memory from registers.  A 360 x 300 x 216 Poisson
-// solve: 671 us with run-time schedules, 283 us compiled; the r2c pair of a
-// 240 x 180 x 150 x 3 field with halo 1: 580 and 222 us; cubes of 30 to 480
+// solve: 671 us with run-time schedules, 238 us compiled; the r2c pair of a
+// 240 x 180 x 150 x 3 field with halo 1: 580 and 219 us; cubes of 30 to 480
 // points 1.5 to 3.4 times faster, none slower.  Two lists of about equal
 // compile time.
 #pragma once
