@@ -137,7 +137,11 @@ lf2_status lf2_fft_kspace(lf2_plan p, int64_t ksize[3], int64_t kstride[3]);
  * LDS); bit 1:
  * nontemporal global loads and stores (they pay on long strides, where each
  * line is touched once).  chunk = consecutive tiles given to one XCD in the
- * tile order (1..1024, default 16).  Narrow and wide tiles compute the same
+ * tile order (1..1024, default 16).  The default variant depends on the
+ * line length, the spectrum's bytes and its strides (0 below 64 MB and on
+ * most larger lattices), and the backward z pass of a large spectrum may
+ * default to nontemporal accesses where the forward one does not (get reports
+ * the forward one, set sets both).  Narrow and wide tiles compute the same
  * transform bit for bit; the register tile computes it up to FP32 rounding
  * (another order of the butterflies).  The fused Poisson / power-spectrum pass always uses narrow tiles,
  * nontemporal accesses and chunk 16.  get reports the setting and, after

@@ -225,6 +225,42 @@ bool plane_fits(const lf2_plan_s *p)
            (p->n[2] < 256 ? (size_t)128 * 1024 : kPlaneLds);
 }
 
+// Tile settings of the y and z passes until one is set or tuned.  Narrow
+// tiles with normal accesses, except where another setting measured faster
+// (us a pass, forward / backward):
+//  - y lines of 768 points and more: wide tiles, whose row segments the
+//    narrow ones' 64 bytes cut a cache line short (768^3 real 960 / 947 ->
+//    859 / 839, 1024^3 real 2140 / 2104 -> 1905 / 1832; 640^3 474 -> 482);
+//  - z lines of a spectrum past the memory-side cache (256 MB): register
+//    tiles, nontemporal, over 1024 and 2048 points (1024^3 real 2152 / 2016 ->
+//    1800 / 1770); wide nontemporal ones over 640 and 768 points (768^3 real
+//    966 / 932 -> 912 / 846) and over 512 points where the rows' stride is a
+//    multiple of 64 KB, so that a tile's rows fall on few memory channels
+//    (512^3 complex 596 / 577 -> 434 / 426);
+//  - the other backward z passes of lines of 320 points and more, which read
+//    a spectrum not written just before, from 430 MB on: nontemporal (512^3
+//    real 235 -> 215, 384^3 complex 206 -> 178; 384^3 real, 226 MB, 93 -> 101).
+// Narrow and wide tiles give the same bits; so P(k), which no plain z pass
+// feeds, does not depend on these.
+void default_tiles(lf2_plan_s *p)
+{
+    const size_t bytes = spectrum_bytes(p);
+    const int ly = p->len[1], lz = p->len[2];
+    if (!p->gen_only[1] && ly >= 768 && s_wide_supported(ly) && bytes > ((size_t)64 << 20))
+        p->svar[1] = p->svar_b[1] = 1;
+    if (bytes <= ((size_t)256 << 20) || p->klay == 2) return;
+    const int64_t stride = 8 * (p->klay == 1 ? p->nxk * p->nc : p->nxk * p->nc * p->n[1]);
+    if (p->gen_only[2]) {
+        if (p->nat[2] && lz >= 320 && bytes > ((size_t)430 << 20)) p->svar_b[2] = 2;
+    } else if (s_reg_supported(lz)) {
+        p->svar[2] = p->svar_b[2] = 6;
+    } else if (lz == 640 || lz == 768 || (lz == 512 && stride % 65536 == 0)) {
+        p->svar[2] = p->svar_b[2] = 3;
+    } else if (lz >= 320 && bytes > ((size_t)430 << 20)) {
+        p->svar_b[2] = 2;
+    }
+}
+
 // Workspace layout: [W spectrum][pk partials][sums][sumsq partials][sumsq];
 // the results of the two reductions go straight to the caller's arrays, and
 // their places stay so that the size a caller planned for does not change.
@@ -556,7 +592,7 @@ lf2_status run_strided(const lf2_plan_s *p, int axis, int sign, const SArgs &a, 
     const bool freg = epi && sign < 0 && (a.epi & EPI_POISSON) && p->fvar == 1 &&
                       fused_reg_supported(p->len[axis]) &&
                       fused_reg_fits(p->len[axis], (a.epi & (EPI_PK | EPI_PK_AFTER)) ? a.mt.nbins : 0);
-    const int variant = tr ? 0 : epi ? (freg ? 8 : 0) : p->svar[axis];
+    const int variant = tr ? 0 : epi ? (freg ? 8 : 0) : sign < 0 ? p->svar[axis] : p->svar_b[axis];
     const int ntm = ((variant & 2) || epi) ? 1 : 0;  // the fused pass always streams
     int t = -1;
     if (prof::active()) {
@@ -927,7 +963,7 @@ lf2_status autotune(lf2_plan p)
                     // that timing noise does not flip the choice from run to run
                     if (best < 0 || t[i] < 0.97 * best) {
                         best = t[i];
-                        p->svar[axis] = cfg[i].first;
+                        p->svar[axis] = p->svar_b[axis] = cfg[i].first;
                         p->schunk[axis] = cfg[i].second;
                     }
                 }
@@ -1053,6 +1089,7 @@ lf2_status lf2_fft_plan(lf2_plan *out, const lf2_lattice *lat, int32_t ncomp, lf
         int64_t a = (p->n[i] / 2) * (p->lcm / p->n[i]);
         p->qmax += a * a;
     }
+    default_tiles(p);
     p->plane = plane_fits(p);
     p->plane_bits = p->plane && plane_axis_bits(p->len[0], kind == LF2_R2C) &&
                     plane_axis_bits(p->len[1], false);
@@ -1202,7 +1239,7 @@ lf2_status lf2_plan_set_tuning(lf2_plan p, int32_t axis, int32_t variant, int32_
     if ((variant & 4) && ((variant & 1) || !s_reg_supported(p->len[axis])))
         return fail(LF2_ERR_UNSUPPORTED, "no register tile for line length %d (or with wide tiles)",
                     p->len[axis]);
-    p->svar[axis] = variant;
+    p->svar[axis] = p->svar_b[axis] = variant;
     p->schunk[axis] = chunk;
     p->gen[axis] = false;  // the compiled kernels again
     if (axis == 1) p->plane = false;  // the pass that was asked for
