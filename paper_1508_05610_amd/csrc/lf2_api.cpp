@@ -1091,8 +1091,9 @@ lf2_status lf2_fft_plan(lf2_plan *out, const lf2_lattice *lat, int32_t ncomp, lf
     }
     default_tiles(p);
     p->plane = plane_fits(p);
-    p->plane_bits = p->plane && plane_axis_bits(p->len[0], kind == LF2_R2C) &&
-                    plane_axis_bits(p->len[1], false);
+    p->plane_bits = p->plane &&
+                    plane_axis_bits(p->len[0], kind == LF2_R2C ? PLANE_X_REAL : PLANE_X_COMPLEX) &&
+                    plane_axis_bits(p->len[1], PLANE_Y);
     hipStream_t s = nullptr;
     lf2_status st = LF2_OK;
     // the fused binning evaluates the bin rule in 32 x 32 -> 64-bit products
@@ -1547,7 +1548,7 @@ lf2_status lf2_power_spectrum(lf2_plan p, const void *field, int32_t field_is_ks
         void *W = ws + L.w;
         const int which = p->kind == LF2_R2C ? 0 : 2;
         const XArgs xa = x_args(p, field, W, true, false, which == 0);
-        if ((st = run_xy(p, which, -1, xa, W, s, p->plane_bits))) return st;
+        if ((st = run_xy(p, which, -1, xa, W, s, p->plane && p->plane_bits))) return st;
         SArgs za = s_args(p, 2, W, W, EPI_PK);
         use_shell(za.mt, sh);
         za.partial = part;

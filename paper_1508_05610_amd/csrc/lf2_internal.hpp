@@ -155,7 +155,8 @@ hipError_t launch_gradient(const float *in, float *out, const int64_t n[3], int6
 // x: the offsets and strides of the plane's rows on both sides.
 constexpr int kPlaneStages = 6;  // most factors of a line
 bool plane_axis_ok(int len);
-bool plane_axis_bits(int len, bool real_x);  // the bits of the two passes, forward
+enum PlaneAxis { PLANE_X_REAL, PLANE_X_COMPLEX, PLANE_Y };
+bool plane_axis_bits(int len, PlaneAxis axis);  // the bits of the two passes, forward
 size_t plane_lds_bytes(int m, int np, int nc, int n1);
 hipError_t launch_plane(int mode, int sign, const XArgs &x, int m, int np, int nc, int n1, int n2,
                         const void *tw_y, hipStream_t s);

@@ -377,14 +377,17 @@ bool plane_axis_ok(int len)
 // Forward, a stage rounds as the two passes' stage does (twiddle_mul,
 // dft_fixed) except where the compiler chose otherwise there: on
 // run-time-schedule lines always; on compiled ones not the 16-point
-// butterfly (real x lines of 16 points excepted) nor, on complex lines, the
-// 5-point one.
-bool plane_axis_bits(int len, bool real_x)
+// butterfly (real x lines of 16 points excepted) nor, on y and complex x
+// lines, the 5-point one; and not on compiled complex x lines of two stages
+// and more, whose last twiddles it rounds one way in some of a thread's
+// butterflies and another way in others.
+bool plane_axis_bits(int len, PlaneAxis axis)
 {
     const RadixPlan p = radix_plan(len);
     if (p.nodd > 1) return true;
     const bool f16 = p.f[0] == 16, f5 = p.f[p.nf - 1] == 5;
-    return real_x ? !f16 || len == 16 : !f16 && !f5;
+    if (axis == PLANE_X_REAL) return !f16 || len == 16;
+    return !f16 && !f5 && (axis == PLANE_Y || p.nf == 1);
 }
 
 hipError_t launch_plane(int mode, int sign, const XArgs &x, int m, int np, int nc, int n1, int n2,
