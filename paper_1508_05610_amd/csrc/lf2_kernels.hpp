@@ -339,8 +339,7 @@ struct XC2RGen {
 // fe = (Z[k] + conj Z[M-k]) / 2, fo = (Z[k] - conj Z[M-k]) / (2i).
 template <int M, int NT>
 struct XR2CV {
-    // LDS lines hold the M packed points, then the NH = M + 1 output bins
-    static constexpr int RB = x_rb(M, 1, NT), LP = row_pitch(M + 1), NH = M + 1, HALF = M / 2 + 1;
+    static constexpr int RB = x_rb(M, 1, NT), LP = row_pitch(M), NH = M + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * RB * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
                             O_IB = al16(O_TWP + sizeof(c32) * NH), O_OB = O_IB + 8 * RB,
@@ -350,17 +349,18 @@ struct XR2CV {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
+    // TAB: the tile loads the tables too, behind its own first loads.
+    template <bool TAB = false>
     static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
         int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
         const int64_t r0 = blk * RB;
-        row_bases<RB, NT>(ib, ob, a, r0, tid);
-        __syncthreads();
         const int nv = rows_valid<RB>(a, r0);
         double ss = 0.0;
-        const float *src = (const float *)a.in + ib[0];
+        const bool dense_out = a.out_row == NH && a.out_plane == (int64_t)a.n1 * NH;
+        const float *src = (const float *)a.in + a.in_off + r0 * (2 * M);
         if (M % 2 == 0 && a.in_row == 2 * M && a.in_plane == (int64_t)a.n1 * 2 * M &&
             ((uintptr_t)src & 15) == 0) {
             // Dense rows: the tile is one contiguous run of nv N0 reals, read
@@ -380,6 +380,8 @@ struct XR2CV {
                 const int e = tid + i * NT;
                 if (e < np) w[i] = __builtin_nontemporal_load(s4 + e);
             }
+            if (TAB) tables(a, sm, tid);
+            if (!dense_out) row_bases<RB, NT>(ib, ob, a, r0, tid);
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
                 const int e = tid + i * NT;
@@ -396,52 +398,39 @@ struct XR2CV {
             row_fft<M, -1, RB, 1, LP, NT, false, false>(buf, nullptr, nullptr, nullptr, nullptr, nv,
                                                         tw, tid);
         } else {
+            if (TAB) tables(a, sm, tid);
+            row_bases<RB, NT>(ib, ob, a, r0, tid);
             for (int i = tid; i < RB; i += NT) ib[i] >>= 1;  // float offset -> complex offset
             __syncthreads();
             row_fft<M, -1, RB, 1, LP, NT, true, false, 0, 1, true>(
                 buf, (const c32 *)a.in, nullptr, ib, nullptr, nv, tw, tid, sumsq ? &ss : nullptr);
         }
         if (sumsq) block_sum_f64<NT>(ss, sumsq, (double *)(sm + O_RED));
-        // bins of every line in place: the thread of pair (k, M - k) reads
-        // and writes only those two slots (k = 0 writes X[M] to slot M)
-        constexpr int NI = RB * HALF;
-#pragma unroll
-        for (int i = 0; i < (NI + NT - 1) / NT; ++i) {
-            const int idx = tid + i * NT;
-            if (idx < NI) {
-                const int l = idx / HALF;
-                const int k = idx - l * HALF;
-                if (l < nv) {
-                    c32 *line = buf + l * LP;
-                    const c32 z = line[lpad(k)];
-                    const c32 zc = conjg(line[lpad(k == 0 ? 0 : M - k)]);
-                    const c32 fe = scl(add(z, zc), 0.5f);
-                    const c32 d = sub(z, zc);
-                    const c32 fo = c32{0.5f * d.y, -0.5f * d.x};
-                    const c32 wf = mul(twp[k], fo);
-                    line[lpad(k)] = add(fe, wf);
-                    if (2 * k != M) line[lpad(M - k)] = conjg(sub(fe, wf));
-                }
-            }
-        }
-        __syncthreads();
+        // The store forms the bins from the points as it reads them: bin k of
+        // line l from Z[k] and Z[M - k], indices mod M.
         c32 *out = (c32 *)a.out;
-        auto bin = [&](int e) {  // value e of the tile's output rows, row-major
-            const int l = e / NH;
-            return buf[l * LP + lpad(e - l * NH)];
+        auto bin = [&](int l, int k) {
+            const c32 *line = buf + l * LP;
+            const c32 z = line[lpad(k == M ? 0 : k)];
+            const c32 zc = conjg(line[lpad(k == 0 || k == M ? 0 : M - k)]);
+            const c32 fe = scl(add(z, zc), 0.5f);
+            const c32 d = sub(z, zc);
+            return add(fe, mul(twp[k], c32{0.5f * d.y, -0.5f * d.x}));
         };
-        if (a.out_row == NH && a.out_plane == (int64_t)a.n1 * NH) {
+        if (dense_out) {
             // dense half spectrum: the tile's rows are one contiguous run,
             // written with 16-byte nontemporal stores from the first 16-byte
             // boundary on
             typedef float nf4 __attribute__((ext_vector_type(4)));
-            c32 *dst = out + ob[0];
+            c32 *dst = out + a.out_off + r0 * NH;
             const int cnt = nv * NH;
             const int e0 = ((uintptr_t)dst & 15) ? 1 : 0;
             const int np = (cnt - e0) / 2;
             nf4 *d4 = (nf4 *)(dst + e0);
             for (int e = tid; e < np; e += NT) {
-                const c32 u = bin(e0 + 2 * e), w = bin(e0 + 2 * e + 1);
+                const int f = e0 + 2 * e, l = f / NH, k = f - l * NH;
+                const bool wrap = k == M;
+                const c32 u = bin(l, k), w = bin(wrap ? l + 1 : l, wrap ? 0 : k + 1);
                 nf4 v;
                 v.x = u.x;
                 v.y = u.y;
@@ -449,12 +438,12 @@ struct XR2CV {
                 v.w = w.y;
                 __builtin_nontemporal_store(v, d4 + e);
             }
-            if (tid == 0 && e0 && cnt > 0) gstore<true>(dst, bin(0));
-            if (tid == 0 && e0 + 2 * np < cnt) gstore<true>(dst + (cnt - 1), bin(cnt - 1));
+            if (tid == 0 && e0 && cnt > 0) gstore<true>(dst, bin(0, 0));
+            if (tid == 0 && e0 + 2 * np < cnt) gstore<true>(dst + (cnt - 1), bin(nv - 1, M));
         } else {
             for (int e = tid; e < nv * NH; e += NT) {
-                const int l = e / NH;
-                gstore<true>(out + ob[l] + (e - l * NH), bin(e));
+                const int l = e / NH, k = e - l * NH;
+                gstore<true>(out + ob[l] + k, bin(l, k));
             }
         }
         __syncthreads();
@@ -1161,8 +1150,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_r2c_v(XArgs a)
 {
     using T = XR2CV<M, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::tables(a, sm, threadIdx.x);
-    T::tile(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr);
+    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr);
 }
 
 template <int M>
