@@ -551,9 +551,17 @@ __device__ __forceinline__ void dft_first(c32 (&v)[R], const c32 *tw)
         Dft<R, S>::run(v);
 }
 
-template <int L, int R, int R1, int NS, int S, int NL, int NT, bool SRC_G, bool DST_G, bool NTM = false>
+// A first stage's hooks: on each value it loads from memory (row engine),
+// and between its loads and its butterflies.
+struct NoHook {
+    __device__ __forceinline__ void value(c32) const {}
+    __device__ __forceinline__ void loaded() const {}
+};
+
+template <int L, int R, int R1, int NS, int S, int NL, int NT, bool SRC_G, bool DST_G, bool NTM = false,
+          class Hook = NoHook>
 __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, int64_t gs,
-                                          bool gv, const c32 *tw, int tid)
+                                          bool gv, const c32 *tw, int tid, Hook hook = {})
 {
     constexpr int Q = L / R;
     constexpr int JS = NT / NL;
@@ -575,6 +583,7 @@ __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, i
             }
         }
     }
+    hook.loaded();
     if (!SRC_G && !DST_G) __syncthreads();
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -608,7 +617,7 @@ __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, i
 
 // ------------------------------------------------------------ row engine
 // RB rows of NC interleaved components (the x pass): component c of point p
-// of row q sits at global offset rowoff[q] + p * NC + c and at
+// of row q sits at global offset at(q) + p * NC + c (RowAt) and at
 // buf[(q * NC + c) * LP + lpad(p)] in LDS (one LDS line per row and
 // component).  lpad inserts one empty slot after every 16 points, so the
 // stride-R writes of the early Stockham stages (points j R + r over
@@ -623,6 +632,39 @@ __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, i
 // array with row offsets in floats, and point p of component c is the pair
 // (f[2p][c], f[2p + 1][c]) = floats (2p) NC + c and (2p + 1) NC + c, loaded
 // (first stage) or stored (last stage) as two floats.
+
+// Element offset of row q of a tile: rows y0 + q of plane z0 on, n1 rows a
+// plane.  Where planes follow each other like rows (flat), a multiply;
+// computed where it is used, since a table of them in LDS had to be filled
+// and waited for before a tile's first load.
+struct RowAt {
+    int64_t base, row, plane;
+    uint32_t y0, n1;
+    bool flat;
+    __device__ __forceinline__ int64_t operator()(int q) const
+    {
+        if (flat) return base + (int64_t)q * row;
+        const uint32_t y = y0 + (uint32_t)q, dz = y / n1;
+        return base + (int64_t)dz * plane + (int64_t)(y - dz * n1) * row;
+    }
+};
+// The same from a table in LDS.
+struct RowTable {
+    const int64_t *at;
+    __device__ __forceinline__ int64_t operator()(int q) const { return at[q]; }
+};
+__device__ __forceinline__ RowAt row_at(int64_t off, int64_t row, int64_t plane, int n1, int64_t r0)
+{
+    RowAt a;
+    const uint32_t z0 = (uint32_t)r0 / (uint32_t)n1;  // fewer than 2^31 rows
+    a.row = row;
+    a.plane = plane;
+    a.n1 = (uint32_t)n1;
+    a.y0 = (uint32_t)r0 - z0 * a.n1;
+    a.flat = plane == row * n1;
+    a.base = off + (int64_t)z0 * plane + (a.flat ? (int64_t)a.y0 * row : 0);
+    return a;
+}
 
 __host__ __device__ constexpr int lpad(int p) { return p + (p >> 4); }
 __host__ __device__ constexpr int row_pitch(int npoints) { return lpad(npoints - 1) + 1; }
@@ -646,10 +688,10 @@ __device__ __forceinline__ void gstoref(float *p, float v)
 }
 
 template <int L, int R, int R1, int NS, int S, int RB, int NC, int LP, int NT, bool SRC_G, bool DST_G,
-          bool NTM = false, bool PACK = false>
-__device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
-                                          const int64_t *rowoff_in, const int64_t *rowoff_out,
-                                          int nvalid, const c32 *tw, int tid, double *ssq)
+          bool NTM = false, bool PACK = false, class At, class Hook = NoHook>
+__device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout, const At &in_at,
+                                          const At &out_at, int nvalid, const c32 *tw, int tid,
+                                          Hook hook = {})
 {
     constexpr int Q = L / R;
     constexpr int NBF = RB * NC * Q;
@@ -663,26 +705,27 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
             const int c = b % NC, t = b / NC;
             const int j = t % Q, q = t / Q;
             const int l = q * NC + c;
+            const int64_t at = SRC_G ? in_at(q) : 0;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (SRC_G && PACK) {
-                    const float *fp = (const float *)gin + rowoff_in[q] + 2 * (j + r * Q) * NC + c;
+                    const float *fp = (const float *)gin + at + 2 * (j + r * Q) * NC + c;
                     v[i][r] = q < nvalid ? c32{gloadf<NTM>(fp), gloadf<NTM>(fp + NC)}
                                          : c32{0.f, 0.f};
                 } else if (SRC_G) {
-                    v[i][r] = q < nvalid ? gload<NTM>(gin + rowoff_in[q] + (j + r * Q) * NC + c)
+                    v[i][r] = q < nvalid ? gload<NTM>(gin + at + (j + r * Q) * NC + c)
                                          : c32{0.f, 0.f};
                 } else {
                     v[i][r] = buf[l * LP + lpad(j + r * Q)];
                 }
             }
-            if (SRC_G && ssq) {
+            if (SRC_G) {
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    *ssq += (double)v[i][r].x * v[i][r].x + (double)v[i][r].y * v[i][r].y;
+                for (int r = 0; r < R; ++r) hook.value(v[i][r]);
             }
         }
     }
+    hook.loaded();
     if (!SRC_G && !DST_G) __syncthreads();
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -692,6 +735,7 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
             const int j = t % Q, q = t / Q;
             const int l = q * NC + c;
             const int k = j % NS;
+            const int64_t at = DST_G ? out_at(q) : 0;
             if constexpr (kPaired<L>) {
                 butterfly<L, R, R1, NS, S>(v[i], k, tw);
             } else {
@@ -709,7 +753,7 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
                 if (q < nvalid) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        float *fp = (float *)gout + rowoff_out[q] + 2 * (j + r * Q) * NC + c;
+                        float *fp = (float *)gout + at + 2 * (j + r * Q) * NC + c;
                         gstoref<NTM>(fp, v[i][r].x);
                         gstoref<NTM>(fp + NC, v[i][r].y);
                     }
@@ -718,7 +762,7 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
                 if (q < nvalid) {
 #pragma unroll
                     for (int r = 0; r < R; ++r)
-                        gstore<NTM>(gout + rowoff_out[q] + (j + r * Q) * NC + c, v[i][r]);
+                        gstore<NTM>(gout + at + (j + r * Q) * NC + c, v[i][r]);
                 }
             } else {
                 c32 *dst = buf + l * LP;
@@ -732,30 +776,31 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout,
 }
 
 template <int L, int S, int RB, int NC, int LP, int NT, bool SRC_G, bool DST_G, int ST = 0,
-          int NS = 1, bool NTM = false, bool PACK = false>
-__device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout,
-                                        const int64_t *rowoff_in, const int64_t *rowoff_out,
-                                        int nvalid, const c32 *tw, int tid, double *ssq = nullptr)
+          int NS = 1, bool NTM = false, bool PACK = false, class At, class Hook = NoHook>
+__device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout, const At &in_at,
+                                        const At &out_at, int nvalid, const c32 *tw, int tid,
+                                        Hook hook = {})
 {
     if constexpr (L == 1) {
+        hook.loaded();
         for (int b = tid; b < RB * NC; b += NT) {
             const int c = b % NC, q = b / NC;
             c32 v = buf[b * LP];
             if (SRC_G && PACK) {
-                const float *fp = (const float *)gin + rowoff_in[q] + c;
+                const float *fp = (const float *)gin + in_at(q) + c;
                 v = q < nvalid ? c32{fp[0], fp[NC]} : c32{0.f, 0.f};
             } else if (SRC_G) {
-                v = q < nvalid ? gin[rowoff_in[q] + c] : c32{0.f, 0.f};
+                v = q < nvalid ? gin[in_at(q) + c] : c32{0.f, 0.f};
             }
-            if (SRC_G && ssq) *ssq += (double)v.x * v.x + (double)v.y * v.y;
+            if (SRC_G) hook.value(v);
             if (DST_G && PACK) {
                 if (q < nvalid) {
-                    float *fp = (float *)gout + rowoff_out[q] + c;
+                    float *fp = (float *)gout + out_at(q) + c;
                     fp[0] = v.x;
                     fp[NC] = v.y;
                 }
             } else if (DST_G) {
-                if (q < nvalid) gout[rowoff_out[q] + c] = v;
+                if (q < nvalid) gout[out_at(q) + c] = v;
             } else {
                 buf[b * LP] = v;
             }
@@ -765,9 +810,9 @@ __device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout,
         constexpr int R = kPlan<L>.r[ST], R1 = kPlan<L>.r1[ST];
         constexpr bool first = ST == 0, last = NS * R == L;
         row_stage<L, R, R1, NS, S, RB, NC, LP, NT, first && SRC_G, last && DST_G, NTM, PACK>(
-            buf, gin, gout, rowoff_in, rowoff_out, nvalid, tw, tid, ssq);
+            buf, gin, gout, in_at, out_at, nvalid, tw, tid, hook);
         row_fft<L, S, RB, NC, LP, NT, SRC_G, DST_G, ST + 1, NS * R, NTM, PACK>(
-            buf, gin, gout, rowoff_in, rowoff_out, nvalid, tw, tid, ssq);
+            buf, gin, gout, in_at, out_at, nvalid, tw, tid);
     }
 }
 
@@ -879,11 +924,13 @@ __device__ __forceinline__ void col_stage_out(c32 *buf, c32 *gout, int64_t gs, b
 // REV runs the radices in reverse order; SKIP_LAST stops before the last
 // stage (whose inputs are then in LDS).
 template <int L, int S, int NL, int NT, bool SRC_G, bool DST_G, int ST = 0, int NS = 1,
-          bool NTM = false, bool REV = false, bool SKIP_LAST = false, int CAP = kMaxPair>
+          bool NTM = false, bool REV = false, bool SKIP_LAST = false, int CAP = kMaxPair,
+          class Hook = NoHook>
 __device__ __forceinline__ void col_fft(c32 *buf, const c32 *gin, c32 *gout, int64_t gs, bool gv,
-                                        const c32 *tw, int tid)
+                                        const c32 *tw, int tid, Hook hook = {})
 {
     if constexpr (L == 1) {
+        hook.loaded();
         if (tid < NL) {
             const int l = tid;
             c32 v = SRC_G ? (gv ? gin[0] : c32{0.f, 0.f}) : buf[l];
@@ -899,7 +946,7 @@ __device__ __forceinline__ void col_fft(c32 *buf, const c32 *gin, c32 *gout, int
         constexpr bool first = ST == 0, last = NS * R == L;
         if constexpr (!(last && SKIP_LAST)) {
             col_stage<L, R, R1, NS, S, NL, NT, first && SRC_G, last && DST_G, NTM>(buf, gin, gout, gs,
-                                                                               gv, tw, tid);
+                                                                               gv, tw, tid, hook);
             col_fft<L, S, NL, NT, SRC_G, DST_G, ST + 1, NS * R, NTM, REV, SKIP_LAST, CAP>(buf, gin, gout,
                                                                                     gs, gv, tw, tid);
         }

@@ -46,20 +46,6 @@ __host__ __device__ constexpr size_t s_bytes(int L)
     return al16(al16(sizeof(c32) * L * s_b(L)) + sizeof(c32) * L);
 }
 
-// Row base offsets of the RB rows of tile `blk`, in LDS.
-template <int RB, int NT>
-__device__ __forceinline__ void row_bases(int64_t *ib, int64_t *ob, const XArgs &a, int64_t r0,
-                                          int tid)
-{
-    for (int i = tid; i < RB; i += NT) {
-        int64_t r = r0 + i;
-        if (r >= a.nrows) r = a.nrows - 1;
-        int64_t z = r / a.n1, y = r - z * a.n1;
-        ib[i] = a.in_off + z * a.in_plane + y * a.in_row;
-        ob[i] = a.out_off + z * a.out_plane + y * a.out_row;
-    }
-}
-
 template <int RB>
 __device__ __forceinline__ int rows_valid(const XArgs &a, int64_t r0)
 {
@@ -89,7 +75,62 @@ __device__ __forceinline__ void load_table(c32 *dst, const void *src, int n, int
     for (int i = tid; i < n; i += nt) dst[i] = g[i];
 }
 
+// A table of N values on its way to LDS through the threads' registers: its
+// loads are issued beside a tile's own, so that both are waited for once.
+// (x passes over 512^3 with three components, us: r2c 710 -> 669, c2r 681 ->
+// 641; 256^3 c2r 25.6 -> 24.2.)
+template <int N, int NT>
+struct TableRegs {
+    static constexpr int K = (N + NT - 1) / NT;
+    c32 w[K];
+    __device__ __forceinline__ void load(const void *src, int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (N % NT == 0 || tid + i * NT < N) w[i] = ((const c32 *)src)[tid + i * NT];
+    }
+    __device__ __forceinline__ void store(c32 *dst, int tid) const
+    {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (N % NT == 0 || tid + i * NT < N) dst[tid + i * NT] = w[i];
+    }
+};
+
+// The real x tiles' hooks: the sum of squares of the input, where it is asked
+// for, and the tables' way on to LDS, with a barrier where the first stage
+// reads them (kPaired).
+template <class Tabs>
+struct RealHook {
+    double *ss;
+    bool sum;
+    Tabs tabs;
+    __device__ __forceinline__ void value(c32 v) const
+    {
+        if (sum) *ss += (double)v.x * v.x + (double)v.y * v.y;
+    }
+    __device__ __forceinline__ void loaded() const { tabs(); }
+};
+template <class Tabs>
+struct TabHook {
+    Tabs tabs;
+    __device__ __forceinline__ void value(c32) const {}
+    __device__ __forceinline__ void loaded() const { tabs(); }
+};
+template <class Tabs>
+__device__ __forceinline__ TabHook<Tabs> tab_hook(Tabs t)
+{
+    return TabHook<Tabs>{t};
+}
+template <class Tabs>
+__device__ __forceinline__ RealHook<Tabs> real_hook(double &ss, bool sum, Tabs t)
+{
+    return RealHook<Tabs>{&ss, sum, t};
+}
+
 // =================================================================== x tiles
+// TAB of a tile function: the block's only tile, which fetches the tables
+// itself, its own first loads behind theirs (else the caller's tables() did).
 
 // ---- general r2c (interleaved components, any float offsets): the first
 // stage loads component c's packed point n = (f[2n][c], f[2n + 1][c]) as two
@@ -100,28 +141,41 @@ struct XR2CGen {
                          NH = M + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * NL * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
-                            O_IB = al16(O_TWP + sizeof(c32) * NH), O_OB = O_IB + 8 * RB,
-                            O_RED = O_OB + 8 * RB, BYTES = al16(O_RED + 8 * (NT / 64));
+                            O_RED = al16(O_TWP + sizeof(c32) * NH),
+                            BYTES = al16(O_RED + 8 * (NT / 64));
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
     // sumsq: where to put this tile's FP64 sum of squares (nullptr: skip)
+    template <bool TAB = false>
     static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
-        int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
         const int64_t r0 = blk * RB;
-        row_bases<RB, NT>(ib, ob, a, r0, tid);
-        __syncthreads();
+        const RowAt in_at = row_at(a.in_off, a.in_row, a.in_plane, a.n1, r0);
+        const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
+        TableRegs<M, NT> wt;
+        TableRegs<NH, NT> wp;
+        if (TAB) {
+            wt.load(a.tw, tid);
+            wp.load(a.tw_post, tid);
+        }
+        auto tabs = [&](bool sync) {
+            if (!TAB) return;
+            wt.store((c32 *)(sm + O_TW), tid);
+            wp.store((c32 *)(sm + O_TWP), tid);
+            if (sync) __syncthreads();
+        };
         const int nv = rows_valid<RB>(a, r0);
         // the first stage reads each component's packed pairs straight from
         // the real rows (two float loads per point; no alignment needed)
         double ss = 0.0;
         row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
-            buf, (const c32 *)a.in, nullptr, ib, nullptr, nv, tw, tid, sumsq ? &ss : nullptr);
+            buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
+            real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
         if (sumsq) block_sum_f64<NT>(ss, sumsq, (double *)(sm + O_RED));
         // X[k] = fe + W^k fo and X[M-k] = conj(fe - W^k fo) per component;
         // work item (row, k, component), component fastest
@@ -142,7 +196,7 @@ struct XR2CGen {
                     const c32 d = sub(z, zc);
                     const c32 fo = c32{0.5f * d.y, -0.5f * d.x};  // (z - zc) / (2i)
                     const c32 wf = mul(twp[k], fo);
-                    c32 *orow = out + ob[l] + c;
+                    c32 *orow = out + out_at(l) + c;
                     gstore<true>(orow + k * NC, add(fe, wf));
                     if (2 * k != M) gstore<true>(orow + (M - k) * NC, conjg(sub(fe, wf)));
                 }
@@ -159,8 +213,7 @@ struct XC2RGen {
     static constexpr int RB = x_rb(M, NC, NT), NL = RB * NC, LP = row_pitch(M + 1), NH = M + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * NL * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
-                            O_IB = al16(O_TWP + sizeof(c32) * NH), O_OB = O_IB + 8 * RB,
-                            BYTES = al16(O_OB + 8 * RB);
+                            BYTES = al16(O_TWP + sizeof(c32) * NH);
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
@@ -175,7 +228,7 @@ struct XC2RGen {
     }
     // Real rows from the LDS lines: float x NC + c of row l is part x & 1 of
     // point x >> 1 of line l NC + c.
-    static __device__ void store_rows(const XArgs &a, const c32 *buf, const int64_t *ob, int nv,
+    static __device__ void store_rows(const XArgs &a, const c32 *buf, const RowAt &out_at, int nv,
                                       int tid)
     {
         typedef float nf4 __attribute__((ext_vector_type(4)));
@@ -195,17 +248,29 @@ struct XC2RGen {
             v.y = w[1];
             v.z = w[2];
             v.w = w[3];
-            __builtin_nontemporal_store(v, (nf4 *)(out + ob[l]) + (e - l * W4));
+            __builtin_nontemporal_store(v, (nf4 *)(out + out_at(l)) + (e - l * W4));
         }
     }
+    template <bool TAB = false>
     static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
-        int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
         const int64_t r0 = blk * RB;
-        row_bases<RB, NT>(ib, ob, a, r0, tid);
-        __syncthreads();
+        const RowAt in_at = row_at(a.in_off, a.in_row, a.in_plane, a.n1, r0);
+        const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
+        TableRegs<M, NT> wt;
+        TableRegs<NH, NT> wp;
+        if (TAB) {
+            wt.load(a.tw, tid);
+            wp.load(a.tw_post, tid);
+        }
+        auto tabs = [&](bool sync) {
+            if (!TAB) return;
+            wt.store((c32 *)(sm + O_TW), tid);
+            wp.store((c32 *)(sm + O_TWP), tid);
+            if (sync) __syncthreads();
+        };
         const c32 *in = (const c32 *)a.in;
         constexpr int NI = RB * NH * NC;
         const int nv = rows_valid<RB>(a, r0);
@@ -215,7 +280,7 @@ struct XC2RGen {
             const int k = rem / NC, c = rem - k * NC;
             buf[(row * NC + c) * LP + lpad(k)] = v;
         };
-        const c32 *src = in + ib[0];
+        const c32 *src = in + in_at(0);
         if (a.in_row == NH * NC && a.in_plane == (int64_t)a.n1 * NH * NC &&
             ((uintptr_t)src & 7) == 0) {
             // dense half spectrum: the tile's rows are one contiguous run,
@@ -250,11 +315,12 @@ struct XC2RGen {
                 const int idx = tid + i * NT;
                 if (idx < NI) {
                     const int row = idx / (NH * NC);
-                    put(idx, row < nv ? gload<true>(in + ib[row] + (idx - row * (NH * NC)))
+                    put(idx, row < nv ? gload<true>(in + in_at(row) + (idx - row * (NH * NC)))
                                       : c32{0.f, 0.f});
                 }
             }
         }
+        tabs(false);
         __syncthreads();
         // Z[k] = (X[k] + conj X[M-k]) + i W^{-k} (X[k] - conj X[M-k]), k < M,
         // with the imaginary parts of X[0] and X[M] dropped.
@@ -303,13 +369,13 @@ struct XC2RGen {
             __syncthreads();
             if (vec_out(a)) {
                 // remaining stages in LDS, then whole rows out as 16-byte stores
-                row_fft<M, +1, RB, NC, LP, NT, false, false, 1, R>(buf, nullptr, nullptr, nullptr,
-                                                                   nullptr, nv, tw, tid);
-                store_rows(a, buf, ob, nv, tid);
+                row_fft<M, +1, RB, NC, LP, NT, false, false, 1, R>(buf, nullptr, nullptr, out_at,
+                                                                   out_at, nv, tw, tid);
+                store_rows(a, buf, out_at, nv, tid);
             } else {
                 // the last stage stores each component's pairs straight to the rows
                 row_fft<M, +1, RB, NC, LP, NT, false, true, 1, R, true, true>(
-                    buf, nullptr, (c32 *)a.out, nullptr, ob, nv, tw, tid);
+                    buf, nullptr, (c32 *)a.out, out_at, out_at, nv, tw, tid);
             }
         } else {
             constexpr int NZ = NL * M;
@@ -328,7 +394,7 @@ struct XC2RGen {
             }
             __syncthreads();
             row_fft<M, +1, RB, NC, LP, NT, false, true, 0, 1, true, true>(
-                buf, nullptr, (c32 *)a.out, nullptr, ob, nv, tw, tid);
+                buf, nullptr, (c32 *)a.out, out_at, out_at, nv, tw, tid);
         }
         __syncthreads();
     }
@@ -342,22 +408,35 @@ struct XR2CV {
     static constexpr int RB = x_rb(M, 1, NT), LP = row_pitch(M), NH = M + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * RB * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
-                            O_IB = al16(O_TWP + sizeof(c32) * NH), O_OB = O_IB + 8 * RB,
-                            O_RED = O_OB + 8 * RB, BYTES = al16(O_RED + 8 * (NT / 64));
+                            O_RED = al16(O_TWP + sizeof(c32) * NH),
+                            BYTES = al16(O_RED + 8 * (NT / 64));
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
-    // TAB: the tile loads the tables too, behind its own first loads.
     template <bool TAB = false>
     static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
-        int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
         const int64_t r0 = blk * RB;
         const int nv = rows_valid<RB>(a, r0);
+        const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
+        TableRegs<M, NT> wt;
+        TableRegs<NH, NT> wp;
+        // dense rows: behind the data, not ahead of it (400^3 98 us, 112 ahead)
+        auto fetch = [&] {
+            if (!TAB) return;
+            wt.load(a.tw, tid);
+            wp.load(a.tw_post, tid);
+        };
+        auto tabs = [&](bool sync) {
+            if (!TAB) return;
+            wt.store((c32 *)(sm + O_TW), tid);
+            wp.store((c32 *)(sm + O_TWP), tid);
+            if (sync) __syncthreads();
+        };
         double ss = 0.0;
         const bool dense_out = a.out_row == NH && a.out_plane == (int64_t)a.n1 * NH;
         const float *src = (const float *)a.in + a.in_off + r0 * (2 * M);
@@ -380,8 +459,8 @@ struct XR2CV {
                 const int e = tid + i * NT;
                 if (e < np) w[i] = __builtin_nontemporal_load(s4 + e);
             }
-            if (TAB) tables(a, sm, tid);
-            if (!dense_out) row_bases<RB, NT>(ib, ob, a, r0, tid);
+            fetch();
+            tabs(false);
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
                 const int e = tid + i * NT;
@@ -395,15 +474,15 @@ struct XR2CV {
             }
             for (int e = nv * M + tid; e < RB * M; e += NT) put(e, c32{0.f, 0.f});
             __syncthreads();
-            row_fft<M, -1, RB, 1, LP, NT, false, false>(buf, nullptr, nullptr, nullptr, nullptr, nv,
+            row_fft<M, -1, RB, 1, LP, NT, false, false>(buf, nullptr, nullptr, out_at, out_at, nv,
                                                         tw, tid);
         } else {
-            if (TAB) tables(a, sm, tid);
-            row_bases<RB, NT>(ib, ob, a, r0, tid);
-            for (int i = tid; i < RB; i += NT) ib[i] >>= 1;  // float offset -> complex offset
-            __syncthreads();
+            fetch();
+            // float offsets -> complex offsets
+            const RowAt in_at = row_at(a.in_off / 2, a.in_row / 2, a.in_plane / 2, a.n1, r0);
             row_fft<M, -1, RB, 1, LP, NT, true, false, 0, 1, true>(
-                buf, (const c32 *)a.in, nullptr, ib, nullptr, nv, tw, tid, sumsq ? &ss : nullptr);
+                buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
+                real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
         }
         if (sumsq) block_sum_f64<NT>(ss, sumsq, (double *)(sm + O_RED));
         // The store forms the bins from the points as it reads them: bin k of
@@ -443,7 +522,7 @@ struct XR2CV {
         } else {
             for (int e = tid; e < nv * NH; e += NT) {
                 const int l = e / NH, k = e - l * NH;
-                gstore<true>(out + ob[l] + k, bin(l, k));
+                gstore<true>(out + out_at(l) + k, bin(l, k));
             }
         }
         __syncthreads();
@@ -458,29 +537,40 @@ struct XC2RV {
     static constexpr int RB = x_rb(M, 1, NT), LP = row_pitch(M + 1), NH = M + 1, HALF = M / 2 + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * RB * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
-                            O_IB = al16(O_TWP + sizeof(c32) * NH), O_OB = O_IB + 8 * RB,
-                            BYTES = al16(O_OB + 8 * RB);
+                            BYTES = al16(O_TWP + sizeof(c32) * NH);
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
+    template <bool TAB = false>
     static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
-        int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
         const int64_t r0 = blk * RB;
-        row_bases<RB, NT>(ib, ob, a, r0, tid);
-        __syncthreads();
-        for (int i = tid; i < RB; i += NT) ob[i] >>= 1;
+        const RowAt in_at = row_at(a.in_off, a.in_row, a.in_plane, a.n1, r0);
+        // float offsets -> complex offsets
+        const RowAt out_at = row_at(a.out_off / 2, a.out_row / 2, a.out_plane / 2, a.n1, r0);
+        TableRegs<M, NT> wt;
+        TableRegs<NH, NT> wp;
+        if (TAB) {
+            wt.load(a.tw, tid);
+            wp.load(a.tw_post, tid);
+        }
+        auto tabs = [&](bool sync) {
+            if (!TAB) return;
+            wt.store((c32 *)(sm + O_TW), tid);
+            wp.store((c32 *)(sm + O_TWP), tid);
+            if (sync) __syncthreads();
+        };
         const int nv = rows_valid<RB>(a, r0);
         const c32 *in = (const c32 *)a.in;
         if (a.in_row == NH && a.in_plane == (int64_t)a.n1 * NH) {
             // Dense half spectrum: the tile's rows are one contiguous run of
             // nv * NH values, read with 16-byte loads when the run is 16-byte
             // aligned and placed into the padded LDS rows.
-            const c32 *src = in + ib[0];
+            const c32 *src = in + in_at(0);
             const int cnt = nv * NH;
             auto put = [&](int e, c32 v) {
                 const int l = e / NH, k = e - l * NH;
@@ -516,7 +606,7 @@ struct XC2RV {
             constexpr int TPR = NT / RB >= 1 ? NT / RB : 1;
             constexpr int NK = (NH + TPR - 1) / TPR;
             for (int l = tid / TPR; l < RB; l += NT / TPR) {
-                const int64_t base = ib[l];
+                const int64_t base = in_at(l);
                 const bool ok = l < nv;
                 const int k0 = tid % TPR;
 #pragma unroll
@@ -526,6 +616,7 @@ struct XC2RV {
                 }
             }
         }
+        tabs(false);
         __syncthreads();
         if constexpr (kPlan<M>.n >= 2) {
             // The first inverse stage forms its inputs Z[k] from the bins
@@ -567,8 +658,8 @@ struct XC2RV {
                 }
             }
             __syncthreads();
-            row_fft<M, +1, RB, 1, LP, NT, false, true, 1, R, true>(buf, nullptr, (c32 *)a.out, nullptr,
-                                                             ob, nv, tw, tid);
+            row_fft<M, +1, RB, 1, LP, NT, false, true, 1, R, true>(buf, nullptr, (c32 *)a.out, out_at,
+                                                             out_at, nv, tw, tid);
         } else {
             constexpr int NP = RB * HALF;
 #pragma unroll
@@ -595,7 +686,7 @@ struct XC2RV {
                 }
             }
             __syncthreads();
-            row_fft<M, +1, RB, 1, LP, NT, false, true>(buf, nullptr, (c32 *)a.out, nullptr, ob, nv,
+            row_fft<M, +1, RB, 1, LP, NT, false, true>(buf, nullptr, (c32 *)a.out, out_at, out_at, nv,
                                                        tw, tid);
         }
         __syncthreads();
@@ -613,17 +704,40 @@ struct XC2CV {
     {
         load_table((c32 *)(sm + O_TW), a.tw, L, tid, NT);
     }
+    template <bool TAB = false>
     static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW);
-        int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
         const int64_t r0 = blk * RB;
-        row_bases<RB, NT>(ib, ob, a, r0, tid);
-        __syncthreads();
         const int nv = rows_valid<RB>(a, r0);
-        row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(buf, (const c32 *)a.in, (c32 *)a.out, ib, ob,
-                                                  nv, tw, tid);
+        const RowAt in_at = row_at(a.in_off, a.in_row, a.in_plane, a.n1, r0);
+        const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
+        if constexpr (S < 0) {
+            // Forward, the table and the row offsets are waited for before
+            // the loads: with either behind them the compiler rounds the
+            // twiddle products of some rows another way, and P(k) of a field
+            // would move in its ninth digit.
+            if (TAB) tables(a, sm, tid);
+            int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
+            for (int i = tid; i < RB; i += NT) {
+                const int q = i < nv ? i : nv - 1;
+                ib[i] = in_at(q);
+                ob[i] = out_at(q);
+            }
+            __syncthreads();
+            row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
+                buf, (const c32 *)a.in, (c32 *)a.out, RowTable{ib}, RowTable{ob}, nv, tw, tid);
+        } else {
+            TableRegs<L, NT> wt;
+            if (TAB) wt.load(a.tw, tid);
+            row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
+                buf, (const c32 *)a.in, (c32 *)a.out, in_at, out_at, nv, tw, tid, tab_hook([&] {
+                    if (!TAB) return;
+                    wt.store((c32 *)(sm + O_TW), tid);
+                    if (kPaired<L>) __syncthreads();  // else the first stage reads no table
+                }));
+        }
         __syncthreads();
     }
 };
@@ -812,6 +926,23 @@ struct STile {
         }
     }
 
+    // A block's only tile, tables included (EPI = false): the table values are
+    // fetched first and go to LDS once the tile's own loads are issued behind
+    // them, so that the two waits are one: a tile lives for about 13 us, and
+    // a wait for the table ahead of its loads took 1 us of them (512^3 real y
+    // 203 -> 187 us, 400^3 y 107 -> 99, 240 x 180 x 150 with three components
+    // z 36 -> 30, 128^3 y 9.4 -> 8.9; the y pass over 256^3 complex, at 45.5
+    // us near the rate its write-back allows, 47).
+    static __device__ void only_tile(const SArgs &a, int64_t t, char *sm, int tid)
+    {
+        TableRegs<L, NT> wt;
+        wt.load(a.tw, tid);
+        plain(a, t, sm, tid, tab_hook([&] {
+            wt.store((c32 *)(sm + O_TW), tid);
+            if (kPaired<L>) __syncthreads();  // else the first stage reads no table
+        }));
+    }
+
     static __device__ void tile(const SArgs &a, int64_t t, char *sm, int tid, double *hist,
                                 const BinEdge *edges)
     {
@@ -819,8 +950,16 @@ struct STile {
             In in;
             load_in(a, t, tid, in);
             tile_in(a, t, sm, tid, hist, edges, in);
-            return;
+        } else {
+            plain(a, t, sm, tid, NoHook{});
+            __syncthreads();
         }
+    }
+
+    template <class Hook>
+    static __device__ __forceinline__ void plain(const SArgs &a, int64_t t, char *sm, int tid,
+                                                 Hook hook)
+    {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW);
         const int col = tid % B;
@@ -832,8 +971,7 @@ struct STile {
         c32 *gout = (c32 *)a.out + base;
         // global -> registers -> stages -> registers -> global
         col_fft<L, S, B, NT, true, true, 0, 1, NTM>(buf, gin, gout, a.stride, valid && store, tw,
-                                                     tid);
-        __syncthreads();
+                                                     tid, hook);
     }
 
     // The fused tile from its loaded inputs (load_in of the same t).
@@ -1132,8 +1270,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_r2c(XArgs a)
 {
     using T = XR2CGen<M, NC, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::tables(a, sm, threadIdx.x);
-    T::tile(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr);
+    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr);
 }
 
 template <int M, int NC>
@@ -1141,8 +1278,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2r(XArgs a)
 {
     using T = XC2RGen<M, NC, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::tables(a, sm, threadIdx.x);
-    T::tile(a, blockIdx.x, sm, threadIdx.x);
+    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x);
 }
 
 template <int M>
@@ -1158,8 +1294,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2r_v(XArgs a)
 {
     using T = XC2RV<M, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::tables(a, sm, threadIdx.x);
-    T::tile(a, blockIdx.x, sm, threadIdx.x);
+    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x);
 }
 
 template <int L, int NC, int S>
@@ -1167,11 +1302,32 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2c_v(XArgs a)
 {
     using T = XC2CV<L, NC, S, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::tables(a, sm, threadIdx.x);
-    T::tile(a, blockIdx.x, sm, threadIdx.x);
+    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x);
 }
 
-// Strided pass: persistent-style walk over tiles.
+// The XCD-aware walk of the strided passes over virtual block ids
+// vb = blockIdx.x + i * G (G is a multiple of 8).  The chip hands block ids to
+// its 8 XCDs in turn, so vb mod 8 is this block's XCD.  Chunks of K
+// consecutive tiles go to one XCD and the chunks rotate over the XCDs:
+// neighbouring tiles, which share cache lines when rows are not 128-byte
+// aligned, meet in one L2, while all XCDs stream from nearby addresses.
+// Passes have fewer than 2^31 columns, so tiles and ids are 32-bit.
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t vb, uint32_t K)
+{
+    const uint32_t lb = vb / 8, c = lb / K;
+    return (c * 8 + (vb % 8)) * K + (lb - c * K);
+}
+
+// Forward lines whose table stays ahead of the loads: behind them the
+// compiler rounds the 16-point butterfly of 16 3 and 16 5 (2^a) points another
+// way, and P(k) of a field would move in its ninth digit.
+__host__ __device__ constexpr bool s_table_first(int L)
+{
+    const RadixPlan p = radix_plan(L);
+    return p.nodd == 1 && p.f[0] == 16;
+}
+
+// Strided pass: persistent-style walk over tiles where they are binned.
 // Occupancy target: four waves per SIMD (two blocks per CU) except where the
 // fused pass's LDS tables leave room for one block (lines of 1024 points and
 // more), where two waves per SIMD are all it can reach.
@@ -1185,6 +1341,13 @@ __global__ __launch_bounds__(EPI ? e_nt<L> : s_nt<L>)
     __shared__ __align__(16) char sm[T::BYTES];
     extern __shared__ double dyn[];  // hist[hcopies][nbins + 1], edges[nbins + 1]
     const int tid = threadIdx.x;
+    const uint32_t ntiles = (uint32_t)((a.ncols + B - 1) / B), K = a.xcd_chunk;
+    if constexpr (!EPI && !(S < 0 && s_table_first(L))) {
+        // one tile a block (launch_strided's grid covers the walk)
+        const uint32_t t = xcd_tile(blockIdx.x, K);
+        if (t < ntiles) T::only_tile(a, t, sm, tid);
+        return;
+    }
     T::tables(a, sm, tid);
     const bool pk = EPI && (a.epi & (EPI_PK | EPI_PK_AFTER)) != 0;
     const int nb = a.mt.nbins;
@@ -1192,21 +1355,9 @@ __global__ __launch_bounds__(EPI ? e_nt<L> : s_nt<L>)
     BinEdge *edges = (BinEdge *)(dyn + a.hcopies * (nb + 1));
     if (pk) hist_init(a.mt, a.hcopies, hist, edges, tid, NT);
     __syncthreads();
-    const int64_t ntiles = (a.ncols + B - 1) / B;
-    // XCD-aware walk over virtual block ids vb = blockIdx.x + i * G (G is a
-    // multiple of 8).  The chip hands block ids to its 8 XCDs in turn, so
-    // vb mod 8 is this block's XCD.  Chunks of K consecutive tiles go to one
-    // XCD and the chunks rotate over the XCDs: neighbouring tiles, which
-    // share cache lines when rows are not 128-byte aligned, meet in one L2,
-    // while all XCDs stream from nearby addresses.
-    const int64_t K = a.xcd_chunk;
-    const int64_t span = (ntiles + 8 * K - 1) / (8 * K) * (8 * K);
-    auto tile_of = [&](int64_t vb) {
-        const int64_t lb = vb / 8;
-        return ((lb / K) * 8 + (vb % 8)) * K + lb % K;
-    };
-    for (int64_t vb = blockIdx.x; vb < span; vb += gridDim.x) {
-        const int64_t t = tile_of(vb);
+    const uint32_t span = (ntiles + 8 * K - 1) / (8 * K) * (8 * K);
+    for (uint32_t vb = blockIdx.x; vb < span; vb += gridDim.x) {
+        const uint32_t t = xcd_tile(vb, K);
         if (t >= ntiles) continue;  // uniform over the block
         T::tile(a, t, sm, opaque_tid<EPI>(tid), hist, edges);
     }
@@ -1225,12 +1376,10 @@ __global__ __launch_bounds__(kSWThreads) void k_strided_w(SArgs a)
     const int tid = threadIdx.x;
     T::tables(a, sm, tid);
     __syncthreads();
-    const int64_t ntiles = (a.ncols + B - 1) / B;
-    const int64_t K = a.xcd_chunk;  // the XCD-aware walk of k_strided
-    const int64_t span = (ntiles + 8 * K - 1) / (8 * K) * (8 * K);
-    for (int64_t vb = blockIdx.x; vb < span; vb += gridDim.x) {
-        const int64_t lb = vb / 8;
-        const int64_t t = ((lb / K) * 8 + (vb % 8)) * K + lb % K;
+    const uint32_t ntiles = (uint32_t)((a.ncols + B - 1) / B), K = a.xcd_chunk;
+    const uint32_t span = (ntiles + 8 * K - 1) / (8 * K) * (8 * K);
+    for (uint32_t vb = blockIdx.x; vb < span; vb += gridDim.x) {
+        const uint32_t t = xcd_tile(vb, K);
         if (t >= ntiles) continue;  // uniform over the block
         T::tile(a, t, sm, tid);
     }
