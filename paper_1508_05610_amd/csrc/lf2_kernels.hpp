@@ -97,6 +97,23 @@ struct TableRegs {
     }
 };
 
+// Forward lines whose table (and x rows' offsets, in LDS) stay ahead of loads
+// that feed the first stage: behind them the compiler rounds the 16-point
+// butterfly of 16 3 and 16 5 (2^a) points another way, and P(k) of a field
+// would move in its ninth digit.
+__host__ __device__ constexpr bool table_first(int L)
+{
+    const RadixPlan p = radix_plan(L);
+    return p.nodd == 1 && p.f[0] == 16;
+}
+
+// Row offsets of a tile's first nv rows into LDS.
+template <int RB, int NT>
+__device__ __forceinline__ void fill_rows(int64_t *ib, const RowAt &at, int nv, int tid)
+{
+    for (int i = tid; i < RB; i += NT) ib[i] = at(i < nv ? i : nv - 1);
+}
+
 // The real x tiles' hooks: the sum of squares of the input, where it is asked
 // for, and the tables' way on to LDS, with a barrier where the first stage
 // reads them (kPaired).
@@ -142,7 +159,8 @@ struct XR2CGen {
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * NL * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
                             O_RED = al16(O_TWP + sizeof(c32) * NH),
-                            BYTES = al16(O_RED + 8 * (NT / 64));
+                            O_IB = al16(O_RED + 8 * (NT / 64)),
+                            BYTES = O_IB + (table_first(M) ? 8 * RB : 0);
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
@@ -159,7 +177,7 @@ struct XR2CGen {
         const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
         TableRegs<M, NT> wt;
         TableRegs<NH, NT> wp;
-        if (TAB) {
+        if (TAB && !table_first(M)) {
             wt.load(a.tw, tid);
             wp.load(a.tw_post, tid);
         }
@@ -173,9 +191,19 @@ struct XR2CGen {
         // the first stage reads each component's packed pairs straight from
         // the real rows (two float loads per point; no alignment needed)
         double ss = 0.0;
-        row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
-            buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
-            real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
+        if constexpr (table_first(M)) {
+            if (TAB) tables(a, sm, tid);
+            int64_t *ib = (int64_t *)(sm + O_IB);
+            fill_rows<RB, NT>(ib, in_at, nv, tid);
+            __syncthreads();
+            row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
+                buf, (const c32 *)a.in, nullptr, RowTable{ib}, RowTable{ib}, nv, tw, tid,
+                real_hook(ss, sumsq != nullptr, [] {}));
+        } else {
+            row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
+                buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
+                real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
+        }
         if (sumsq) block_sum_f64<NT>(ss, sumsq, (double *)(sm + O_RED));
         // X[k] = fe + W^k fo and X[M-k] = conj(fe - W^k fo) per component;
         // work item (row, k, component), component fastest
@@ -409,7 +437,8 @@ struct XR2CV {
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * RB * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
                             O_RED = al16(O_TWP + sizeof(c32) * NH),
-                            BYTES = al16(O_RED + 8 * (NT / 64));
+                            O_IB = al16(O_RED + 8 * (NT / 64)),
+                            BYTES = O_IB + (table_first(M) ? 8 * RB : 0);
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
@@ -477,12 +506,22 @@ struct XR2CV {
             row_fft<M, -1, RB, 1, LP, NT, false, false>(buf, nullptr, nullptr, out_at, out_at, nv,
                                                         tw, tid);
         } else {
-            fetch();
             // float offsets -> complex offsets
             const RowAt in_at = row_at(a.in_off / 2, a.in_row / 2, a.in_plane / 2, a.n1, r0);
-            row_fft<M, -1, RB, 1, LP, NT, true, false, 0, 1, true>(
-                buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
-                real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
+            if constexpr (table_first(M)) {
+                if (TAB) tables(a, sm, tid);
+                int64_t *ib = (int64_t *)(sm + O_IB);
+                fill_rows<RB, NT>(ib, in_at, nv, tid);
+                __syncthreads();
+                row_fft<M, -1, RB, 1, LP, NT, true, false, 0, 1, true>(
+                    buf, (const c32 *)a.in, nullptr, RowTable{ib}, RowTable{ib}, nv, tw, tid,
+                    real_hook(ss, sumsq != nullptr, [] {}));
+            } else {
+                fetch();
+                row_fft<M, -1, RB, 1, LP, NT, true, false, 0, 1, true>(
+                    buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
+                    real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
+            }
         }
         if (sumsq) block_sum_f64<NT>(ss, sumsq, (double *)(sm + O_RED));
         // The store forms the bins from the points as it reads them: bin k of
@@ -720,11 +759,8 @@ struct XC2CV {
             // would move in its ninth digit.
             if (TAB) tables(a, sm, tid);
             int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
-            for (int i = tid; i < RB; i += NT) {
-                const int q = i < nv ? i : nv - 1;
-                ib[i] = in_at(q);
-                ob[i] = out_at(q);
-            }
+            fill_rows<RB, NT>(ib, in_at, nv, tid);
+            fill_rows<RB, NT>(ob, out_at, nv, tid);
             __syncthreads();
             row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
                 buf, (const c32 *)a.in, (c32 *)a.out, RowTable{ib}, RowTable{ob}, nv, tw, tid);
@@ -1318,15 +1354,6 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t vb, uint32_t K)
     return (c * 8 + (vb % 8)) * K + (lb - c * K);
 }
 
-// Forward lines whose table stays ahead of the loads: behind them the
-// compiler rounds the 16-point butterfly of 16 3 and 16 5 (2^a) points another
-// way, and P(k) of a field would move in its ninth digit.
-__host__ __device__ constexpr bool s_table_first(int L)
-{
-    const RadixPlan p = radix_plan(L);
-    return p.nodd == 1 && p.f[0] == 16;
-}
-
 // Strided pass: persistent-style walk over tiles where they are binned.
 // Occupancy target: four waves per SIMD (two blocks per CU) except where the
 // fused pass's LDS tables leave room for one block (lines of 1024 points and
@@ -1342,7 +1369,7 @@ __global__ __launch_bounds__(EPI ? e_nt<L> : s_nt<L>)
     extern __shared__ double dyn[];  // hist[hcopies][nbins + 1], edges[nbins + 1]
     const int tid = threadIdx.x;
     const uint32_t ntiles = (uint32_t)((a.ncols + B - 1) / B), K = a.xcd_chunk;
-    if constexpr (!EPI && !(S < 0 && s_table_first(L))) {
+    if constexpr (!EPI && !(S < 0 && table_first(L))) {
         // one tile a block (launch_strided's grid covers the walk)
         const uint32_t t = xcd_tile(blockIdx.x, K);
         if (t < ntiles) T::only_tile(a, t, sm, tid);
