@@ -1536,12 +1536,11 @@ lf2_status lf2_power_spectrum(lf2_plan p, const void *field, int32_t field_is_ks
     if (field_is_kspace) {
         ModeTables mt = base_tables(p);
         use_shell(mt, sh);
-        grid = kPkGrid;
         const int t = prof::begin("k_pk_kspace", (double)spectrum_bytes(p), s);
         int64_t kst[3];
         (void)lf2_fft_kspace(p, nullptr, kst);
         hipError_t e = launch_pk_kspace(field, (int)p->n[1], (int)p->n[2], kst[0], kst[1], kst[2], mt,
-                                        part, grid, s);
+                                        part, kPkGrid, s, &grid);
         prof::end(t, s);
         LF2_HIP(e);
     } else {

@@ -116,6 +116,22 @@ hipError_t launch_strided_reg(int len, int sign, const SArgs &a, int grid_cap, h
 // have e_nt<len>).
 int epi_hist_copies(int len, int nbins, size_t budget, bool persistent = false);
 
+// Blocks of a binned z pass over lines of `len` points: one round of what the
+// chip's 256 CUs hold at `lds` bytes and `waves` waves a block, 16 waves a CU.
+// More blocks than that only repeat the tables' set-up.  With 1024 blocks and
+// with a round (us): Poisson with 32 bins at 256^3 153 and 149, 400^3 594 and
+// 556, 600^3 2590 and 2482 (300^3 295 and 298), P(k) at 256^3 87 and 83, 512^3
+// 538 and 530.  Lines of 640 points and more take long enough a tile that the
+// balance of 1024 blocks is worth more (P(k) at 640^3 1287 and 1293, 768^3
+// 2223 and 2269, 1024^3 5634 and 5801).
+inline int binning_blocks(int len, int cap, size_t lds, int waves)
+{
+    if (len >= 640) return cap;
+    const int by_lds = (int)(160 * 1024 / lds), by_waves = 16 / waves;
+    const int n = by_lds < by_waves ? by_lds : by_waves, r = 256 * (n < 1 ? 1 : n);
+    return cap < r ? cap : r;
+}
+
 // Kernels of the lengths of LF2_RAGGED_LENGTHS (lf2_kx.hip, lf2_kragged.hip):
 // the x tiles, and the narrow strided tile with its fused epilogue.  The
 // launchers above call them for those lengths.
@@ -127,10 +143,10 @@ hipError_t ragged_x_c2r_b(int m, int nc, const XArgs &a, hipStream_t s);
 hipError_t ragged_x_c2c_a(int len, int nc, int sign, const XArgs &a, hipStream_t s);
 hipError_t ragged_x_c2c_b(int len, int nc, int sign, const XArgs &a, hipStream_t s);
 // plain pass (shm 0) or the fused last-axis pass (a.epi, forward sign only)
-hipError_t ragged_strided_a(int len, int sign, const SArgs &a, int grid, size_t shm, bool ntm,
-                            hipStream_t s);
-hipError_t ragged_strided_b(int len, int sign, const SArgs &a, int grid, size_t shm, bool ntm,
-                            hipStream_t s);
+hipError_t ragged_strided_a(int len, int sign, const SArgs &a, int grid_cap, size_t shm, bool ntm,
+                            hipStream_t s, int *grid_used);
+hipError_t ragged_strided_b(int len, int sign, const SArgs &a, int grid_cap, size_t shm, bool ntm,
+                            hipStream_t s, int *grid_used);
 
 // Run-time-schedule kernels (lf2_kgen.hip): LDS bytes of an x tile of RB
 // rows and of a strided tile of B columns (nbins > 0: with the binning
@@ -173,7 +189,8 @@ hipError_t launch_shell_partials(const ModeTables &mt, int n1, int n2, double ls
 hipError_t launch_reduce_cols(const double *partial, int64_t grid, int width, double *out,
                               hipStream_t s);
 hipError_t launch_pk_kspace(const void *F, int n1, int n2, int64_t sx, int64_t sy, int64_t sz,
-                            const ModeTables &mt, double *partial, int grid, hipStream_t s);
+                            const ModeTables &mt, double *partial, int grid_cap, hipStream_t s,
+                            int *grid_used);
 // Results of a binning pass from its partials ([rows][nbins + 1], slot nbins
 // the row's total) and the lattice's shell table.
 struct PkTail {

@@ -1424,4 +1424,18 @@ __global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4))) 
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) T::tile(a, t, sm, tid);
 }
 
+// Grid of a narrow strided pass: every tile of the walk a block (the plain
+// pass), at most grid_cap blocks (the fused one), at most a round of them
+// where they bin.
+template <int L>
+inline int s_grid(const SArgs &a, int grid_cap, size_t shm)
+{
+    const int64_t chunk = a.xcd_chunk, ntiles = (a.ncols + s_b(L) - 1) / s_b(L);
+    const int64_t span = (ntiles + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
+    if ((a.epi & (EPI_PK | EPI_PK_AFTER | EPI_POISSON)) == 0) return (int)span;
+    if (a.epi & (EPI_PK | EPI_PK_AFTER))
+        grid_cap = binning_blocks(L, grid_cap, s_bytes(L) + shm, e_nt<L> / 64);
+    return (int)(span < grid_cap ? span : grid_cap);
+}
+
 }  // namespace lf2

@@ -285,10 +285,19 @@ __global__ __launch_bounds__(kPkThreads) void k_pk_kspace(const c32 *F, int n1, 
 }
 
 hipError_t launch_pk_kspace(const void *F, int n1, int n2, int64_t sx, int64_t sy, int64_t sz,
-                            const ModeTables &mt, double *partial, int grid, hipStream_t s)
+                            const ModeTables &mt, double *partial, int grid_cap, hipStream_t s,
+                            int *grid_used)
 {
+    // Two blocks a CU, more only for the largest spectra (us at 512 and 1024
+    // blocks: 64^3 real 9.1 and 9.9, 256^3 25.7 and 27.5, 400^3 49 and 55,
+    // 600^3 187 and 181), no more than there are tiles.
+    const int64_t ncols = (int64_t)mt.nxk * n1, ntiles = (ncols + 63) / 64;
+    int64_t grid = ncols * n2 < (int64_t)1 << 26 ? 512 : 1024;
+    if (grid > ntiles) grid = ntiles;
+    if (grid > grid_cap) grid = grid_cap;
+    *grid_used = (int)grid;
     const size_t shm = (size_t)(mt.nbins + 1) * 16;
-    hipLaunchKernelGGL(k_pk_kspace, dim3(grid), dim3(kPkThreads), shm, s, (const c32 *)F, n1, n2,
+    hipLaunchKernelGGL(k_pk_kspace, dim3((unsigned)grid), dim3(kPkThreads), shm, s, (const c32 *)F, n1, n2,
                        sx, sy, sz, mt, partial);
     return hipGetLastError();
 }

@@ -30,12 +30,15 @@ hipError_t ragged_strided_a(
 #else
 hipError_t ragged_strided_b(
 #endif
-    int len, int sign, const SArgs &a, int grid, size_t shm, bool ntm, hipStream_t s)
+    int len, int sign, const SArgs &a, int grid_cap, size_t shm, bool ntm, hipStream_t s,
+    int *grid_used)
 {
     const bool epi = (a.epi & (EPI_PK | EPI_PK_AFTER | EPI_POISSON)) != 0;
     if (epi && (sign > 0 || ntm)) return hipErrorInvalidValue;
 #define LF2_CASE(L)                                                                          \
-    case L:                                                                                  \
+    case L: {                                                                                \
+        const int grid = s_grid<L>(a, grid_cap, shm);                                        \
+        if (grid_used) *grid_used = grid;                                                    \
         if (epi && a.mt.k2z_unit > 0.0)                                                      \
             hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(grid), dim3(e_nt<L>), \
                                shm, s, a);                                                   \
@@ -46,7 +49,8 @@ hipError_t ragged_strided_b(
             plain<L, true>(sign, grid, a, s);                                                \
         else                                                                                 \
             plain<L, false>(sign, grid, a, s);                                               \
-        return hipGetLastError();
+        return hipGetLastError();                                                            \
+    }
     switch (len) {
         LF2_KR_LENGTHS(LF2_CASE)
     default:

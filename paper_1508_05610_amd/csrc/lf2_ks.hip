@@ -162,19 +162,12 @@ hipError_t launch_strided(int len, int sign, const SArgs &a_in, int grid_cap, hi
         return launch_wide(len, sign, a, grid_cap, s, grid_used, kChunk, ntm);
     }
     if (epi && ntm) return hipErrorInvalidValue;
-    if (ragged_supported(len)) {
-        const int b = s_b(len);
-        const int64_t ntiles = (a.ncols + b - 1) / b;
-        const int64_t span = (ntiles + 8 * kChunk - 1) / (8 * kChunk) * (8 * kChunk);
-        const int g = (int)(span < grid_cap ? span : grid_cap);
-        if (grid_used) *grid_used = g;
-        return (len <= 270 ? ragged_strided_a : ragged_strided_b)(len, sign, a, g, shm, ntm, s);
-    }
+    if (ragged_supported(len))
+        return (len <= 270 ? ragged_strided_a : ragged_strided_b)(len, sign, a, grid_cap, shm, ntm, s,
+                                                                  grid_used);
 #define LF2_CASE(L)                                                                          \
     case L: {                                                                                \
-        int64_t ntiles = (a.ncols + s_b(L) - 1) / s_b(L);                                    \
-        int64_t span = (ntiles + 8 * kChunk - 1) / (8 * kChunk) * (8 * kChunk);              \
-        int g = (int)(span < grid_cap ? span : grid_cap);                                    \
+        const int g = s_grid<L>(a, grid_cap, shm);                                           \
         if (grid_used) *grid_used = g;                                                       \
         if (epi && sign < 0 && a.mt.k2z_unit > 0.0)                                          \
             hipLaunchKernelGGL((k_strided<L, -1, true, true, 1>), dim3(g), dim3(e_nt<L>), shm,  \

@@ -1,6 +1,7 @@
 """Edges of the pass tiles: rows and columns that do not fill a tile, tiles whose
 rows span several planes or start inside one, tables fetched ahead of or behind a
-tile's loads, and the derivative's planes per block."""
+tile's loads, binning passes of more tiles than blocks, and the derivative's
+planes per block."""
 import numpy as np
 import pytest
 
@@ -84,6 +85,32 @@ def test_complex(lf2, shape, ncomp, halo, direction):
     for c in range(ncomp):
         assert_close(got[..., c] if ncomp > 1 else got,
                      oracle.c2c(z[..., c].astype(np.complex128), direction), shape, f"comp {c}")
+
+
+# fewer tiles than blocks; one more than a round of two blocks a CU, of three;
+# a line past the rule's limit; a spectrum past the k-space pass's limit
+@pytest.mark.parametrize("shape", [(16, 4, 8), (256, 128, 256), (300, 216, 300), (40, 300, 640), (512, 512, 540)])
+def test_binning_passes_agree(lf2, shape):
+    """P(k) from the field (z pass), from the solve's fused pass, and from the
+    spectrum (k-space pass): the same modes, powers of one FP32 transform
+    rounded in at most two ways."""
+    print(f"case tiles bins {shape}", flush=True)
+    p = lf2.Plan(shape)
+    g = torch.Generator(device=dev())
+    g.manual_seed(73)
+    x = torch.randn(p.x_shape, generator=g, device=dev())
+    field = p.power_spectrum(x, 24)
+    solve = p.poisson(x, nbins=24, parseval=True)
+    spec = p.power_spectrum(p.forward(x), 24, field_is_kspace=True)
+    assert torch.equal(field[2], spec[2]) and torch.equal(field[2], solve[3])
+    assert float(field[2].sum()) == np.prod(shape) - 1
+    # FP32 transforms of 2^26 points are within 1e-6 of each other in norm, a
+    # bin's power within twice that of the largest
+    top = float(field[0].max())
+    assert float((field[0] - spec[0]).abs().max()) <= 4e-6 * top
+    assert float((field[0] - solve[1]).abs().max()) <= 4e-6 * top
+    pv = solve[4].cpu().numpy()
+    assert abs(pv[0] - pv[1]) <= 1e-5 * pv[0]
 
 
 # 32, 16, 8 and 4 planes a block (12288 waves in the grid or fewer), the last
