@@ -39,9 +39,7 @@ __global__ __launch_bounds__(kXThreads) void k_bx_fwd(const BatchField *fields,
     __shared__ __align__(16) char sm[T::BYTES];
     const BatchItem it = items[blockIdx.x];
     const BatchField &F = fields[it.field];
-    T::tables(F.xf, sm, threadIdx.x);
-    __syncthreads();
-    [[clang::always_inline]] T::tile(F.xf, it.tile, sm, threadIdx.x, nullptr);
+    [[clang::always_inline]] T::tile(F.xf, it.tile, sm, threadIdx.x, nullptr, true);
 }
 
 template <int L>
@@ -52,9 +50,7 @@ __global__ __launch_bounds__(kXThreads) void k_bx_inv(const BatchField *fields,
     __shared__ __align__(16) char sm[T::BYTES];
     const BatchItem it = items[blockIdx.x];
     const BatchField &F = fields[it.field];
-    T::tables(F.xi, sm, threadIdx.x);
-    __syncthreads();
-    [[clang::always_inline]] T::tile(F.xi, it.tile, sm, threadIdx.x);
+    [[clang::always_inline]] T::tile(F.xi, it.tile, sm, threadIdx.x, true);
 }
 
 // S = -1: forward y pass; S = +1: backward y pass.
@@ -67,9 +63,7 @@ __global__ __launch_bounds__(s_nt<L>) __attribute__((amdgpu_waves_per_eu(4))) vo
     const BatchItem it = items[blockIdx.x];
     const BatchField &F = fields[it.field];
     const SArgs &a = S < 0 ? F.yf : F.yi;
-    T::tables(a, sm, threadIdx.x);
-    __syncthreads();
-    [[clang::always_inline]] T::tile(a, it.tile, sm, threadIdx.x, nullptr, nullptr);
+    [[clang::always_inline]] T::tile(a, it.tile, sm, threadIdx.x, nullptr, nullptr, true);
 }
 
 // z pass: forward * -1/(N k^2) * backward, with the tile's w|F|^2 bin sums
@@ -304,8 +298,8 @@ __device__ void p_finalize(const BatchField &F, double *red)
 
 // Not inlined: each (length) body is register-allocated on its own, as in
 // its grouped kernel, instead of all of them inside one function.
-// The tiles t0 .. t1 - 1 of one item of pass P (line length L), after one
-// load of the pass tables; z tiles (fused Poisson scale and binning, K2 as
+// The tiles t0 .. t1 - 1 of one item of pass P (line length L); the first
+// fetches the pass tables beside its own loads; z tiles (fused Poisson scale and binning, K2 as
 // for STile) each write their own row of bin sums.  One function per
 // (L, P, K2), not inlined into the kernel: each is register-allocated on
 // its own, as a standalone pass kernel would be, and the tile code is
@@ -317,23 +311,17 @@ __device__ __attribute__((noinline)) void p_pass(const BatchField &F, const QIte
     const int t0 = it.tile, t1 = it.tile + it.ntile;
     if constexpr (P == BP_XF) {
         using T = XR2CV<L, kPThreads>;
-        T::tables(F.xf, sm, tid);
-        __syncthreads();
         for (int t = t0; t < t1; ++t)
-            [[clang::always_inline]] T::tile(F.xf, t, sm, opaque_tid<true>(tid), nullptr);
+            [[clang::always_inline]] T::tile(F.xf, t, sm, opaque_tid<true>(tid), nullptr, t == t0);
     } else if constexpr (P == BP_XI) {
         using T = XC2RV<L, kPThreads>;
-        T::tables(F.xi, sm, tid);
-        __syncthreads();
         for (int t = t0; t < t1; ++t)
-            [[clang::always_inline]] T::tile(F.xi, t, sm, opaque_tid<true>(tid));
+            [[clang::always_inline]] T::tile(F.xi, t, sm, opaque_tid<true>(tid), t == t0);
     } else if constexpr (P == BP_YF || P == BP_YI) {
         using T = STile<L, P == BP_YF ? -1 : 1, false, kPThreads>;
         const SArgs &a = P == BP_YF ? F.yf : F.yi;
-        T::tables(a, sm, tid);
-        __syncthreads();
         for (int t = t0; t < t1; ++t)
-            [[clang::always_inline]] T::tile(a, t, sm, opaque_tid<true>(tid), nullptr, nullptr);
+            [[clang::always_inline]] T::tile(a, t, sm, opaque_tid<true>(tid), nullptr, nullptr, t == t0);
     } else {
         using T = STile<L, -1, true, kPThreads, true, K2>;
         const int nb = F.nbins;

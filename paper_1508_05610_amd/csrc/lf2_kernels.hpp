@@ -146,8 +146,8 @@ __device__ __forceinline__ RealHook<Tabs> real_hook(double &ss, bool sum, Tabs t
 }
 
 // =================================================================== x tiles
-// TAB of a tile function: the block's only tile, which fetches the tables
-// itself, its own first loads behind theirs (else the caller's tables() did).
+// tab of a tile function: the block's first tile, which fetches the tables
+// itself, beside its own loads (else they are in LDS).
 
 // ---- general r2c (interleaved components, any float offsets): the first
 // stage loads component c's packed point n = (f[2n][c], f[2n + 1][c]) as two
@@ -167,8 +167,8 @@ struct XR2CGen {
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
     // sumsq: where to put this tile's FP64 sum of squares (nullptr: skip)
-    template <bool TAB = false>
-    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq)
+    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq,
+                                bool tab = false)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
@@ -177,12 +177,12 @@ struct XR2CGen {
         const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
         TableRegs<M, NT> wt;
         TableRegs<NH, NT> wp;
-        if (TAB && !table_first(M)) {
+        if (tab && !table_first(M)) {
             wt.load(a.tw, tid);
             wp.load(a.tw_post, tid);
         }
         auto tabs = [&](bool sync) {
-            if (!TAB) return;
+            if (!tab) return;
             wt.store((c32 *)(sm + O_TW), tid);
             wp.store((c32 *)(sm + O_TWP), tid);
             if (sync) __syncthreads();
@@ -192,7 +192,7 @@ struct XR2CGen {
         // the real rows (two float loads per point; no alignment needed)
         double ss = 0.0;
         if constexpr (table_first(M)) {
-            if (TAB) tables(a, sm, tid);
+            if (tab) tables(a, sm, tid);
             int64_t *ib = (int64_t *)(sm + O_IB);
             fill_rows<RB, NT>(ib, in_at, nv, tid);
             __syncthreads();
@@ -279,8 +279,7 @@ struct XC2RGen {
             __builtin_nontemporal_store(v, (nf4 *)(out + out_at(l)) + (e - l * W4));
         }
     }
-    template <bool TAB = false>
-    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid)
+    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, bool tab = false)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
@@ -289,12 +288,12 @@ struct XC2RGen {
         const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
         TableRegs<M, NT> wt;
         TableRegs<NH, NT> wp;
-        if (TAB) {
+        if (tab) {
             wt.load(a.tw, tid);
             wp.load(a.tw_post, tid);
         }
         auto tabs = [&](bool sync) {
-            if (!TAB) return;
+            if (!tab) return;
             wt.store((c32 *)(sm + O_TW), tid);
             wp.store((c32 *)(sm + O_TWP), tid);
             if (sync) __syncthreads();
@@ -444,8 +443,8 @@ struct XR2CV {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
-    template <bool TAB = false>
-    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq)
+    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, double *sumsq,
+                                bool tab = false)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
@@ -456,12 +455,12 @@ struct XR2CV {
         TableRegs<NH, NT> wp;
         // dense rows: behind the data, not ahead of it (400^3 98 us, 112 ahead)
         auto fetch = [&] {
-            if (!TAB) return;
+            if (!tab) return;
             wt.load(a.tw, tid);
             wp.load(a.tw_post, tid);
         };
         auto tabs = [&](bool sync) {
-            if (!TAB) return;
+            if (!tab) return;
             wt.store((c32 *)(sm + O_TW), tid);
             wp.store((c32 *)(sm + O_TWP), tid);
             if (sync) __syncthreads();
@@ -509,7 +508,7 @@ struct XR2CV {
             // float offsets -> complex offsets
             const RowAt in_at = row_at(a.in_off / 2, a.in_row / 2, a.in_plane / 2, a.n1, r0);
             if constexpr (table_first(M)) {
-                if (TAB) tables(a, sm, tid);
+                if (tab) tables(a, sm, tid);
                 int64_t *ib = (int64_t *)(sm + O_IB);
                 fill_rows<RB, NT>(ib, in_at, nv, tid);
                 __syncthreads();
@@ -582,8 +581,7 @@ struct XC2RV {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
         load_table((c32 *)(sm + O_TWP), a.tw_post, NH, tid, NT);
     }
-    template <bool TAB = false>
-    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid)
+    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, bool tab = false)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
@@ -593,12 +591,12 @@ struct XC2RV {
         const RowAt out_at = row_at(a.out_off / 2, a.out_row / 2, a.out_plane / 2, a.n1, r0);
         TableRegs<M, NT> wt;
         TableRegs<NH, NT> wp;
-        if (TAB) {
+        if (tab) {
             wt.load(a.tw, tid);
             wp.load(a.tw_post, tid);
         }
         auto tabs = [&](bool sync) {
-            if (!TAB) return;
+            if (!tab) return;
             wt.store((c32 *)(sm + O_TW), tid);
             wp.store((c32 *)(sm + O_TWP), tid);
             if (sync) __syncthreads();
@@ -743,8 +741,7 @@ struct XC2CV {
     {
         load_table((c32 *)(sm + O_TW), a.tw, L, tid, NT);
     }
-    template <bool TAB = false>
-    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid)
+    static __device__ void tile(const XArgs &a, int64_t blk, char *sm, int tid, bool tab = false)
     {
         c32 *buf = (c32 *)(sm + O_BUF);
         const c32 *tw = (const c32 *)(sm + O_TW);
@@ -757,7 +754,7 @@ struct XC2CV {
             // the loads: with either behind them the compiler rounds the
             // twiddle products of some rows another way, and P(k) of a field
             // would move in its ninth digit.
-            if (TAB) tables(a, sm, tid);
+            if (tab) tables(a, sm, tid);
             int64_t *ib = (int64_t *)(sm + O_IB), *ob = (int64_t *)(sm + O_OB);
             fill_rows<RB, NT>(ib, in_at, nv, tid);
             fill_rows<RB, NT>(ob, out_at, nv, tid);
@@ -766,10 +763,10 @@ struct XC2CV {
                 buf, (const c32 *)a.in, (c32 *)a.out, RowTable{ib}, RowTable{ob}, nv, tw, tid);
         } else {
             TableRegs<L, NT> wt;
-            if (TAB) wt.load(a.tw, tid);
+            if (tab) wt.load(a.tw, tid);
             row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
                 buf, (const c32 *)a.in, (c32 *)a.out, in_at, out_at, nv, tw, tid, tab_hook([&] {
-                    if (!TAB) return;
+                    if (!tab) return;
                     wt.store((c32 *)(sm + O_TW), tid);
                     if (kPaired<L>) __syncthreads();  // else the first stage reads no table
                 }));
@@ -962,32 +959,35 @@ struct STile {
         }
     }
 
-    // A block's only tile, tables included (EPI = false): the table values are
-    // fetched first and go to LDS once the tile's own loads are issued behind
-    // them, so that the two waits are one: a tile lives for about 13 us, and
-    // a wait for the table ahead of its loads took 1 us of them (512^3 real y
-    // 203 -> 187 us, 400^3 y 107 -> 99, 240 x 180 x 150 with three components
-    // z 36 -> 30, 128^3 y 9.4 -> 8.9; the y pass over 256^3 complex, at 45.5
-    // us near the rate its write-back allows, 47).
-    static __device__ void only_tile(const SArgs &a, int64_t t, char *sm, int tid)
-    {
-        TableRegs<L, NT> wt;
-        wt.load(a.tw, tid);
-        plain(a, t, sm, tid, tab_hook([&] {
-            wt.store((c32 *)(sm + O_TW), tid);
-            if (kPaired<L>) __syncthreads();  // else the first stage reads no table
-        }));
-    }
-
+    // tab (EPI = false): the block's first tile, tables included.  Their
+    // values are fetched first and go to LDS once the tile's own loads are
+    // issued behind them, so that the two waits are one: a tile lives for
+    // about 13 us, and a wait for the table ahead of its loads took 1 us of
+    // them (512^3 real y 203 -> 187 us, 400^3 y 107 -> 99, 240 x 180 x 150
+    // with three components z 36 -> 30, 128^3 y 9.4 -> 8.9; the y pass over
+    // 256^3 complex, at 45.5 us near the rate its write-back allows, 47).
     static __device__ void tile(const SArgs &a, int64_t t, char *sm, int tid, double *hist,
-                                const BinEdge *edges)
+                                const BinEdge *edges, bool tab = false)
     {
         if constexpr (EPI) {
             In in;
             load_in(a, t, tid, in);
             tile_in(a, t, sm, tid, hist, edges, in);
-        } else {
+        } else if constexpr (S < 0 && table_first(L)) {
+            if (tab) {
+                tables(a, sm, tid);
+                __syncthreads();
+            }
             plain(a, t, sm, tid, NoHook{});
+            __syncthreads();
+        } else {
+            TableRegs<L, NT> wt;
+            if (tab) wt.load(a.tw, tid);
+            plain(a, t, sm, tid, tab_hook([&] {
+                if (!tab) return;
+                wt.store((c32 *)(sm + O_TW), tid);
+                if (kPaired<L>) __syncthreads();  // else the first stage reads no table
+            }));
             __syncthreads();
         }
     }
@@ -1306,7 +1306,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_r2c(XArgs a)
 {
     using T = XR2CGen<M, NC, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr);
+    T::tile(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr, true);
 }
 
 template <int M, int NC>
@@ -1314,7 +1314,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2r(XArgs a)
 {
     using T = XC2RGen<M, NC, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x);
+    T::tile(a, blockIdx.x, sm, threadIdx.x, true);
 }
 
 template <int M>
@@ -1322,7 +1322,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_r2c_v(XArgs a)
 {
     using T = XR2CV<M, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr);
+    T::tile(a, blockIdx.x, sm, threadIdx.x, a.sumsq ? a.sumsq + blockIdx.x : nullptr, true);
 }
 
 template <int M>
@@ -1330,7 +1330,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2r_v(XArgs a)
 {
     using T = XC2RV<M, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x);
+    T::tile(a, blockIdx.x, sm, threadIdx.x, true);
 }
 
 template <int L, int NC, int S>
@@ -1338,7 +1338,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_c2c_v(XArgs a)
 {
     using T = XC2CV<L, NC, S, kXThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
-    T::template tile<true>(a, blockIdx.x, sm, threadIdx.x);
+    T::tile(a, blockIdx.x, sm, threadIdx.x, true);
 }
 
 // The XCD-aware walk of the strided passes over virtual block ids
@@ -1369,10 +1369,10 @@ __global__ __launch_bounds__(EPI ? e_nt<L> : s_nt<L>)
     extern __shared__ double dyn[];  // hist[hcopies][nbins + 1], edges[nbins + 1]
     const int tid = threadIdx.x;
     const uint32_t ntiles = (uint32_t)((a.ncols + B - 1) / B), K = a.xcd_chunk;
-    if constexpr (!EPI && !(S < 0 && table_first(L))) {
-        // one tile a block (launch_strided's grid covers the walk)
+    if constexpr (!EPI) {
+        // one tile a block (s_grid)
         const uint32_t t = xcd_tile(blockIdx.x, K);
-        if (t < ntiles) T::only_tile(a, t, sm, tid);
+        if (t < ntiles) T::tile(a, t, sm, tid, nullptr, nullptr, true);
         return;
     }
     T::tables(a, sm, tid);
