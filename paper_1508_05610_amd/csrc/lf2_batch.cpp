@@ -378,7 +378,13 @@ lf2_status lf2_batch_plan(lf2_batch *out, int32_t nfields, const lf2_lattice *la
         }
         // tiles per item: about fifteen items per block, so that each item's
         // wait and publication (and the call into its tile code) are spread
-        // over several tiles while the last items of a pass stay short
+        // over several tiles while the last items of a pass stay short.  In
+        // one queue for all XCDs every item also writes back and refetches
+        // its XCD's L2: eight items per block, of two tiles at least (10
+        // fields of 64 to 256 sites a side, 24 tiles per block: items of 1
+        // tile 1001 us, of 3 600, of 6 637; 48 fields, 104 tiles: of 6 1935,
+        // of 12 1724; one 256^3, 10 tiles: of 1 584, of 2 444; three 64^3,
+        // less than a tile per block: of 1 121, of 2 140).
         int64_t ntiles_all = 0;
         for (int f = 0; f < nfields; ++f)
             for (int p = 0; p < BP_COUNT; ++p) ntiles_all += tiles[f][p];
@@ -386,7 +392,8 @@ lf2_status lf2_batch_plan(lf2_batch *out, int32_t nfields, const lf2_lattice *la
         if (hipDeviceGetAttribute(&ncu0, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess ||
             ncu0 < 1)
             ncu0 = 256;
-        int per_item = (int)(ntiles_all / (2 * ncu0 * 15));
+        int per_item = (int)(ntiles_all / (2 * ncu0 * (b->local ? 15 : 8)));
+        if (!b->local && per_item < 2 && ntiles_all >= 2 * (2 * ncu0)) per_item = 2;
         if (const char *ev = getenv("LF2_BATCH_TILES_PER_ITEM")) per_item = atoi(ev);
         per_item = per_item < 1 ? 1 : per_item > 64 ? 64 : per_item;
         b->per_item = per_item;
