@@ -551,10 +551,11 @@ __device__ __forceinline__ void dft_first(c32 (&v)[R], const c32 *tw)
         Dft<R, S>::run(v);
 }
 
-// A first stage's hooks: on each value it loads from memory (row engine),
-// and between its loads and its butterflies.
+// A first stage's hooks: on the values of a butterfly it loads from memory
+// (row engine), and between its loads and its butterflies.
 struct NoHook {
-    __device__ __forceinline__ void value(c32) const {}
+    template <int R>
+    __device__ __forceinline__ void values(const c32 (&)[R]) const {}
     __device__ __forceinline__ void loaded() const {}
 };
 
@@ -719,10 +720,7 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout, c
                     v[i][r] = buf[l * LP + lpad(j + r * Q)];
                 }
             }
-            if (SRC_G) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) hook.value(v[i][r]);
-            }
+            if (SRC_G) hook.values(v[i]);
         }
     }
     hook.loaded();
@@ -792,7 +790,10 @@ __device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout, con
             } else if (SRC_G) {
                 v = q < nvalid ? gin[in_at(q) + c] : c32{0.f, 0.f};
             }
-            if (SRC_G) hook.value(v);
+            if (SRC_G) {
+                const c32 u[1] = {v};
+                hook.values(u);
+            }
             if (DST_G && PACK) {
                 if (q < nvalid) {
                     float *fp = (float *)gout + out_at(q) + c;

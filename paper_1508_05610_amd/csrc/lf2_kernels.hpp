@@ -122,16 +122,20 @@ struct RealHook {
     double *ss;
     bool sum;
     Tabs tabs;
-    __device__ __forceinline__ void value(c32 v) const
+    template <int R>
+    __device__ __forceinline__ void values(const c32 (&v)[R]) const
     {
-        if (sum) *ss += (double)v.x * v.x + (double)v.y * v.y;
+        if (!sum) return;
+#pragma unroll
+        for (int r = 0; r < R; ++r) *ss += (double)v[r].x * v[r].x + (double)v[r].y * v[r].y;
     }
     __device__ __forceinline__ void loaded() const { tabs(); }
 };
 template <class Tabs>
 struct TabHook {
     Tabs tabs;
-    __device__ __forceinline__ void value(c32) const {}
+    template <int R>
+    __device__ __forceinline__ void values(const c32 (&)[R]) const {}
     __device__ __forceinline__ void loaded() const { tabs(); }
 };
 template <class Tabs>
@@ -175,18 +179,6 @@ struct XR2CGen {
         const int64_t r0 = blk * RB;
         const RowAt in_at = row_at(a.in_off, a.in_row, a.in_plane, a.n1, r0);
         const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
-        TableRegs<M, NT> wt;
-        TableRegs<NH, NT> wp;
-        if (tab && !table_first(M)) {
-            wt.load(a.tw, tid);
-            wp.load(a.tw_post, tid);
-        }
-        auto tabs = [&](bool sync) {
-            if (!tab) return;
-            wt.store((c32 *)(sm + O_TW), tid);
-            wp.store((c32 *)(sm + O_TWP), tid);
-            if (sync) __syncthreads();
-        };
         const int nv = rows_valid<RB>(a, r0);
         // the first stage reads each component's packed pairs straight from
         // the real rows (two float loads per point; no alignment needed)
@@ -200,9 +192,20 @@ struct XR2CGen {
                 buf, (const c32 *)a.in, nullptr, RowTable{ib}, RowTable{ib}, nv, tw, tid,
                 real_hook(ss, sumsq != nullptr, [] {}));
         } else {
+            TableRegs<M, NT> wt;
+            TableRegs<NH, NT> wp;
+            if (tab) {
+                wt.load(a.tw, tid);
+                wp.load(a.tw_post, tid);
+            }
             row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
                 buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
-                real_hook(ss, sumsq != nullptr, [&] { tabs(kPaired<M>); }));
+                real_hook(ss, sumsq != nullptr, [&] {
+                    if (!tab) return;
+                    wt.store((c32 *)(sm + O_TW), tid);
+                    wp.store((c32 *)(sm + O_TWP), tid);
+                    if (kPaired<M>) __syncthreads();  // else the first stage reads no table
+                }));
         }
         if (sumsq) block_sum_f64<NT>(ss, sumsq, (double *)(sm + O_RED));
         // X[k] = fe + W^k fo and X[M-k] = conj(fe - W^k fo) per component;
