@@ -240,6 +240,9 @@ bool plane_fits(const lf2_plan_s *p)
 //  - the other backward z passes of lines of 320 points and more, which read
 //    a spectrum not written just before, from 430 MB on: nontemporal (512^3
 //    real 235 -> 215, 384^3 complex 206 -> 178; 384^3 real, 226 MB, 93 -> 101).
+// Spectra in the paper's order keep narrow tiles along z, which there are rows
+// of one plane (backward, nontemporal: 512 x 256 x 320 with three components
+// 229 -> 475, 512^3 251 -> 512).
 // Narrow and wide tiles give the same bits; so P(k), which no plain z pass
 // feeds, does not depend on these.
 void default_tiles(lf2_plan_s *p)
@@ -248,8 +251,8 @@ void default_tiles(lf2_plan_s *p)
     const int ly = p->len[1], lz = p->len[2];
     if (!p->gen_only[1] && ly >= 768 && s_wide_supported(ly) && bytes > ((size_t)64 << 20))
         p->svar[1] = p->svar_b[1] = 1;
-    if (bytes <= ((size_t)256 << 20) || p->klay == 2) return;
-    const int64_t stride = 8 * (p->klay == 1 ? p->nxk * p->nc : p->nxk * p->nc * p->n[1]);
+    if (bytes <= ((size_t)256 << 20) || p->klay != 0) return;
+    const int64_t stride = 8 * p->nxk * p->nc * p->n[1];
     if (p->gen_only[2]) {
         if (p->nat[2] && lz >= 320 && bytes > ((size_t)430 << 20)) p->svar_b[2] = 2;
     } else if (s_reg_supported(lz)) {
