@@ -645,8 +645,17 @@ struct RowAt {
     __device__ __forceinline__ int64_t operator()(int q) const
     {
         if (flat) return base + (int64_t)q * row;
-        const uint32_t y = y0 + (uint32_t)q, dz = y / n1;
-        return base + (int64_t)dz * plane + (int64_t)(y - dz * n1) * row;
+        uint32_t y = y0 + (uint32_t)q, dz = 0;
+        if (y >= n1) {  // past the tile's first plane; past its second, divide
+            y -= n1;
+            dz = 1;
+            if (y >= n1) {
+                const uint32_t d = y / n1;
+                dz += d;
+                y -= d * n1;
+            }
+        }
+        return base + (int64_t)dz * plane + (int64_t)y * row;
     }
 };
 // The same from a table in LDS.
