@@ -222,7 +222,7 @@ bool plane_fits(const lf2_plan_s *p)
     if (p->ntot * p->nc * (p->kind == LF2_C2C ? 2 : 1) > kPlaneFloats) return false;
     if (!plane_axis_ok(p->len[0]) || !plane_axis_ok(p->len[1])) return false;
     return plane_lds_bytes(p->len[0], (int)p->nxk, p->nc, p->len[1]) <=
-           (p->n[2] < 256 ? (size_t)128 * 1024 : kPlaneLds);
+           (p->n[2] < 256 ? (size_t)128 * 1024 : p->n[2] == 256 ? kPlaneLds : kPlaneLds / 2);
 }
 
 // Tile settings of the y and z passes until one is set or tuned.  Narrow
