@@ -35,6 +35,7 @@ UNITS = [
       for t in (0, 2, 1) for p, nm in ((2, "c2c"), (0, "r2c"), (1, "c2r"))),
     *(("lf2_kragged.hip", [f"-DLF2_KR_PART={p}"], f"kragged{p}.o") for p in (0, 1)),
     ("lf2_ks.hip", [], "ks.o"),
+    ("lf2_kst.hip", [], "kst.o"),
     ("lf2_kreg.hip", [], "kreg.o"),
     ("lf2_kmisc.hip", [], "kmisc.o"),
     ("lf2_kplane.hip", [], "kplane.o"),

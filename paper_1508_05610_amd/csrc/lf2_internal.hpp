@@ -109,6 +109,9 @@ hipError_t launch_fused_reg(int len, const SArgs &a, size_t shm, int grid_cap, h
                             int *grid_used);
 hipError_t launch_strided_reg(int len, int sign, const SArgs &a, int grid_cap, hipStream_t s,
                               int *grid_used, int chunk, bool ntm);
+// z pass between the natural order and the paper's c2c order (lf2_kst.hip).
+hipError_t launch_transposed(int len, int sign, const SArgs &a, int grid_cap, hipStream_t s,
+                             int *grid_used);
 // LDS histogram copies of a fused last-axis tile of length len binning into
 // nbins bins, when the block's LDS is `budget` bytes: one per wave if they
 // fit with the tile, else one.  0 if len has no compiled fused tile.

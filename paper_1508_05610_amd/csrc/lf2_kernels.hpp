@@ -107,15 +107,6 @@ __host__ __device__ constexpr bool table_first(int L)
     return p.nodd == 1 && p.f[0] == 16;
 }
 
-// Waves a SIMD that the registers of a transposing tile's kernel leave room for:
-// six where its LDS does (three blocks a CU) and 80 registers hold it (not 16
-// and 384 points, which would spill), else four.  With 85 registers the c2c z
-// pass over 320^3 took 140 and 187 us, 123 and 150 with 80.
-__host__ __device__ constexpr int t_waves(int L)
-{
-    return s_bytes(L) <= 160 * 1024 / 3 && L >= 48 && L != 384 ? 6 : 4;
-}
-
 // Row offsets of a tile's first nv rows into LDS.
 template <int RB, int NT>
 __device__ __forceinline__ void fill_rows(int64_t *ib, const RowAt &at, int nv, int tid)
@@ -1425,8 +1416,7 @@ __global__ __launch_bounds__(kSWThreads) void k_strided_w(SArgs a)
 }
 
 template <int L, int S>
-__global__ __launch_bounds__(kSThreads)
-    __attribute__((amdgpu_waves_per_eu(t_waves(L)))) void k_strided_t(SArgs a)
+__global__ __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_strided_t(SArgs a)
 {
     using T = STileT<L, S, kSThreads>;
     __shared__ __align__(16) char sm[T::BYTES];
