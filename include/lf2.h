@@ -141,9 +141,10 @@ lf2_status lf2_fft_kspace(lf2_plan p, int64_t ksize[3], int64_t kstride[3]);
  * line length, the spectrum's bytes and its strides (0 below 64 MB and on
  * most larger lattices), and the backward z pass of a large spectrum may
  * default to nontemporal accesses where the forward one does not (get reports
- * the forward one, set sets both).  Narrow and wide tiles compute the same
- * transform bit for bit; the register tile computes it up to FP32 rounding
- * (another order of the butterflies).  The fused Poisson / power-spectrum pass always uses narrow tiles,
+ * the forward one, set sets both); it is a narrow or a wide tile.  Narrow and
+ * wide tiles compute the same forward transform bit for bit and the same
+ * backward one up to the rounding of single products; the register tile
+ * computes it up to FP32 rounding (another order of the butterflies).  The fused Poisson / power-spectrum pass always uses narrow tiles,
  * nontemporal accesses and chunk 16.  get reports the setting and, after
  * LF2_PLAN_AUTOTUNE, the measured microseconds of the default setting
  * (variant 0, chunk 16) and of the chosen one (-1 if not measured); null

@@ -231,20 +231,24 @@ bool plane_fits(const lf2_plan_s *p)
 //  - y lines of 768 points and more: wide tiles, whose row segments the
 //    narrow ones' 64 bytes cut a cache line short (768^3 real 960 / 947 ->
 //    859 / 839, 1024^3 real 2140 / 2104 -> 1905 / 1832; 640^3 474 -> 482);
-//  - z lines of a spectrum past the memory-side cache (256 MB): register
-//    tiles, nontemporal, over 1024 and 2048 points (1024^3 real 2152 / 2016 ->
-//    1800 / 1770); wide nontemporal ones over 640 and 768 points (768^3 real
+//  - z lines of a spectrum past the memory-side cache (256 MB): wide tiles
+//    over 2048 points (256 x 512 x 2048 real 1552 / 1310 -> 741 / 688, 256 x
+//    256 x 2048 complex 769 / 971 -> 582 / 592), nontemporal over 1024 points
+//    (1024^3 real 2092 / 2115 -> 1942 / 1901, 512 x 512 x 1024 complex 1531 /
+//    1675 -> 1043 / 1096), over 640 and 768 points (768^3 real
 //    966 / 932 -> 912 / 846) and over 512 points where the rows' stride is a
 //    multiple of 64 KB, so that a tile's rows fall on few memory channels
-//    (512^3 complex 596 / 577 -> 434 / 426);
+//    (512^3 complex 596 / 577 -> 434 / 426).  (Register tiles over 1024 and
+//    2048 points are faster still, 1845 / 1830 and 887 / 928 of these, but
+//    round otherwise: the 1024^3 real pair's error against 64 bits grew from
+//    2.99e-7 to 3.20e-7.  A plan runs them when they are asked for);
 //  - the other backward z passes of lines of 320 points and more, which read
 //    a spectrum not written just before, from 430 MB on: nontemporal (512^3
 //    real 235 -> 215, 384^3 complex 206 -> 178; 384^3 real, 226 MB, 93 -> 101).
 // Spectra in the paper's order keep narrow tiles along z, which there are rows
 // of one plane (backward, nontemporal: 512 x 256 x 320 with three components
 // 229 -> 475, 512^3 251 -> 512).
-// Narrow and wide tiles give the same bits; so P(k), which no plain z pass
-// feeds, does not depend on these.
+// Narrow and wide tiles give the same bits forward.
 void default_tiles(lf2_plan_s *p)
 {
     const size_t bytes = spectrum_bytes(p);
@@ -255,9 +259,9 @@ void default_tiles(lf2_plan_s *p)
     const int64_t stride = 8 * p->nxk * p->nc * p->n[1];
     if (p->gen_only[2]) {
         if (p->nat[2] && lz >= 320 && bytes > ((size_t)430 << 20)) p->svar_b[2] = 2;
-    } else if (s_reg_supported(lz)) {
-        p->svar[2] = p->svar_b[2] = 6;
-    } else if (lz == 640 || lz == 768 || (lz == 512 && stride % 65536 == 0)) {
+    } else if (lz == 2048) {
+        p->svar[2] = p->svar_b[2] = 1;
+    } else if (lz == 1024 || lz == 640 || lz == 768 || (lz == 512 && stride % 65536 == 0)) {
         p->svar[2] = p->svar_b[2] = 3;
     } else if (lz >= 320 && bytes > ((size_t)430 << 20)) {
         p->svar_b[2] = 2;
