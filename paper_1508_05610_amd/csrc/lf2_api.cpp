@@ -245,6 +245,9 @@ bool plane_fits(const lf2_plan_s *p)
 //  - the other backward z passes of lines of 320 points and more, which read
 //    a spectrum not written just before, from 430 MB on: nontemporal (512^3
 //    real 235 -> 215, 384^3 complex 206 -> 178; 384^3 real, 226 MB, 93 -> 101).
+//    Not the run-time-schedule lengths, whose tiles lose by it (back, normal
+//    and nontemporal: 540^3 356 and 689, 600^3 455 and 549, 900 x 400 x 900 808
+//    and 963, 400 x 400 x 480 complex 334 and 378; 450 points 334 and 302).
 // Spectra in the paper's order keep narrow tiles along z, which there are rows
 // of one plane (backward, nontemporal: 512 x 256 x 320 with three components
 // 229 -> 475, 512^3 251 -> 512).
@@ -255,11 +258,9 @@ void default_tiles(lf2_plan_s *p)
     const int ly = p->len[1], lz = p->len[2];
     if (!p->gen_only[1] && ly >= 768 && s_wide_supported(ly) && bytes > ((size_t)64 << 20))
         p->svar[1] = p->svar_b[1] = 1;
-    if (bytes <= ((size_t)256 << 20) || p->klay != 0) return;
+    if (bytes <= ((size_t)256 << 20) || p->klay != 0 || p->gen_only[2]) return;
     const int64_t stride = 8 * p->nxk * p->nc * p->n[1];
-    if (p->gen_only[2]) {
-        if (p->nat[2] && lz >= 320 && bytes > ((size_t)430 << 20)) p->svar_b[2] = 2;
-    } else if (lz == 2048) {
+    if (lz == 2048) {
         p->svar[2] = p->svar_b[2] = 1;
     } else if (lz == 1024 || lz == 640 || lz == 768 || (lz == 512 && stride % 65536 == 0)) {
         p->svar[2] = p->svar_b[2] = 3;

@@ -55,3 +55,27 @@ def test_rounds_as_narrow_tiles(lf2, shape, kind, ncomp):
                  for t in (b, bq))
         print(f"  backward error {e:.4e}, narrow tiles {eq:.4e}", flush=True)
         assert e <= 1.02 * eq
+
+
+def _kernels(fn):
+    """Names of the kernels a call launches."""
+    from paper_1508_05610_amd import _lib
+    _lib.lf2_profile_enable(1)
+    try:
+        fn()
+        return " ".join(_lib.profile_table())
+    finally:
+        _lib.lf2_profile_enable(0)
+
+
+# backward z passes: nontemporal in narrow tiles of 320 to 512 points past 430 MB,
+# normal over lengths that take run-time schedules
+@pytest.mark.parametrize("shape,kernel", [
+    ((320, 640, 540), "k_strided<540,1,0,0> z"), ((360, 640, 540), "k_strided<540,1,0,0> z"),
+    ((600, 400, 480), "k_strided<480,1,0,0> z"), ((384, 640, 512), "k_strided<512,1,0,1> z")])
+def test_backward_z_kernel(lf2, shape, kernel):
+    print(f"case default backward z {shape}", flush=True)
+    p = lf2.Plan(shape)
+    F = torch.zeros(p.k_shape, dtype=torch.complex64, device=dev())
+    names = _kernels(lambda: p.backward(F))
+    assert kernel in names, names
