@@ -235,10 +235,14 @@ bool plane_fits(const lf2_plan_s *p)
 //    over 2048 points (256 x 512 x 2048 real 1552 / 1310 -> 741 / 688, 256 x
 //    256 x 2048 complex 769 / 971 -> 582 / 592), nontemporal over 1024 points
 //    (1024^3 real 2092 / 2115 -> 1942 / 1901, 512 x 512 x 1024 complex 1531 /
-//    1675 -> 1043 / 1096), over 640 and 768 points (768^3 real
-//    966 / 932 -> 912 / 846) and over 512 points where the rows' stride is a
-//    multiple of 64 KB, so that a tile's rows fall on few memory channels
-//    (512^3 complex 596 / 577 -> 434 / 426).  (Register tiles over 1024 and
+//    1675 -> 1043 / 1096), and over 512, 640 and 768 points where the rows'
+//    stride is a multiple of 64 KB, so that a tile's rows fall on few memory
+//    channels (512^3 complex 596 / 577 -> 434 / 426, 512 x 512 x 640 complex
+//    922 / 994 -> 681 / 717, 512 x 384 x 768 complex 620 / 639 -> 566 / 600).
+//    At other strides 640 and 768 points take them forward alone (768^3 real
+//    947 -> 905 and 899 -> 880 on two cards, 640^3 538 -> 504 and 472 -> 478;
+//    back 875 -> 929, 876 -> 944, 528 -> 531, 491 -> 517, 384 x 512 x 768 270 ->
+//    308).  (Register tiles over 1024 and
 //    2048 points are faster still, 1845 / 1830 and 887 / 928 of these, but
 //    round otherwise: the 1024^3 real pair's error against 64 bits grew from
 //    2.99e-7 to 3.20e-7.  A plan runs them when they are asked for);
@@ -262,8 +266,10 @@ void default_tiles(lf2_plan_s *p)
     const int64_t stride = 8 * p->nxk * p->nc * p->n[1];
     if (lz == 2048) {
         p->svar[2] = p->svar_b[2] = 1;
-    } else if (lz == 1024 || lz == 640 || lz == 768 || (lz == 512 && stride % 65536 == 0)) {
+    } else if (lz == 1024 || ((lz == 512 || lz == 640 || lz == 768) && stride % 65536 == 0)) {
         p->svar[2] = p->svar_b[2] = 3;
+    } else if (lz == 640 || lz == 768) {
+        p->svar[2] = 3;
     } else if (lz >= 320 && bytes > ((size_t)430 << 20)) {
         p->svar_b[2] = 2;
     }

@@ -28,12 +28,14 @@ def _random(shape, dtype, seed):
     return torch.randn(shape, generator=g, device=dev(), dtype=dtype)
 
 
-# spectra of 256 to 340 MiB, past the memory-side cache: z lines of every length
+# spectra of 256 to 520 MiB, past the memory-side cache: z lines of every length
 # with a default of its own, rows a multiple of 64 KB apart (complex) and not
 # (real); long y lines
 @pytest.mark.parametrize("shape,kind,ncomp", [
     ((256, 256, 1024), 0, 1), ((128, 320, 1024), 1, 1), ((256, 128, 2048), 0, 1),
-    ((64, 320, 2048), 1, 1)])
+    ((64, 320, 2048), 1, 1), ((320, 384, 640), 0, 1), ((256, 320, 640), 1, 1),
+    ((256, 384, 768), 0, 1), ((128, 128, 768), 1, 3), ((256, 320, 512), 1, 1),
+    ((512, 512, 512), 0, 1), ((128, 1024, 320), 0, 1), ((96, 768, 320), 1, 2)])
 def test_rounds_as_narrow_tiles(lf2, shape, kind, ncomp):
     print(f"case default tiles {shape} kind={kind} ncomp={ncomp}", flush=True)
     p, q = (lf2.Plan(shape, kind, ncomp=ncomp) for _ in range(2))
@@ -69,10 +71,12 @@ def _kernels(fn):
 
 
 # backward z passes: nontemporal in narrow tiles of 320 to 512 points past 430 MB,
-# normal over lengths that take run-time schedules
+# normal over lengths that take run-time schedules and over 640 and 768 points
+# (rows not a multiple of 64 KB apart)
 @pytest.mark.parametrize("shape,kernel", [
     ((320, 640, 540), "k_strided<540,1,0,0> z"), ((360, 640, 540), "k_strided<540,1,0,0> z"),
-    ((600, 400, 480), "k_strided<480,1,0,0> z"), ((384, 640, 512), "k_strided<512,1,0,1> z")])
+    ((600, 400, 480), "k_strided<480,1,0,0> z"), ((384, 640, 512), "k_strided<512,1,0,1> z"),
+    ((320, 384, 640), "k_strided<640,1,0,0> z"), ((256, 384, 768), "k_strided<768,1,0,0> z")])
 def test_backward_z_kernel(lf2, shape, kernel):
     print(f"case default backward z {shape}", flush=True)
     p = lf2.Plan(shape)
