@@ -138,7 +138,7 @@ lf2_status lf2_fft_kspace(lf2_plan p, int64_t ksize[3], int64_t kstride[3]);
  * nontemporal global loads and stores (they pay on long strides, where each
  * line is touched once).  chunk = consecutive tiles given to one XCD in the
  * tile order (1..1024, default 16).  The default variant depends on the
- * line length, the spectrum's bytes and its strides (0 below 64 MB and on
+ * line length, the spectrum's bytes and its strides (0 up to 256 MB and on
  * most larger lattices), and the backward z pass of a large spectrum may
  * default to nontemporal accesses where the forward one does not (get reports
  * the forward one, set sets both); it is a narrow or a wide tile.  Narrow and

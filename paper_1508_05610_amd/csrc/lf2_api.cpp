@@ -225,44 +225,45 @@ bool plane_fits(const lf2_plan_s *p)
            (p->n[2] < 256 ? (size_t)128 * 1024 : p->n[2] == 256 ? kPlaneLds : kPlaneLds / 2);
 }
 
-// Tile settings of the y and z passes until one is set or tuned.  Narrow
-// tiles with normal accesses, except where another setting measured faster
-// (us a pass, forward / backward):
-//  - y lines of 768 points and more: wide tiles, whose row segments the
-//    narrow ones' 64 bytes cut a cache line short (768^3 real 960 / 947 ->
-//    859 / 839, 1024^3 real 2140 / 2104 -> 1905 / 1832; 640^3 474 -> 482);
-//  - z lines of a spectrum past the memory-side cache (256 MB): wide tiles
-//    over 2048 points (256 x 512 x 2048 real 1552 / 1310 -> 741 / 688, 256 x
-//    256 x 2048 complex 769 / 971 -> 582 / 592), nontemporal over 1024 points
-//    (1024^3 real 2092 / 2115 -> 1942 / 1901, 512 x 512 x 1024 complex 1531 /
-//    1675 -> 1043 / 1096), and over 512, 640 and 768 points where the rows'
-//    stride is a multiple of 64 KB, so that a tile's rows fall on few memory
-//    channels (512^3 complex 596 / 577 -> 434 / 426, 512 x 512 x 640 complex
-//    922 / 994 -> 681 / 717, 512 x 384 x 768 complex 620 / 639 -> 566 / 600).
-//    At other strides 640 and 768 points take them forward alone (768^3 real
-//    947 -> 905 and 899 -> 880 on two cards, 640^3 538 -> 504 and 472 -> 478;
-//    back 875 -> 929, 876 -> 944, 528 -> 531, 491 -> 517, 384 x 512 x 768 270 ->
-//    308).  (Register tiles over 1024 and
-//    2048 points are faster still, 1845 / 1830 and 887 / 928 of these, but
-//    round otherwise: the 1024^3 real pair's error against 64 bits grew from
-//    2.99e-7 to 3.20e-7.  A plan runs them when they are asked for);
-//  - the other backward z passes of lines of 320 points and more, which read
-//    a spectrum not written just before, from 430 MB on: nontemporal (512^3
-//    real 235 -> 215, 384^3 complex 206 -> 178; 384^3 real, 226 MB, 93 -> 101).
-//    Not the run-time-schedule lengths, whose tiles lose by it (back, normal
-//    and nontemporal: 540^3 356 and 689, 600^3 455 and 549, 900 x 400 x 900 808
-//    and 963, 400 x 400 x 480 complex 334 and 378; 450 points 334 and 302).
-// Spectra in the paper's order keep narrow tiles along z, which there are rows
-// of one plane (backward, nontemporal: 512 x 256 x 320 with three components
-// 229 -> 475, 512^3 251 -> 512).
-// Narrow and wide tiles give the same bits forward.
+// Tile settings of the y and z passes until one is set or tuned.  Narrow tiles
+// with normal accesses, except where another setting measured faster (us a pass,
+// forward / backward), on spectra past the memory-side cache (256 MB):
+//  - y lines of 768 points and more: wide tiles, whose row segments the narrow
+//    ones' 64 bytes cut a cache line short (768^3 real 960 / 947 -> 859 / 839,
+//    1024^3 real 2140 / 2104 -> 1905 / 1832; 128 x 2048 x 64 complex with three
+//    components 206 / 214 -> 182 / 189; 640^3 474 -> 482).  Smaller spectra lose
+//    by them: 512 x 1024 x 64 complex (256 MB) 99 / 105 -> 112 / 110, 96 x 1024 x
+//    96 complex 35 / 30 -> 41 / 38, 256 x 768 x 128 real 58 / 48 -> 59 / 53;
+//  - z lines: wide tiles over 2048 points (256 x 512 x 2048 real 1552 / 1310 ->
+//    741 / 688, 256 x 256 x 2048 complex 769 / 971 -> 582 / 592), nontemporal
+//    over 1024 points (1024^3 real 2092 / 2115 -> 1942 / 1901, 512 x 512 x 1024
+//    complex 1531 / 1675 -> 1043 / 1096), and over 512, 640 and 768 points where
+//    the rows' stride is a multiple of 64 KB, so that a tile's rows fall on few
+//    memory channels (512^3 complex 596 / 577 -> 434 / 426, 512 x 512 x 640
+//    complex 922 / 994 -> 681 / 717, 512 x 384 x 768 complex 620 / 639 -> 566 /
+//    600). At other strides 640 and 768 points take them forward alone (768^3
+//    real 947 -> 905 and 899 -> 880 on two cards, 640^3 538 -> 504 and 472 ->
+//    478; back 875 -> 929, 876 -> 944, 528 -> 531, 491 -> 517, 384 x 512 x 768
+//    270 -> 308).  (Register tiles over 1024 and 2048 points are faster still,
+//    1845 / 1830 and 887 / 928 of these, but round otherwise: the 1024^3 real
+//    pair's error against 64 bits grew from 2.99e-7 to 3.20e-7.  A plan runs them
+//    when they are asked for);
+//  - the other backward z passes of lines of 320 points and more, which read a
+//    spectrum not written just before, from 430 MB on: nontemporal (512^3 real
+//    235 -> 215, 384^3 complex 206 -> 178; 384^3 real, 226 MB, 93 -> 101). Not
+//    the run-time-schedule lengths, whose tiles lose by it (back, normal and
+//    nontemporal: 540^3 356 and 689, 600^3 455 and 549, 900 x 400 x 900 808 and
+//    963, 400 x 400 x 480 complex 334 and 378; 450 points 334 and 302).
+// Spectra in the paper's order keep narrow tiles along z, which there are rows of
+// one plane (backward, nontemporal: 512 x 256 x 320 with three components 229 ->
+// 475, 512^3 251 -> 512). Narrow and wide tiles give the same bits forward.
 void default_tiles(lf2_plan_s *p)
 {
     const size_t bytes = spectrum_bytes(p);
     const int ly = p->len[1], lz = p->len[2];
-    if (!p->gen_only[1] && ly >= 768 && s_wide_supported(ly) && bytes > ((size_t)64 << 20))
-        p->svar[1] = p->svar_b[1] = 1;
-    if (bytes <= ((size_t)256 << 20) || p->klay != 0 || p->gen_only[2]) return;
+    if (bytes <= ((size_t)256 << 20)) return;
+    if (!p->gen_only[1] && ly >= 768 && s_wide_supported(ly)) p->svar[1] = p->svar_b[1] = 1;
+    if (p->klay != 0 || p->gen_only[2]) return;
     const int64_t stride = 8 * p->nxk * p->nc * p->n[1];
     if (lz == 2048) {
         p->svar[2] = p->svar_b[2] = 1;

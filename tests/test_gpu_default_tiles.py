@@ -83,3 +83,16 @@ def test_backward_z_kernel(lf2, shape, kernel):
     F = torch.zeros(p.k_shape, dtype=torch.complex64, device=dev())
     names = _kernels(lambda: p.backward(F))
     assert kernel in names, names
+
+
+# long y lines: wide tiles past 256 MB only
+@pytest.mark.parametrize("shape,kind,ncomp,kernel", [
+    ((96, 1024, 96), 1, 1, "k_strided<1024,%d,0,0> y"), ((512, 1024, 64), 1, 1, "k_strided<1024,%d,0,0> y"),
+    ((96, 768, 320), 1, 2, "k_strided_w<768,%d,0> y")])
+def test_y_kernel(lf2, shape, kind, ncomp, kernel):
+    print(f"case default y {shape}", flush=True)
+    p = lf2.Plan(shape, kind, ncomp=ncomp)
+    x = torch.zeros(p.x_shape, dtype=torch.complex64, device=dev())
+    F = p.forward(x)
+    assert kernel % -1 in _kernels(lambda: p.forward(x))
+    assert kernel % 1 in _kernels(lambda: p.backward(F))
