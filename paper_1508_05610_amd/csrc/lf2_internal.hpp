@@ -6,6 +6,7 @@
 
 #include "lf2_batch_items.hpp"
 #include "lf2_gen.hpp"
+#include "lf2_rules.hpp"
 
 namespace lf2 {
 
@@ -118,22 +119,6 @@ hipError_t launch_transposed(int len, int sign, const SArgs &a, int grid_cap, hi
 // persistent: the persistent batch kernel's blocks of 512 threads (the others
 // have e_nt<len>).
 int epi_hist_copies(int len, int nbins, size_t budget, bool persistent = false);
-
-// Blocks of a binned z pass over lines of `len` points: one round of what the
-// chip's 256 CUs hold at `lds` bytes and `waves` waves a block, 16 waves a CU.
-// More blocks than that only repeat the tables' set-up.  With 1024 blocks and
-// with a round (us): Poisson with 32 bins at 256^3 153 and 149, 400^3 594 and
-// 556, 600^3 2590 and 2482 (300^3 295 and 298), P(k) at 256^3 87 and 83, 512^3
-// 538 and 530.  Lines of 640 points and more take long enough a tile that the
-// balance of 1024 blocks is worth more (P(k) at 640^3 1287 and 1293, 768^3
-// 2223 and 2269, 1024^3 5634 and 5801).
-inline int binning_blocks(int len, int cap, size_t lds, int waves)
-{
-    if (len >= 640) return cap;
-    const int by_lds = (int)(160 * 1024 / lds), by_waves = 16 / waves;
-    const int n = by_lds < by_waves ? by_lds : by_waves, r = 256 * (n < 1 ? 1 : n);
-    return cap < r ? cap : r;
-}
 
 // Kernels of the lengths of LF2_RAGGED_LENGTHS (lf2_kx.hip, lf2_kragged.hip):
 // the x tiles, and the narrow strided tile with its fused epilogue.  The

@@ -427,7 +427,7 @@ static hipError_t launch_fused_len(SArgs a, int grid_cap, hipStream_t s, int *gr
     const int64_t ntiles = (a.ncols + T::B - 1) / T::B;
     const int chunk = a.xcd_chunk;
     const int64_t span = (ntiles + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-    if (pk) grid_cap = binning_blocks(L, grid_cap, T::LDS + shm, kWaves);
+    if (pk) grid_cap = binning_blocks(L, grid_cap, T::LDS + shm, kWaves, true);
     const int g = (int)(span < grid_cap ? span : grid_cap);
     if (grid_used) *grid_used = g;
     if (a.mt.k2z_unit > 0.0)
