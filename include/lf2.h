@@ -93,7 +93,8 @@ typedef enum { LF2_FORWARD = -1, LF2_BACKWARD = +1 } lf2_direction;
                                          (k_x, k_z, k_y), i.e. C array [N1][N2][Nh][ncomp]; c2c
                                          (k_z, k_x, k_y), i.e. [N1][N0][N2][ncomp] */
 #define LF2_PLAN_AUTOTUNE 0x10u       /* time the tile variants and XCD chunk sizes of the y and
-                                         z passes at plan time and keep the fastest per axis */
+                                         z passes in both directions at plan time and keep the
+                                         fastest per axis and direction */
 /* Poisson flags. */
 #define LF2_POISSON_CONTINUOUS_K2 0u  /* k^2 = sum_i (2 pi nt_i / (N_i dx))^2 (default) */
 #define LF2_POISSON_DISCRETE_K2 1u    /* k^2 = sum_i (2/dx)^2 sin^2(pi n_i / N_i) */
@@ -140,15 +141,16 @@ lf2_status lf2_fft_kspace(lf2_plan p, int64_t ksize[3], int64_t kstride[3]);
  * tile order (1..1024, default 16).  The default variant depends on the
  * line length, the spectrum's bytes and its strides (0 up to 256 MB and on
  * most larger lattices), and the backward z pass of a large spectrum may
- * default to nontemporal accesses where the forward one does not (get reports
- * the forward one, set sets both); it is a narrow or a wide tile.  Narrow and
+ * default to nontemporal accesses where the forward one does not, and
+ * LF2_PLAN_AUTOTUNE may choose another variant backward than forward (get reports
+ * the forward one, set sets both); the default is a narrow or a wide tile.  Narrow and
  * wide tiles compute the same forward transform bit for bit and the same
  * backward one up to the rounding of single products; the register tile
  * computes it up to FP32 rounding (another order of the butterflies).  The fused Poisson / power-spectrum pass always uses narrow tiles,
  * nontemporal accesses and chunk 16.  get reports the setting and, after
- * LF2_PLAN_AUTOTUNE, the measured microseconds of the default setting
- * (variant 0, chunk 16) and of the chosen one (-1 if not measured); null
- * outputs are skipped; variant -1 means the axis runs a run-time radix
+ * LF2_PLAN_AUTOTUNE, the measured microseconds a pass (mean of the two
+ * directions) of the plan's default setting and of the chosen one (-1 if not
+ * measured); null outputs are skipped; variant -1 means the axis runs a run-time radix
  * schedule (lf2_plan_get_schedule).  set overrides the setting and returns
  * the axis to its compiled kernels (LF2_ERR_UNSUPPORTED for wide tiles or
  * the register tile on a length without them, or for a length without

@@ -836,23 +836,39 @@ bool x_lane_exchange_ok(const lf2_plan_s *p)
 // lanes), the tile variants and XCD chunk sizes of the y and z passes, and the
 // candidate radix schedules of the run-time-schedule kernels (every axis
 // without a compiled kernel, and the y and z passes as an alternative to
-// the compiled ones), on a scratch spectrum of the plan's shape (one
-// warm-up, then the mean of three launches each; the compiled tile settings
-// of the y and z passes in two sweeps, each keeping its faster time), and
-// keep the fastest, the default (compiled narrow tiles, chunk 16, or the
-// first schedule) first.
-// Without memory for the scratch spectrum the defaults stay.
+// the compiled ones), on a scratch spectrum of the plan's shape, and keep the
+// fastest.  Each is timed in both directions (one warm-up, then the mean of
+// three launches each way; the compiled tile settings of the y and z passes in
+// two sweeps, each keeping its faster times).  The plan's own default
+// (default_tiles with chunk 16, compiled ragged tiles, or the first schedule)
+// stays unless another beats it by 3 %; the y and z passes may take another
+// variant backward than forward (a 512^3 real z pass backward: nontemporal 208
+// us, normal 229; forward 198 and 194).  An axis keeps its winner only if whole
+// transforms, forward and back, gain by it: a pass repeated on one array finds
+// its rows in the memory-side cache as a transform does not (384^3 complex, the
+// backward z pass: normal accesses won by 3 % in the repeats and lost by 12 % in
+// the transform).  Last, where the plan runs x and y of its planes in one
+// launch, that launch against the two passes so tuned.  Without memory for the
+// scratch arrays the defaults stay, or the winners of the repeats.
 lf2_status autotune(lf2_plan p)
 {
     const size_t bytes = spectrum_bytes(p);
-    void *w = nullptr, *w2 = nullptr;
+    const int64_t h2 = 2 * p->halo;
+    const size_t xbytes = (size_t)((p->n[0] + h2) * (p->n[1] + h2) * (p->n[2] + h2)) * p->nc *
+                          (p->kind == LF2_R2C ? 4 : 8);
+    // a spectrum, an x-space array (or spectrum), and the workspace's spectrum
+    void *w = nullptr, *w2 = nullptr, *w3 = nullptr;
     if (hipMalloc(&w, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return LF2_OK;
     }
-    if ((p->gen_only[0] || x_lane_exchange_ok(p)) && hipMalloc(&w2, bytes) != hipSuccess) {
+    const size_t bytes2 = xbytes > bytes ? xbytes : bytes;
+    if (hipMalloc(&w2, bytes2) != hipSuccess) {
         (void)hipGetLastError();
         w2 = nullptr;
+    } else if (hipMalloc(&w3, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        w3 = nullptr;
     }
     hipStream_t s = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -861,49 +877,61 @@ lf2_status autotune(lf2_plan p)
         if (e != hipSuccess && st == LF2_OK) st = fail(LF2_ERR_DEVICE, "autotune %s: %s", what, hipGetErrorString(e));
         return st == LF2_OK;
     };
-    // mean microseconds of three launches after a warm-up (-1 on failure)
-    auto time_it = [&](auto &&launch) -> double {
+    // mean microseconds of n launches after a warm-up (-1 on failure)
+    auto time_it = [&](auto &&launch, int n = 3) -> double {
         hip_ok(launch(), "launch");
         hip_ok(hipEventRecord(e0, s), "record");
-        for (int r = 0; r < 3; ++r) hip_ok(launch(), "launch");
+        for (int r = 0; r < n; ++r) hip_ok(launch(), "launch");
         hip_ok(hipEventRecord(e1, s), "record");
         float ms = 0.f;
         if (!hip_ok(hipEventSynchronize(e1), "sync") || !hip_ok(hipEventElapsedTime(&ms, e0, e1), "elapsed"))
             return -1.0;
-        return 1e3 * ms / 3.0;
+        return 1e3 * ms / n;
+    };
+    // both directions of launch(sign) together (-1 on failure)
+    auto time_both = [&](auto &&launch, int n = 3) -> double {
+        const double f = time_it([&] { return launch(-1); }, n);
+        const double b = f < 0 ? -1.0 : time_it([&] { return launch(1); }, n);
+        return b < 0 ? -1.0 : f + b;
     };
     static const int kChunks[] = {16, 4, 64};  // the default first
+    const lf2_plan_s def = *p;
     if (hip_ok(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "stream") &&
         hip_ok(hipEventCreate(&e0), "event") && hip_ok(hipEventCreate(&e1), "event") &&
         hip_ok(hipMemsetAsync(w, 0, bytes, s), "memset") &&
-        (!w2 || hip_ok(hipMemsetAsync(w2, 0, bytes, s), "memset"))) {
-        // x axis without a compiled kernel: its schedules, on dense rows
+        (!w2 || hip_ok(hipMemsetAsync(w2, 0, bytes2, s), "memset"))) {
+        // x axis without a compiled kernel: its schedules, on dense rows of w2
         if (p->gen_only[0] && w2) {
-            XArgs a{};
-            a.nrows = p->n[1] * p->n[2];
-            a.n1 = (int)p->n[1];
-            a.tw = p->tw[0];
-            a.tw_post = p->tw_post;
             const int64_t c1 = p->nxk * p->nc;
             const int64_t xr = p->n[0] * p->nc;  // floats (r2c) or complex (c2c) per row
-            a.in = w;
-            a.out = w2;
-            a.in_row = xr;
-            a.in_plane = xr * p->n[1];
-            a.out_row = c1;
-            a.out_plane = c1 * p->n[1];
-            const int mode = p->kind == LF2_R2C ? 1 : 0;
+            auto args = [&](int sign) {
+                XArgs a{};
+                a.nrows = p->n[1] * p->n[2];
+                a.n1 = (int)p->n[1];
+                a.tw = p->tw[0];
+                a.tw_post = p->tw_post;
+                a.in = sign < 0 ? w2 : w;
+                a.out = sign < 0 ? w : w2;
+                a.in_row = sign < 0 ? xr : c1;
+                a.out_row = sign < 0 ? c1 : xr;
+                a.in_plane = a.in_row * p->n[1];
+                a.out_plane = a.out_row * p->n[1];
+                return a;
+            };
             double best = -1.0;
             if (p->nat[0]) {  // the compiled tiles first: the default
-                best = p->tune_us[0][0] = time_it([&] {
-                    return mode == 1 ? launch_x_r2c(p->len[0], p->nc, a, s)
-                                     : launch_x_c2c(p->len[0], p->nc, -1, a, s);
+                best = p->tune_us[0][0] = time_both([&](int sign) {
+                    const XArgs a = args(sign);
+                    return p->kind == LF2_C2C ? launch_x_c2c(p->len[0], p->nc, sign, a, s)
+                           : sign < 0         ? launch_x_r2c(p->len[0], p->nc, a, s)
+                                              : launch_x_c2r(p->len[0], p->nc, a, s);
                 });
             }
             for (const GSched &sc : sched_candidates(p->len[0])) {
                 if (st != LF2_OK) break;
-                const double us = time_it([&] {
-                    return launch_gx(mode, -1, a, sc, p->len[0], p->nc, p->gen_rb, s);
+                const double us = time_both([&](int sign) {
+                    const int mode = p->kind == LF2_C2C ? 0 : sign < 0 ? 1 : 2;
+                    return launch_gx(mode, sign, args(sign), sc, p->len[0], p->nc, p->gen_rb, s);
                 });
                 if (p->tune_us[0][0] < 0) p->tune_us[0][0] = us;
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
@@ -926,8 +954,9 @@ lf2_status autotune(lf2_plan p)
             a.in_plane = a.out_plane = p->n[0] * p->n[1];
             double best = -1.0;
             for (int v = 0; v < 3 && st == LF2_OK; ++v) {
-                const double us = time_it([&] {
-                    return v == 0 ? launch_x_c2c(64, 1, -1, a, s) : launch_x_c2c_shfl(-1, v == 2, a, s);
+                const double us = time_both([&](int sign) {
+                    return v == 0 ? launch_x_c2c(64, 1, sign, a, s)
+                                  : launch_x_c2c_shfl(sign, v == 2, a, s);
                 });
                 if (v == 0) p->tune_us[0][0] = us;
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
@@ -945,49 +974,47 @@ lf2_status autotune(lf2_plan p)
             if (!p->gen_only[axis] || p->nat[axis]) {
                 // two sweeps over the settings, each setting keeping its
                 // faster time: a setting timed while the chip's clocks or
-                // memory state drift is timed again in the other sweep
-                // Order: the default first, then the nontemporal settings,
-                // then the rest; within 3 % the earlier one stays.  Timed in
+                // memory state drift is timed again in the other sweep.
+                // Order: the nontemporal settings, then the rest; within 3 % the
+                // earlier one stays.  Timed in
                 // short bursts, the cached-store settings of long-stride passes
                 // come out faster than they run inside a transform (the
                 // 3-component 512^3 z pass: plain wide tile 1.35-1.37 ms in the
                 // tuner, 1.53-1.67 ms in the transforms; nontemporal wide tile
                 // 1.33 ms and 1.40-1.42 ms), so ties go to the streaming ones.
-                std::vector<std::pair<int, int>> cfg{{0, 16}};
+                std::vector<TileTime> t;
                 for (int pass = 0; pass < 2; ++pass)
                     for (int v = 0; v < 8; ++v) {
                         if (((v & 2) != 0) != (pass == 0)) continue;
                         if ((v & 1) && !wide) continue;
                         if ((v & 4) && (!reg || (v & 1))) continue;
-                        for (int c : kChunks)
-                            if (v != 0 || c != 16) cfg.emplace_back(v, c);
+                        for (int c : kChunks) t.push_back({v, c, -1.0, -1.0});
                     }
-                std::vector<double> t(cfg.size(), -1.0);
                 for (int sweep = 0; sweep < 2 && st == LF2_OK; ++sweep)
-                    for (size_t i = 0; i < cfg.size() && st == LF2_OK; ++i) {
-                        const double us = time_it([&] {
-                            return launch_strided(p->len[axis], -1, a, kStridedGridCap, s, nullptr,
-                                                  cfg[i].first, cfg[i].second);
-                        });
-                        if (us >= 0 && (t[i] < 0 || us < t[i])) t[i] = us;
+                    for (TileTime &x : t) {
+                        for (int sign = -1; sign <= 1 && st == LF2_OK; sign += 2) {
+                            const double us = time_it([&] {
+                                return launch_strided(p->len[axis], sign, a, kStridedGridCap, s,
+                                                      nullptr, x.variant, x.chunk);
+                            });
+                            double &keep = sign < 0 ? x.fwd : x.bwd;
+                            if (us >= 0 && (keep < 0 || us < keep)) keep = us;
+                        }
+                        if (st != LF2_OK) break;
                     }
-                for (size_t i = 0; i < cfg.size(); ++i) {
-                    if (t[i] < 0) continue;
-                    if (i == 0) p->tune_us[axis][0] = t[i];  // variant 0, chunk 16
-                    // another setting must beat the current choice by 3 %, so
-                    // that timing noise does not flip the choice from run to run
-                    if (best < 0 || t[i] < 0.97 * best) {
-                        best = t[i];
-                        p->svar[axis] = p->svar_b[axis] = cfg[i].first;
-                        p->schunk[axis] = cfg[i].second;
-                    }
-                }
+                const TileChoice c = choose_tiles(
+                    t, TileChoice{p->svar[axis], p->svar_b[axis], p->schunk[axis], -1.0, -1.0});
+                p->tune_us[axis][0] = c.us_default;
+                best = c.us;
+                p->svar[axis] = c.fwd;
+                p->svar_b[axis] = c.bwd;
+                p->schunk[axis] = c.chunk;
             }
             const int b = gs_cols(p, p->len[axis], 0);
             for (const GSched &sc : sched_candidates(p->len[axis])) {
                 if (st != LF2_OK || b < 1) break;
-                const double us = time_it([&] {
-                    return launch_gs(-1, a, sc, p->len[axis], b, kStridedGridCap, s, nullptr);
+                const double us = time_both([&](int sign) {
+                    return launch_gs(sign, a, sc, p->len[axis], b, kStridedGridCap, s, nullptr);
                 });
                 if (p->tune_us[axis][0] < 0) p->tune_us[axis][0] = us;
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
@@ -999,6 +1026,61 @@ lf2_status autotune(lf2_plan p)
             }
             p->tune_us[axis][1] = best;
         }
+        // the winners in whole transforms (w2 laid out as the plan's x-space array)
+        if (w2 && w3 && st == LF2_OK) {
+            const lf2_plan_s tuned = *p;
+            auto take = [&](int i, const lf2_plan_s &from) {  // axis i's settings
+                p->svar[i] = from.svar[i];
+                p->svar_b[i] = from.svar_b[i];
+                p->schunk[i] = from.schunk[i];
+                p->gen[i] = from.gen[i];
+                p->nat[i] = from.nat[i];
+                p->sched[i] = from.sched[i];
+                if (i == 0) p->xx = from.xx;
+            };
+            const bool real = p->kind == LF2_R2C;
+            const int fwd = real ? 0 : 2, bwd = real ? 1 : 2;
+            // where lf2_fft_execute keeps the backward intermediate
+            void *W = !real && p->klay != 2 && p->halo == 0 ? w2 : w3;
+            auto one_pair = [&] {
+                lf2_status e = run_xy(p, fwd, -1, x_args(p, w2, w, true, false, real), w, s, p->plane);
+                if (!e) e = run_strided(p, 2, -1, s_args(p, 2, w, w, EPI_STORE), kStridedGridCap, s, nullptr);
+                if (!e) e = run_strided(p, 2, 1, s_args(p, 2, w, W, EPI_STORE), kStridedGridCap, s, nullptr);
+                if (!e) e = run_xy(p, bwd, 1, x_args(p, W, w2, false, true, real), W, s, p->plane);
+                return e == LF2_OK ? hipSuccess : hipErrorUnknown;
+            };
+            auto pair = [&] { return time_it(one_pair, bytes < ((size_t)16 << 20) ? 20 : 4); };
+            const bool was_quiet = prof::t_quiet;
+            prof::t_quiet = true;
+            p->plane = false;
+            for (int i = 0; i < 3; ++i) take(i, def);
+            double best = pair();
+            for (int i = 0; i < 3 && st == LF2_OK; ++i) {
+                take(i, tuned);
+                const bool same = p->svar[i] == def.svar[i] && p->svar_b[i] == def.svar_b[i] &&
+                                  p->schunk[i] == def.schunk[i] && p->gen[i] == def.gen[i] &&
+                                  p->nat[i] == def.nat[i] && p->xx == (i == 0 ? def.xx : p->xx) &&
+                                  memcmp(&p->sched[i], &def.sched[i], sizeof(GSched)) == 0;
+                if (same) continue;
+                const double us = pair();
+                if (us >= 0 && us < 0.995 * best) {
+                    best = us;
+                } else {
+                    take(i, def);
+                    p->tune_us[i][1] = p->tune_us[i][0];
+                }
+            }
+            if (def.plane && st == LF2_OK) {
+                p->plane = true;
+                const double one = pair();
+                if (one >= 0 && best >= 0 && best < 0.97 * one) p->plane = false;
+            }
+            prof::t_quiet = was_quiet;
+        }
+        // reported per pass: the mean of the two directions
+        for (auto &us : p->tune_us)
+            for (double &v : us)
+                if (v > 0) v *= 0.5;
     }
     if (s) (void)hipStreamSynchronize(s);
     if (e0) (void)hipEventDestroy(e0);
@@ -1006,6 +1088,7 @@ lf2_status autotune(lf2_plan p)
     if (s) (void)hipStreamDestroy(s);
     (void)hipFree(w);
     if (w2) (void)hipFree(w2);
+    if (w3) (void)hipFree(w3);
     return st;
 }
 

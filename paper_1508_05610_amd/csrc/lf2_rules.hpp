@@ -3,6 +3,8 @@
 #pragma once
 #include <stddef.h>
 
+#include <vector>
+
 namespace lf2 {
 
 // Blocks of a binned z pass over lines of `len` points (reg: in register
@@ -24,6 +26,62 @@ inline int binning_blocks(int len, int cap, size_t lds, int waves, bool reg = fa
     const int by_lds = (int)(160 * 1024 / lds), by_waves = 16 / waves;
     const int n = by_lds < by_waves ? by_lds : by_waves, r = 256 * (n < 1 ? 1 : n);
     return cap < r ? cap : r;
+}
+
+// A setting of a strided pass that the autotuner timed: microseconds of the
+// forward and of the backward pass (below 0: not measured).
+struct TileTime {
+    int variant, chunk;
+    double fwd, bwd;
+};
+// The chosen variants of the two directions, their common chunk, and the sum of
+// the two passes' microseconds of the default and of the choice.
+struct TileChoice {
+    int fwd, bwd, chunk;
+    double us_default, us;
+};
+// From the timed settings: per direction and chunk the default's variant, or
+// one that beats the best so far by 3 %, so that noise does not flip the choice
+// from run to run; of the chunks the default's, or one whose two passes
+// together beat the best so far by 3 %.  d: the default setting.
+inline TileChoice choose_tiles(const std::vector<TileTime> &t, TileChoice d)
+{
+    auto pick = [&](int chunk, int def, double TileTime::*us, int &variant) {
+        double best = -1.0;
+        for (int pass = 0; pass < 2; ++pass)  // the default first
+            for (const TileTime &x : t) {
+                if (x.chunk != chunk || (x.variant == def) != (pass == 0) || x.*us < 0) continue;
+                if (best < 0 || x.*us < 0.97 * best) {
+                    best = x.*us;
+                    variant = x.variant;
+                }
+            }
+        return best;
+    };
+    TileChoice out = d;
+    out.us_default = out.us = -1.0;
+    double f0 = -1.0, b0 = -1.0;
+    std::vector<int> chunks{d.chunk};
+    for (const TileTime &x : t) {
+        if (x.chunk == d.chunk && x.variant == d.fwd) f0 = x.fwd;
+        if (x.chunk == d.chunk && x.variant == d.bwd) b0 = x.bwd;
+        bool seen = false;
+        for (int c : chunks) seen = seen || c == x.chunk;
+        if (!seen) chunks.push_back(x.chunk);
+    }
+    if (f0 >= 0 && b0 >= 0) out.us_default = f0 + b0;
+    for (int c : chunks) {
+        int vf = d.fwd, vb = d.bwd;
+        const double f = pick(c, d.fwd, &TileTime::fwd, vf), b = pick(c, d.bwd, &TileTime::bwd, vb);
+        if (f < 0 || b < 0) continue;
+        if (out.us < 0 || f + b < 0.97 * out.us) {
+            out.us = f + b;
+            out.fwd = vf;
+            out.bwd = vb;
+            out.chunk = c;
+        }
+    }
+    return out;
 }
 
 }  // namespace lf2

@@ -20,3 +20,7 @@ def _run(tmp_path, name):
 
 def test_grids_of_the_binned_passes(tmp_path):
     _run(tmp_path, "grid_check")
+
+
+def test_autotuner_choice(tmp_path):
+    _run(tmp_path, "tune_check")
