@@ -309,8 +309,9 @@ lf2_status lf2_plan_destroy(lf2_plan p);
  * length: one launch per group plus one finalize launch, captured in a
  * hipGraph in which each group depends only on the previous pass's groups
  * that hold one of its fields.
- * Each field gives the same result as lf2_poisson_solve on it alone (power
- * spectra within FP64 summation order).
+ * Each field gives the same result as lf2_poisson_solve on it alone up to FP32
+ * rounding: a solve may run other tiles than a batch (the fused register tile,
+ * whole planes of small lattices).
  *
  * lats: nfields dense lattices (halo 0) whose N0/2, N1 and N2 are each one
  *   of 16, 32, 48, 64, 80, 96, 128, 160, 192, 256, 384.

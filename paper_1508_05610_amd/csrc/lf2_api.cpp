@@ -1489,8 +1489,9 @@ lf2_status poisson_impl(lf2_plan p, const float *rho, float *phi, double dx, uin
     const bool parseval = d_parseval != nullptr;
     const int nb = nbins > 0 ? nbins : (parseval ? 1 : 0);
     // bins and Parseval sums are FP64 sums of the forward spectrum: the plane
-    // kernel makes it where it gives the two passes' bits
-    bool plane = p->plane && (nb == 0 || p->plane_bits);
+    // kernel makes it where it gives the two passes' bits, with bins and
+    // without, so that phi does not depend on what else is asked for
+    bool plane = p->plane && p->plane_bits;
     WsLayout L = ws_layout(p, true, nb, parseval, plane);
     const size_t room = ws_given ? ws_given_bytes : p->own_ws ? p->own_ws_bytes : L.total;
     if (plane && room < L.total) {
