@@ -378,16 +378,18 @@ bool plane_axis_ok(int len)
 // dft_fixed) except where the compiler chose otherwise there: on
 // run-time-schedule lines always; on compiled ones not the 16-point
 // butterfly (real x lines of 16 points excepted) nor, on y and complex x
-// lines, the 5-point one; and not on compiled complex x lines of two stages
-// and more, whose last twiddles it rounds one way in some of a thread's
-// butterflies and another way in others.
+// lines, the 5-point one; not on y lines of three power-of-two stages (512
+// points: 8, 8, 8), where P(k) moved by 1e-9 to 6e-9; and not on compiled
+// complex x lines of two stages and more, whose last twiddles it rounds one way
+// in some of a thread's butterflies and another way in others.
 bool plane_axis_bits(int len, PlaneAxis axis)
 {
     const RadixPlan p = radix_plan(len);
     if (p.nodd > 1) return true;
     const bool f16 = p.f[0] == 16, f5 = p.f[p.nf - 1] == 5;
     if (axis == PLANE_X_REAL) return !f16 || len == 16;
-    return !f16 && !f5 && (axis == PLANE_Y || p.nf == 1);
+    const bool f222 = p.nodd == 0 && p.nf > 2;
+    return !f16 && !f5 && (axis == PLANE_Y ? !f222 : p.nf == 1);
 }
 
 hipError_t launch_plane(int mode, int sign, const XArgs &x, int m, int np, int nc, int n1, int n2,

@@ -34,3 +34,50 @@ def test_phi_does_not_depend_on_bins(lf2, shape):
     phi = p.poisson(x)
     for kw in ({"nbins": 8}, {"nbins": 0, "parseval": True}, {"nbins": 20, "parseval": True}):
         assert torch.equal(p.poisson(x, **kw)[0], phi), kw
+
+
+def _kernels(fn):
+    """Names of the kernels a call launches."""
+    from paper_1508_05610_amd import _lib
+    _lib.lf2_profile_enable(1)
+    try:
+        fn()
+        return " ".join(_lib.profile_table())
+    finally:
+        _lib.lf2_profile_enable(0)
+
+
+def _two_pass(lf2, *args, **kw):
+    p = lf2.Plan(*args, **kw)
+    radices, runtime = p.schedule(1)
+    if runtime:
+        p.set_schedule(1, radices)
+    else:
+        p.set_tuning(1, 0, 16)
+    return p
+
+
+LENGTHS = sorted({2 ** a * 3 ** b * 5 ** c for a in range(11) for b in range(7) for c in range(5)
+                  if 1 < 2 ** a * 3 ** b * 5 ** c <= 1024})
+
+
+@pytest.mark.parametrize("axis,kind", [("x", 0), ("x", 1), ("y", 0), ("y", 1)])
+def test_binned_planes_have_the_two_passes_bits(lf2, axis, kind):
+    """Every line length along x and y, real and complex fields, 432 rows (an x tile and
+    part of a second at the shortest lines): where P(k) runs the plane kernel, the
+    spectrum is the two passes'."""
+    dtype = torch.complex64 if kind else torch.float32
+    taken, differ = [], []
+    for n in LENGTHS:
+        # the other axis: 3 points (x) or 6 (y), whose stages have the bits
+        shape = ((n if kind else 2 * n), 6, 72) if axis == "x" else ((3 if kind else 6), n, 72)
+        p, q = lf2.Plan(shape, kind), _two_pass(lf2, shape, kind)
+        x = _random(p.x_shape, dtype, 64)
+        if "k_plane" not in _kernels(lambda: p.power_spectrum(x, 4)):
+            continue
+        taken.append(n)
+        assert "k_plane" not in _kernels(lambda: q.forward(x))
+        if not torch.equal(torch.view_as_real(p.forward(x)), torch.view_as_real(q.forward(x))):
+            differ.append(n)
+    print(f"case plane bits {axis} kind={kind}: {len(taken)} lengths {taken}", flush=True)
+    assert not differ and len(taken) >= 20
