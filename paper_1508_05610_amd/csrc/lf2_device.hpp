@@ -715,21 +715,28 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout, c
             const int c = b % NC, t = b / NC;
             const int j = t % Q, q = t / Q;
             const int l = q * NC + c;
-            const int64_t at = SRC_G ? in_at(q) : 0;
+            // a row past the last one loads the last, and is neither summed nor
+            // stored: loads under a condition were joined by register copies,
+            // each of which waited for its load (complex x passes, us: 16 x 192 x
+            // 1024 back 42.6 and 28.5, 16 x 192 x 768 with six components 68.8 and
+            // 61.5, 512 x 96 x 6 with three forward 11.6 and 10.6).  Not the forward
+            // pass over one complex component, which has no such copies and
+            // whose bits P(k) of a field rests on.
+            constexpr bool kClamp = PACK || NC > 1 || S > 0;
+            const int64_t at = SRC_G ? in_at(!kClamp || q < nvalid ? q : nvalid - 1) : 0;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 if (SRC_G && PACK) {
                     const float *fp = (const float *)gin + at + 2 * (j + r * Q) * NC + c;
-                    v[i][r] = q < nvalid ? c32{gloadf<NTM>(fp), gloadf<NTM>(fp + NC)}
-                                         : c32{0.f, 0.f};
+                    v[i][r] = c32{gloadf<NTM>(fp), gloadf<NTM>(fp + NC)};
                 } else if (SRC_G) {
-                    v[i][r] = q < nvalid ? gload<NTM>(gin + at + (j + r * Q) * NC + c)
-                                         : c32{0.f, 0.f};
+                    const c32 *p = gin + at + (j + r * Q) * NC + c;
+                    v[i][r] = kClamp || q < nvalid ? gload<NTM>(p) : c32{0.f, 0.f};
                 } else {
                     v[i][r] = buf[l * LP + lpad(j + r * Q)];
                 }
             }
-            if (SRC_G) hook.values(v[i]);
+            if (SRC_G && q < nvalid) hook.values(v[i]);
         }
     }
     hook.loaded();

@@ -1,4 +1,5 @@
-"""Registers of the built kernels, from the code object metadata of the built library."""
+"""Registers and load sequences of the built kernels, from the code objects of the built
+library."""
 import os
 import re
 import shutil
@@ -10,10 +11,12 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_1508_05610_amd", "liblf2.so")
 READELF = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
+OBJDUMP = shutil.which("llvm-objdump") or "/opt/rocm/llvm/bin/llvm-objdump"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
-pytestmark = pytest.mark.skipif(not os.path.exists(LIB) or not os.path.exists(READELF),
-                                reason="needs the built library and llvm-readelf")
+pytestmark = pytest.mark.skipif(
+    not all(os.path.exists(f) for f in (LIB, READELF, OBJDUMP)),
+    reason="needs the built library, llvm-readelf and llvm-objdump")
 
 
 def _code_objects():
@@ -68,3 +71,43 @@ def test_transposing_tiles_leave_room_for_their_blocks(kernels):
         if n >= 48 and n not in (384, 768) and 8 * n * (cols + 1) <= 160 * 1024 // 3:
             assert vgprs <= 80, (name, vgprs)
     assert {16, 96, 192, 320, 640, 1024} <= seen
+
+
+def _waits_among_loads(code):
+    """Waits for global loads between one load and the next, nothing being stored to LDS,
+    met at a barrier or computed between the two."""
+    n, waited, loading = 0, False, False
+    for line in code.splitlines():
+        op = line.split()[0] if line.startswith("\t") and line.split() else ""
+        if op.startswith("global_load"):
+            n += waited and loading
+            loading, waited = True, False
+        elif op == "s_waitcnt" and "vmcnt" in line:
+            waited = True
+        elif op.startswith(("ds_write", "s_barrier", "global_store", "v_fma", "v_add_f", "v_mul_f",
+                            "v_sub_f")):
+            loading = waited = False
+    return n
+
+
+# complex x passes of one and of many stages, one component (backward) and several;
+# real ones of interleaved components
+@pytest.mark.parametrize("kernel", ["k_x_c2c_v<16,1,1>", "k_x_c2c_v<16,6,1>", "k_x_c2c_v<24,6,-1>",
+                                    "k_x_c2c_v<48,3,-1>", "k_x_c2c_v<192,6,1>", "k_x_c2c_v<320,2,1>",
+                                    "k_x_c2c_v<512,3,-1>", "k_x_r2c<48,3>", "k_x_r2c<128,2>"])
+def test_first_loads_are_issued_together(kernel, tmp_path):
+    name, args = kernel[:-1].split("<")
+    mangled = "_ZN3lf2%d%sI%sEEvNS_5XArgsE" % (len(name), name, "".join(
+        "Li%sE" % a.replace("-", "n") for a in args.split(",")))
+    path, found = str(tmp_path / "kernels.co"), False
+    for co in _code_objects():
+        if mangled.encode() not in co:
+            continue
+        with open(path, "wb") as f:
+            f.write(co)
+        code = subprocess.run([OBJDUMP, f"--disassemble-symbols={mangled}", path],
+                              capture_output=True, text=True, check=True).stdout
+        assert "global_load" in code
+        found = True
+        assert _waits_among_loads(code) == 0
+    assert found
