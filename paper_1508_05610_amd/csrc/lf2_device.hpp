@@ -698,9 +698,9 @@ __device__ __forceinline__ void gstoref(float *p, float v)
 }
 
 template <int L, int R, int R1, int NS, int S, int RB, int NC, int LP, int NT, bool SRC_G, bool DST_G,
-          bool NTM = false, bool PACK = false, class At, class Hook = NoHook>
-__device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout, const At &in_at,
-                                          const At &out_at, int nvalid, const c32 *tw, int tid,
+          bool NTM = false, bool PACK = false, class AtI, class AtO, class Hook = NoHook>
+__device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout, const AtI &in_at,
+                                          const AtO &out_at, int nvalid, const c32 *tw, int tid,
                                           Hook hook = {})
 {
     constexpr int Q = L / R;
@@ -790,9 +790,9 @@ __device__ __forceinline__ void row_stage(c32 *buf, const c32 *gin, c32 *gout, c
 }
 
 template <int L, int S, int RB, int NC, int LP, int NT, bool SRC_G, bool DST_G, int ST = 0,
-          int NS = 1, bool NTM = false, bool PACK = false, class At, class Hook = NoHook>
-__device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout, const At &in_at,
-                                        const At &out_at, int nvalid, const c32 *tw, int tid,
+          int NS = 1, bool NTM = false, bool PACK = false, class AtI, class AtO, class Hook = NoHook>
+__device__ __forceinline__ void row_fft(c32 *buf, const c32 *gin, c32 *gout, const AtI &in_at,
+                                        const AtO &out_at, int nvalid, const c32 *tw, int tid,
                                         Hook hook = {})
 {
     if constexpr (L == 1) {

@@ -160,11 +160,13 @@ template <int M, int NC, int NT>
 struct XR2CGen {
     static constexpr int RB = x_rb(M, NC, NT), NL = RB * NC, LP = row_pitch(M),
                          NH = M + 1;
+    // one component alone feeds P(k), whose bits the table's place decides
+    static constexpr bool kTableFirst = NC == 1 && table_first(M);
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * NL * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
                             O_RED = al16(O_TWP + sizeof(c32) * NH),
-                            O_IB = al16(O_RED + 8 * (NT / 64)),
-                            BYTES = O_IB + (table_first(M) ? 8 * RB : 0);
+                            O_OB = al16(O_RED + 8 * (NT / 64)), O_IB = O_OB + 8 * RB,
+                            BYTES = O_IB + (kTableFirst ? 8 * RB : 0);
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
@@ -183,10 +185,14 @@ struct XR2CGen {
         // the first stage reads each component's packed pairs straight from
         // the real rows (two float loads per point; no alignment needed)
         double ss = 0.0;
-        if constexpr (table_first(M)) {
+        // the store below looks rows up for every value, so their offsets are
+        // kept (computed there, 96 x 192 x 128 with six components 35 -> 39 us)
+        int64_t *ob = (int64_t *)(sm + O_OB);
+        if constexpr (kTableFirst) {
             if (tab) tables(a, sm, tid);
             int64_t *ib = (int64_t *)(sm + O_IB);
             fill_rows<RB, NT>(ib, in_at, nv, tid);
+            fill_rows<RB, NT>(ob, out_at, nv, tid);
             __syncthreads();
             row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
                 buf, (const c32 *)a.in, nullptr, RowTable{ib}, RowTable{ib}, nv, tw, tid,
@@ -201,6 +207,7 @@ struct XR2CGen {
             row_fft<M, -1, RB, NC, LP, NT, true, false, 0, 1, true, true>(
                 buf, (const c32 *)a.in, nullptr, in_at, out_at, nv, tw, tid,
                 real_hook(ss, sumsq != nullptr, [&] {
+                    fill_rows<RB, NT>(ob, out_at, nv, tid);
                     if (!tab) return;
                     wt.store((c32 *)(sm + O_TW), tid);
                     wp.store((c32 *)(sm + O_TWP), tid);
@@ -227,7 +234,7 @@ struct XR2CGen {
                     const c32 d = sub(z, zc);
                     const c32 fo = c32{0.5f * d.y, -0.5f * d.x};  // (z - zc) / (2i)
                     const c32 wf = mul(twp[k], fo);
-                    c32 *orow = out + out_at(l) + c;
+                    c32 *orow = out + ob[l] + c;
                     gstore<true>(orow + k * NC, add(fe, wf));
                     if (2 * k != M) gstore<true>(orow + (M - k) * NC, conjg(sub(fe, wf)));
                 }
@@ -244,7 +251,7 @@ struct XC2RGen {
     static constexpr int RB = x_rb(M, NC, NT), NL = RB * NC, LP = row_pitch(M + 1), NH = M + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * NL * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
-                            BYTES = al16(O_TWP + sizeof(c32) * NH);
+                            O_OB = al16(O_TWP + sizeof(c32) * NH), BYTES = O_OB + 8 * RB;
     static __device__ void tables(const XArgs &a, char *sm, int tid)
     {
         load_table((c32 *)(sm + O_TW), a.tw, M, tid, NT);
@@ -259,7 +266,7 @@ struct XC2RGen {
     }
     // Real rows from the LDS lines: float x NC + c of row l is part x & 1 of
     // point x >> 1 of line l NC + c.
-    static __device__ void store_rows(const XArgs &a, const c32 *buf, const RowAt &out_at, int nv,
+    static __device__ void store_rows(const XArgs &a, const c32 *buf, const RowTable &out_at, int nv,
                                       int tid)
     {
         typedef float nf4 __attribute__((ext_vector_type(4)));
@@ -288,7 +295,8 @@ struct XC2RGen {
         const c32 *tw = (const c32 *)(sm + O_TW), *twp = (const c32 *)(sm + O_TWP);
         const int64_t r0 = blk * RB;
         const RowAt in_at = row_at(a.in_off, a.in_row, a.in_plane, a.n1, r0);
-        const RowAt out_at = row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0);
+        int64_t *ob = (int64_t *)(sm + O_OB);  // offsets of the rows to store, kept
+        const RowTable out_at{ob};
         TableRegs<M, NT> wt;
         TableRegs<NH, NT> wp;
         if (tab) {
@@ -351,6 +359,7 @@ struct XC2RGen {
             }
         }
         tabs(false);
+        fill_rows<RB, NT>(ob, row_at(a.out_off, a.out_row, a.out_plane, a.n1, r0), nv, tid);
         __syncthreads();
         // Z[k] = (X[k] + conj X[M-k]) + i W^{-k} (X[k] - conj X[M-k]), k < M,
         // with the imaginary parts of X[0] and X[M] dropped.
@@ -435,7 +444,9 @@ struct XC2RGen {
 // fe = (Z[k] + conj Z[M-k]) / 2, fo = (Z[k] - conj Z[M-k]) / (2i).
 template <int M, int NT>
 struct XR2CV {
-    static constexpr int RB = x_rb(M, 1, NT), LP = row_pitch(M), NH = M + 1;
+    // (rows of up to 16 points an odd pitch apart: 32 x 192 x 1024 14.6 us at a
+    // pitch of 16, 13.3 at one of 17)
+    static constexpr int RB = x_rb(M, 1, NT), LP = M <= 16 ? (M | 1) : row_pitch(M), NH = M + 1;
     static constexpr size_t O_BUF = 0, O_TW = al16(O_BUF + sizeof(c32) * RB * LP),
                             O_TWP = al16(O_TW + sizeof(c32) * M),
                             O_RED = al16(O_TWP + sizeof(c32) * NH),
@@ -767,12 +778,21 @@ struct XC2CV {
         } else {
             TableRegs<L, NT> wt;
             if (tab) wt.load(a.tw, tid);
-            row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
-                buf, (const c32 *)a.in, (c32 *)a.out, in_at, out_at, nv, tw, tid, tab_hook([&] {
-                    if (!tab) return;
-                    wt.store((c32 *)(sm + O_TW), tid);
-                    if (kPaired<L>) __syncthreads();  // else the first stage reads no table
-                }));
+            // the last stage's row offsets are kept where a barrier lies before it
+            constexpr bool kept = kPlan<L>.n > 1;
+            int64_t *ob = (int64_t *)(sm + O_OB);
+            auto tabs = tab_hook([&] {
+                if (kept) fill_rows<RB, NT>(ob, out_at, nv, tid);
+                if (!tab) return;
+                wt.store((c32 *)(sm + O_TW), tid);
+                if (kPaired<L>) __syncthreads();  // else the first stage reads no table
+            });
+            if constexpr (kept)
+                row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
+                    buf, (const c32 *)a.in, (c32 *)a.out, in_at, RowTable{ob}, nv, tw, tid, tabs);
+            else
+                row_fft<L, S, RB, NC, LP, NT, true, true, 0, 1, true>(
+                    buf, (const c32 *)a.in, (c32 *)a.out, in_at, out_at, nv, tw, tid, tabs);
         }
         __syncthreads();
     }
