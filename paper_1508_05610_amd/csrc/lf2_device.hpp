@@ -577,7 +577,12 @@ __device__ __forceinline__ void col_stage(c32 *buf, const c32 *gin, c32 *gout, i
         const int j = j0 + i * JS;
         if (Q % JS == 0 || j < Q) {
             if (SRC_G) {
-                gload_pts<R, NTM>(v[i], gin + (int64_t)j * gs, (int64_t)Q * gs, gv);
+                // (a column past the end is column 0; its loads at 1024 points and
+                // more are not conditional, since the compiler waited for the first
+                // of them: 80 x 192 x 1024 z back 48.0 us, 45.8 without.  Forward they
+                // are, where P(k) rests on the bits)
+                gload_pts<R, NTM>(v[i], gin + (int64_t)j * gs, (int64_t)Q * gs,
+                                  gv || (L >= 1024 && S > 0));
             } else {
 #pragma unroll
                 for (int r = 0; r < R; ++r) v[i][r] = buf[l + (j + r * Q) * NL];

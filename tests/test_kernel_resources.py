@@ -90,6 +90,20 @@ def _waits_among_loads(code):
     return n
 
 
+def _kernel_waits(mangled, tmp_path):
+    path = str(tmp_path / "kernels.co")
+    for co in _code_objects():
+        if mangled.encode() not in co:
+            continue
+        with open(path, "wb") as f:
+            f.write(co)
+        code = subprocess.run([OBJDUMP, f"--disassemble-symbols={mangled}", path],
+                              capture_output=True, text=True, check=True).stdout
+        assert "global_load" in code
+        return _waits_among_loads(code)
+    raise AssertionError(f"no kernel {mangled}")
+
+
 # complex x passes of one and of many stages, one component (backward) and several;
 # real ones of interleaved components
 @pytest.mark.parametrize("kernel", ["k_x_c2c_v<16,1,1>", "k_x_c2c_v<16,6,1>", "k_x_c2c_v<24,6,-1>",
@@ -99,15 +113,16 @@ def test_first_loads_are_issued_together(kernel, tmp_path):
     name, args = kernel[:-1].split("<")
     mangled = "_ZN3lf2%d%sI%sEEvNS_5XArgsE" % (len(name), name, "".join(
         "Li%sE" % a.replace("-", "n") for a in args.split(",")))
-    path, found = str(tmp_path / "kernels.co"), False
-    for co in _code_objects():
-        if mangled.encode() not in co:
-            continue
-        with open(path, "wb") as f:
-            f.write(co)
-        code = subprocess.run([OBJDUMP, f"--disassemble-symbols={mangled}", path],
-                              capture_output=True, text=True, check=True).stdout
-        assert "global_load" in code
-        found = True
-        assert _waits_among_loads(code) == 0
-    assert found
+    assert _kernel_waits(mangled, tmp_path) == 0
+
+
+# strided passes over the longest lines, backward, narrow and wide; over 512 points
+@pytest.mark.parametrize("mangled", [
+    "_ZN3lf29k_stridedILi1024ELi1ELb0ELb0ELi0EEEvNS_5SArgsE",
+    "_ZN3lf29k_stridedILi1024ELi1ELb0ELb1ELi0EEEvNS_5SArgsE",
+    "_ZN3lf29k_stridedILi2048ELi1ELb0ELb0ELi0EEEvNS_5SArgsE",
+    "_ZN3lf211k_strided_wILi1024ELi1ELb1EEEvNS_5SArgsE",
+    "_ZN3lf211k_strided_wILi2048ELi1ELb0EEEvNS_5SArgsE",
+    "_ZN3lf29k_stridedILi512ELin1ELb0ELb0ELi0EEEvNS_5SArgsE"])
+def test_first_column_loads_are_issued_together(mangled, tmp_path):
+    assert _kernel_waits(mangled, tmp_path) == 0
