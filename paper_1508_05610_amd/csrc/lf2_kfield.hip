@@ -235,14 +235,8 @@ hipError_t launch_gradient(const float *in, float *out, const int64_t n[3], int6
     const int64_t gx = (rowwords + kGradMaxThreads - 1) / kGradMaxThreads;
     a.width = (int)(((rowwords + gx - 1) / gx + 63) / 64 * 64);
     const int64_t gy = (n[1] + kGradRows - 1) / kGradRows;
-    // A block marches through its planes one memory latency at a time, so a
-    // small lattice's few blocks of 32 planes leave most of the chip idle (64^3,
-    // one component: 32 blocks, 25.2 us).  Planes per block are halved, down
-    // to 4 (every march reads one plane more than it writes), until the grid
-    // has one and a half times the waves the chip holds: 64^3 6.6 us, 128^3
-    // 28.2 -> 9.0, 256^3 76 -> 61, 200^3 with 3 components 103 -> 88; 512^3
-    // with 3 keeps 32.
-    while (a.zc > 4 && gx * gy * ((n[2] + a.zc - 1) / a.zc) * (a.width / 64) < 12288) a.zc /= 2;
+    const int64_t waves = gx * gy * ((n[2] + a.zc - 1) / a.zc) * (a.width / 64);
+    a.zc = gradient_planes(waves, gx * a.width == rowwords, a.zc);
     const int64_t gz = (n[2] + a.zc - 1) / a.zc;
     if (gx * gy * gz > 0x7fffffff) return hipErrorInvalidValue;
     a.gx = (int)gx;

@@ -2,6 +2,7 @@
 // so that they are checked without a GPU.
 #pragma once
 #include <stddef.h>
+#include <stdint.h>
 
 #include <vector>
 
@@ -26,6 +27,22 @@ inline int binning_blocks(int len, int cap, size_t lds, int waves, bool reg = fa
     const int by_lds = (int)(160 * 1024 / lds), by_waves = 16 / waves;
     const int n = by_lds < by_waves ? by_lds : by_waves, r = 256 * (n < 1 ? 1 : n);
     return cap < r ? cap : r;
+}
+
+// Planes per block of the derivative: most, or 4.  waves: of the grid with most
+// (32) planes a block; full: its rows leave no lane idle.  A block marches
+// through its planes one memory latency at a time, so a lattice's few blocks of
+// 32 planes leave most of the chip idle, or the last of them run alone; with
+// blocks of 4 (every march reads one plane more than it writes) 64^3 takes 6.6
+// us of 25.2, 128^3 9.0 of 28.2, 256^3 60 of 75, 384^3 214 of 256, 200^3 with 3
+// components 84 of 101.  Blocks of 32 stay where their waves fill the chip's 8192
+// half to three quarters in one round with no idle lane: 640 x 640 x 96 133 us
+// (147 with 4), 384 x 384 x 256 141 (144), 256^3 with 3 components 160 (166); and
+// past one and a half rounds (512^3 with 3 the same with either).
+inline int gradient_planes(int64_t waves, bool full, int most)
+{
+    const bool round = full && waves >= 4096 && waves <= 6144;
+    return waves >= 12288 || round ? most : 4;
 }
 
 // A setting of a strided pass that the autotuner timed: microseconds of the

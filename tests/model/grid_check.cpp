@@ -1,7 +1,8 @@
 // Host check of the grids of the binned z passes (binning_blocks): a round of
 // the blocks that 256 CUs hold up to the lengths where one was measured
 // faster, the partial rows' whole number past them, never more rows than
-// those, and a multiple of 8 (one virtual block id walk per XCD).
+// those, and a multiple of 8 (one virtual block id walk per XCD); and of the
+// derivative's planes per block (gradient_planes).
 #include <stdio.h>
 
 #include "../../paper_1508_05610_amd/csrc/lf2_rules.hpp"
@@ -34,6 +35,20 @@ int main()
             return 1;
         }
     }
+    struct {
+        int64_t waves;
+        bool full;
+        int want;
+    } d[] = {
+        {32, true, 4},     {4095, true, 4},   {4096, true, 32},  // one round, no idle lane
+        {4800, true, 32},  {6144, true, 32},  {6145, true, 4},
+        {4800, false, 4},  {12287, true, 4},  {12288, false, 32}, {49152, true, 32},
+    };
+    for (const auto &k : d)
+        if (lf2::gradient_planes(k.waves, k.full, 32) != k.want) {
+            printf("FAIL %lld waves full %d\n", (long long)k.waves, (int)k.full);
+            return 1;
+        }
     printf("ok\n");
     return 0;
 }
