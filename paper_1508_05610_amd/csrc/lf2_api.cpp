@@ -210,19 +210,28 @@ int x_grid_blocks(const lf2_plan_s *p)
 }
 
 // Whether the plan's planes run both their axes in one block (k_plane): they
-// fit its LDS, the field is small enough to be bound by latency, and there is
-// a plane for every CU or the planes are small.  With N1 = 64 and N0 = 64 or
-// 128, real: 4.2 M sites 1.2 times faster forward and 1.1 backward, 8.4 M
-// sites equal forward and 0.9 times as fast backward.  128 x 128 planes
-// (142 KB): 256 of them 1.5 and 1.1 times faster, 128 of them 1.1 and 1.0, and
-// the Poisson solve's way back 1 us slower, half the chip being idle; 120 x
-// 120 planes (123 KB), 120 of them: 1.1 and 1.03 times faster.
+// fit its LDS, the field is small enough to be bound by latency, and the blocks
+// fill the chip: planes that take a CU alone (past half its LDS) pay where they
+// are three quarters of the CUs' number up to that number, smaller planes of
+// that kind (128 KB) from fewer on.  With N1 = 64 and N0 = 64 or 128, real: 4.2 M
+// sites 1.2 times faster forward and 1.1 backward, 8.4 M sites equal forward
+// and 0.9 times as fast backward.  128 x 128 planes (140 KB), one launch and two
+// passes, forward / backward / Poisson solve in us: 128 of them 22.6 / 22.8 / 42.7
+// and 23.7 / 22.5 / 41.4, 192 25.5 / 25.2 / 52.2 and 31.4 / 27.7 / 52.5, 240 25.5 /
+// 26.1 / 56.9 and 33.4 / 28.1 / 56.7, 256 25.5 / 26.4 / 54.9 and 35.1 / 28.8 / 56.5,
+// 270 38.3 / 39.7 / 69.4 and 37.2 / 31.3 / 61.1; 96 x 96 complex planes, 192 of
+// them, 27.7 / 26.5 and 31.8 / 28.7; 120 x 120 planes (123 KB), 120 of them: 1.1 and
+// 1.03 times faster.
 bool plane_fits(const lf2_plan_s *p)
 {
     if (p->ntot * p->nc * (p->kind == LF2_C2C ? 2 : 1) > kPlaneFloats) return false;
     if (!plane_axis_ok(p->len[0]) || !plane_axis_ok(p->len[1])) return false;
-    return plane_lds_bytes(p->len[0], (int)p->nxk, p->nc, p->len[1]) <=
-           (p->n[2] < 256 ? (size_t)128 * 1024 : p->n[2] == 256 ? kPlaneLds : kPlaneLds / 2);
+    const size_t lds = p->lds_max < kPlaneLds ? p->lds_max : kPlaneLds;
+    const size_t most = p->n[2] > p->ncu       ? lds / 2
+                        : 4 * p->n[2] >= 3 * p->ncu ? lds
+                        : lds < 128 * 1024     ? lds
+                                               : 128 * 1024;
+    return plane_lds_bytes(p->len[0], (int)p->nxk, p->nc, p->len[1]) <= most;
 }
 
 // Tile settings of the y and z passes until one is set or tuned.  Narrow tiles
@@ -1143,6 +1152,10 @@ lf2_status lf2_fft_plan(lf2_plan *out, const lf2_lattice *lat, int32_t ncomp, lf
             hipSuccess &&
         lds > 0)
         p->lds_max = (size_t)lds;
+    int ncu = 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess &&
+        ncu > 0)
+        p->ncu = ncu;
     // compiled kernels where they exist; run-time radix schedules otherwise
     for (int i = 0; i < 3; ++i) {
         p->gen_only[i] = gen_only[i];

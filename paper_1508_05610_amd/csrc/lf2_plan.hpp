@@ -65,6 +65,7 @@ struct lf2_plan_s {
     bool plane_bits = false; // and forward with the two passes' bits
     int gen_rb = 1;          // x tile rows of the run-time x kernels
     size_t lds_max = 65536;  // LDS bytes a block may use on the plan's device
+    int ncu = 256;           // and its CUs
     void *tw[3] = {nullptr, nullptr, nullptr};
     void *tw_post = nullptr;
     int64_t *q[3] = {nullptr, nullptr, nullptr};

@@ -81,3 +81,20 @@ def test_binned_planes_have_the_two_passes_bits(lf2, axis, kind):
             differ.append(n)
     print(f"case plane bits {axis} kind={kind}: {len(taken)} lengths {taken}", flush=True)
     assert not differ and len(taken) >= 20
+
+
+# 128 x 128 real planes take a CU alone: one launch where they fill three quarters of
+# the 256 CUs up to all of them
+@pytest.mark.parametrize("planes,one", [(160, False), (192, True), (225, True), (256, True), (270, False)])
+def test_large_planes_run_in_one_launch_where_they_fill_the_chip(lf2, planes, one):
+    print(f"case large planes {planes}", flush=True)
+    shape = (128, 128, planes)
+    p, q = lf2.Plan(shape), _two_pass(lf2, shape)
+    x = _random(p.x_shape, torch.float32, 65)
+    F, Fq = p.forward(x), q.forward(x)
+    assert ("k_plane<r2c" in _kernels(lambda: p.forward(x))) == one
+    assert ("k_plane<c2r" in _kernels(lambda: p.backward(F))) == one
+    # two FP32 transforms of 2^22 points, each within 3e-7 of the exact one
+    assert float(torch.linalg.vector_norm(F - Fq) / torch.linalg.vector_norm(Fq)) <= 6e-7
+    b, bq = p.backward(F), q.backward(F)
+    assert float(torch.linalg.vector_norm(b - bq) / torch.linalg.vector_norm(bq)) <= 6e-7
