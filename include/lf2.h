@@ -135,26 +135,31 @@ lf2_status lf2_fft_kspace(lf2_plan p, int64_t ksize[3], int64_t kstride[3]);
  * 2048) instead of narrow tiles (all lengths); bit 2: the register tile
  * (lengths 1024 and 2048, not with bit 0: 32 or 16 columns per tile held in
  * registers as a 32 x 32 or 32 x 64 decomposition with one exchange through
- * LDS); bit 1:
- * nontemporal global loads and stores (they pay on long strides, where each
- * line is touched once).  chunk = consecutive tiles given to one XCD in the
- * tile order (1..1024, default 16).  The default variant depends on the
- * line length, the spectrum's bytes and its strides (0 up to 256 MB and on
- * most larger lattices), and the backward z pass of a large spectrum may
- * default to nontemporal accesses where the forward one does not, and
- * LF2_PLAN_AUTOTUNE may choose another variant backward than forward (get reports
- * the forward one, set sets both); the default is a narrow or a wide tile.  Narrow and
- * wide tiles compute the same forward transform bit for bit and the same
- * backward one up to the rounding of single products; the register tile
- * computes it up to FP32 rounding (another order of the butterflies).  The fused Poisson / power-spectrum pass always uses narrow tiles,
- * nontemporal accesses and chunk 16.  get reports the setting and, after
- * LF2_PLAN_AUTOTUNE, the measured microseconds a pass (mean of the two
- * directions) of the plan's default setting and of the chosen one (-1 if not
- * measured); null outputs are skipped; variant -1 means the axis runs a run-time radix
- * schedule (lf2_plan_get_schedule).  set overrides the setting and returns
- * the axis to its compiled kernels (LF2_ERR_UNSUPPORTED for wide tiles or
- * the register tile on a length without them, or for a length without
- * compiled kernels).
+ * LDS); bit 1: nontemporal global loads and stores (they pay on long
+ * strides, where each line is touched once).  chunk = consecutive tiles
+ * given to one XCD in the tile order (1..1024, default 16).  The default
+ * variant depends on the line length, the spectrum's bytes and its strides
+ * (0 up to 256 MB and on most larger lattices), and the backward z pass of a
+ * large spectrum may default to nontemporal accesses where the forward one
+ * does not, and LF2_PLAN_AUTOTUNE may choose another variant backward than
+ * forward (get reports the forward one, set sets both); the default is a
+ * narrow or a wide tile.  Narrow and wide tiles compute the same forward
+ * transform bit for bit and the same backward one up to the rounding of
+ * single products; the register tile computes it up to FP32 rounding
+ * (another order of the butterflies).  The fused Poisson / power-spectrum
+ * pass always uses narrow tiles, nontemporal accesses and chunk 16.  get
+ * reports the setting and, after LF2_PLAN_AUTOTUNE, the measured
+ * microseconds a pass (mean of the two directions) of the plan's default
+ * setting and of the chosen one (-1 if not measured); null outputs are
+ * skipped; variant -1 means that a run-time radix schedule is set, or that
+ * the axis' length takes schedules alone (lf2_plan_get_schedule).  set
+ * overrides the setting and returns the axis to its compiled kernels
+ * (LF2_ERR_UNSUPPORTED for wide tiles or the register tile on a length
+ * without them, or for a length without compiled kernels). Small lattices
+ * whose planes run x and y in one launch run them as two passes once a
+ * setting or a schedule of axis 0 or 1 is set (LF2_PLAN_AUTOTUNE times that
+ * launch against the tuned passes; a kept one leaves their settings to the
+ * calls that run the passes).
  * axis 0 (the x pass): variant = how the two radix-8 stages of a c2c row of
  * 64 points (one component) exchange their values -- 0 through LDS (every
  * plan), 1 across the row's eight lanes with ds_bpermute, 2 across them with
@@ -177,19 +182,20 @@ lf2_status lf2_plan_set_tuning(lf2_plan p, int32_t axis, int32_t variant, int32_
 
 /*
  * Radix schedule (the radices of the Stockham stages, in order; their
- * product is the line length) of the passes along `axis` (0 = x, 1 = y,
- * 2 = z).  Line lengths with compiled kernels use a schedule fixed at
- * compile time; any other 2^a 3^b 5^c length, and any pass for which a
- * schedule is set, takes its schedule at run time (*runtime = 1; up to 1024
- * points the default schedule's stages are compiled, forward bit for bit the
- * same).  LF2_PLAN_AUTOTUNE times the candidate schedules of every such axis,
- * and of the y and z passes against their compiled kernels, and keeps the
- * fastest.  get: radices[0 .. *nstages - 1] (the rest 0); any output may be
- * NULL.  set: each radix 2, 3, 4, 5, 8 or 16 with product the line length;
- * the fused Poisson / power-spectrum pass of a compiled length keeps its
- * compiled kernel; the x pass of a compiled length cannot be set
- * (LF2_ERR_UNSUPPORTED).  Every schedule computes the same transform up to
- * FP32 rounding.
+ * product is the line length) of the passes along `axis` (0 = x, 1 = y, 2 =
+ * z).  Line lengths with compiled kernels use a schedule fixed at compile
+ * time; any other 2^a 3^b 5^c length, and any pass for which a schedule is
+ * set, takes its schedule at run time (*runtime = 1; up to 1024 points the
+ * default schedule's stages are compiled until one is set, forward bit for
+ * bit the same: setting the schedule that get reports leaves the compiled
+ * kernels, and a new plan has them again).  LF2_PLAN_AUTOTUNE times the
+ * candidate schedules of every such axis, and of the y and z passes against
+ * their compiled kernels, and keeps the fastest.  get: radices[0 .. *nstages
+ * - 1] (the rest 0); any output may be NULL.  set: each radix 2, 3, 4, 5, 8
+ * or 16 with product the line length; the fused Poisson / power-spectrum
+ * pass of a compiled length keeps its compiled kernel; the x pass of a
+ * compiled length cannot be set (LF2_ERR_UNSUPPORTED).  Every schedule
+ * computes the same transform up to FP32 rounding.
  */
 lf2_status lf2_plan_get_schedule(lf2_plan p, int32_t axis, int32_t radices[15], int32_t *nstages,
                                  int32_t *runtime);

@@ -316,8 +316,7 @@ lf2_status lf2_batch_plan(lf2_batch *out, int32_t nfields, const lf2_lattice *la
         set_k2_units(F.z.mt, p, dx, (poisson_flags & LF2_POISSON_DISCRETE_K2) ? 1 : 0);
         // bin histograms per wave where the z tile's LDS leaves room for them
         F.z.hcopies = pk ? epi_hist_copies(p->len[2], nbins,
-                                           b->persistent ? batch_persistent_lds() : 80 * 1024,
-                                           b->persistent)
+                                           b->persistent ? batch_persistent_lds() : 80 * 1024)
                          : 1;
         if (F.z.hcopies < 1) F.z.hcopies = 1;
         F.m = p->len[0];

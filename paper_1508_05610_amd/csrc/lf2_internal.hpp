@@ -116,9 +116,7 @@ hipError_t launch_transposed(int len, int sign, const SArgs &a, int grid_cap, hi
 // LDS histogram copies of a fused last-axis tile of length len binning into
 // nbins bins, when the block's LDS is `budget` bytes: one per wave if they
 // fit with the tile, else one.  0 if len has no compiled fused tile.
-// persistent: the persistent batch kernel's blocks of 512 threads (the others
-// have e_nt<len>).
-int epi_hist_copies(int len, int nbins, size_t budget, bool persistent = false);
+int epi_hist_copies(int len, int nbins, size_t budget);
 
 // Kernels of the lengths of LF2_RAGGED_LENGTHS (lf2_kx.hip, lf2_kragged.hip):
 // the x tiles, and the narrow strided tile with its fused epilogue.  The
@@ -179,8 +177,10 @@ hipError_t launch_reduce_cols(const double *partial, int64_t grid, int width, do
 hipError_t launch_pk_kspace(const void *F, int n1, int n2, int64_t sx, int64_t sy, int64_t sz,
                             const ModeTables &mt, double *partial, int grid_cap, hipStream_t s,
                             int *grid_used);
-// Results of a binning pass from its partials ([rows][nbins + 1], slot nbins
-// the row's total) and the lattice's shell table.
+// Results of a binning pass from its partials and the lattice's shell table.
+// Partials are [rows][nbins + 1]; slot nbins is read with parseval alone, as the
+// row's total (the z passes' rows; the k-space pass, which serves no Parseval
+// sum, leaves the zero mode there).
 struct PkTail {
     const double *partial;
     int64_t rows;

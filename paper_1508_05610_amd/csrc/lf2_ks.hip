@@ -30,12 +30,12 @@ bool ragged_supported(int len)
     }
 }
 
-int epi_hist_copies(int len, int nbins, size_t budget, bool persistent)
+int epi_hist_copies(int len, int nbins, size_t budget)
 {
     switch (len) {
 #define LF2_CASE(L)                                                                          \
     case L: {                                                                                \
-        const int waves = (persistent ? kSThreads : e_nt<L>) / 64;                           \
+        const int waves = e_nt<L> / 64;                                                      \
         const size_t tile = s_bytes(L);                                                      \
         return tile + (size_t)(nbins + 1) * 8 * (waves + 1) <= budget ? waves : 1;           \
     }

@@ -58,7 +58,7 @@ def kernels(tmp_path_factory):
 def test_transposing_tiles_leave_room_for_their_blocks(kernels):
     """Where three blocks of a transposing z tile fit a CU's LDS (at most 160 / 3 KB
     with its twiddles), their registers do as well from 48 points on (six waves a SIMD
-    of 512 registers: at most 80), 384 and 768 points excepted; and no tile spills."""
+    of 512 registers: at most 80), 384 points excepted; and no tile spills."""
     seen = set()
     for name, (vgprs, spills, scratch) in kernels.items():
         m = re.fullmatch(r"_ZN3lf211k_strided_tILi(\d+)ELin?1EEEvNS_5SArgsE", name)
@@ -68,7 +68,7 @@ def test_transposing_tiles_leave_room_for_their_blocks(kernels):
         seen.add(n)
         assert spills == 0 and scratch == 0, (name, vgprs, spills, scratch)
         cols = 64 if n <= 128 else 32 if n <= 256 else 16 if n <= 512 else 8 if n <= 1024 else 4
-        if n >= 48 and n not in (384, 768) and 8 * n * (cols + 1) <= 160 * 1024 // 3:
+        if n >= 48 and n != 384 and 8 * n * (cols + 1) <= 160 * 1024 // 3:
             assert vgprs <= 80, (name, vgprs)
     assert {16, 96, 192, 320, 640, 1024} <= seen
 
