@@ -846,9 +846,10 @@ bool x_lane_exchange_ok(const lf2_plan_s *p)
 // candidate radix schedules of the run-time-schedule kernels (every axis
 // without a compiled kernel, and the y and z passes as an alternative to
 // the compiled ones), on a scratch spectrum of the plan's shape, and keep the
-// fastest.  Each is timed in both directions (one warm-up, then the mean of
-// three launches each way; the compiled tile settings of the y and z passes in
-// two sweeps, each keeping its faster times).  The plan's own default
+// fastest.  Each is timed in both directions (after a warm-up; a schedule
+// backward only where its forward pass may still win; the compiled tile settings
+// of the y and z passes in two sweeps, the second of those near the fastest in a
+// direction, each keeping its faster times).  The plan's own default
 // (default_tiles with chunk 16, compiled ragged tiles, or the first schedule)
 // stays unless another beats it by 3 %; the y and z passes may take another
 // variant backward than forward (a 512^3 real z pass backward: nontemporal 208
@@ -880,7 +881,7 @@ lf2_status autotune(lf2_plan p)
         w3 = nullptr;
     }
     hipStream_t s = nullptr;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
     lf2_status st = LF2_OK;
     auto hip_ok = [&](hipError_t e, const char *what) {
         if (e != hipSuccess && st == LF2_OK) st = fail(LF2_ERR_DEVICE, "autotune %s: %s", what, hipGetErrorString(e));
@@ -897,16 +898,35 @@ lf2_status autotune(lf2_plan p)
             return -1.0;
         return 1e3 * ms / n;
     };
-    // both directions of launch(sign) together (-1 on failure)
-    auto time_both = [&](auto &&launch, int n = 3) -> double {
-        const double f = time_it([&] { return launch(-1); }, n);
-        const double b = f < 0 ? -1.0 : time_it([&] { return launch(1); }, n);
+    // the same of n forward, then n backward launch(sign)s into f and b
+    auto time_dirs = [&](auto &&launch, int n, double &f, double &b) {
+        f = b = -1.0;
+        hip_ok(launch(-1), "launch");
+        hip_ok(hipEventRecord(e0, s), "record");
+        for (int r = 0; r < n; ++r) hip_ok(launch(-1), "launch");
+        hip_ok(hipEventRecord(e1, s), "record");
+        for (int r = 0; r < n; ++r) hip_ok(launch(1), "launch");
+        hip_ok(hipEventRecord(e2, s), "record");
+        float ms = 0.f, ms2 = 0.f;
+        if (!hip_ok(hipEventSynchronize(e2), "sync") || !hip_ok(hipEventElapsedTime(&ms, e0, e1), "elapsed") ||
+            !hip_ok(hipEventElapsedTime(&ms2, e1, e2), "elapsed"))
+            return;
+        f = 1e3 * ms / n;
+        b = 1e3 * ms2 / n;
+    };
+    // both directions of launch(sign) together (-1 on failure, or where the
+    // forward pass alone shows that they are no faster than `best`)
+    auto time_both = [&](auto &&launch, double best = -1.0) -> double {
+        const double f = time_it([&] { return launch(-1); });
+        if (f < 0 || (best >= 0 && 1.6 * f > best)) return -1.0;
+        const double b = time_it([&] { return launch(1); });
         return b < 0 ? -1.0 : f + b;
     };
     static const int kChunks[] = {16, 4, 64};  // the default first
     const lf2_plan_s def = *p;
     if (hip_ok(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "stream") &&
         hip_ok(hipEventCreate(&e0), "event") && hip_ok(hipEventCreate(&e1), "event") &&
+        hip_ok(hipEventCreate(&e2), "event") &&
         hip_ok(hipMemsetAsync(w, 0, bytes, s), "memset") &&
         (!w2 || hip_ok(hipMemsetAsync(w2, 0, bytes2, s), "memset"))) {
         // x axis without a compiled kernel: its schedules, on dense rows of w2
@@ -941,7 +961,7 @@ lf2_status autotune(lf2_plan p)
                 const double us = time_both([&](int sign) {
                     const int mode = p->kind == LF2_C2C ? 0 : sign < 0 ? 1 : 2;
                     return launch_gx(mode, sign, args(sign), sc, p->len[0], p->nc, p->gen_rb, s);
-                });
+                }, best);
                 if (p->tune_us[0][0] < 0) p->tune_us[0][0] = us;
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
                     best = us;
@@ -981,9 +1001,10 @@ lf2_status autotune(lf2_plan p)
             const SArgs a = s_args(p, axis, w, w, EPI_STORE);
             double best = -1.0;
             if (!p->gen_only[axis] || p->nat[axis]) {
-                // two sweeps over the settings, each setting keeping its
-                // faster time: a setting timed while the chip's clocks or
-                // memory state drift is timed again in the other sweep.
+                // two sweeps over the settings (the second over those that may
+                // win), each setting keeping its faster time: a setting timed
+                // while the chip's clocks or memory state drift is timed again
+                // in the other sweep.
                 // Order: the nontemporal settings, then the rest; within 3 % the
                 // earlier one stays.  Timed in
                 // short bursts, the cached-store settings of long-stride passes
@@ -999,17 +1020,22 @@ lf2_status autotune(lf2_plan p)
                         if ((v & 4) && (!reg || (v & 1))) continue;
                         for (int c : kChunks) t.push_back({v, c, -1.0, -1.0});
                     }
+                double f0 = -1.0, b0 = -1.0;  // fastest of the first sweep
                 for (int sweep = 0; sweep < 2 && st == LF2_OK; ++sweep)
                     for (TileTime &x : t) {
-                        for (int sign = -1; sign <= 1 && st == LF2_OK; sign += 2) {
-                            const double us = time_it([&] {
-                                return launch_strided(p->len[axis], sign, a, kStridedGridCap, s,
-                                                      nullptr, x.variant, x.chunk);
-                            });
-                            double &keep = sign < 0 ? x.fwd : x.bwd;
-                            if (us >= 0 && (keep < 0 || us < keep)) keep = us;
-                        }
+                        const bool dflt = x.chunk == p->schunk[axis] &&
+                                          (x.variant == p->svar[axis] || x.variant == p->svar_b[axis]);
                         if (st != LF2_OK) break;
+                        if (sweep == 1 && !dflt && x.fwd > 1.06 * f0 && x.bwd > 1.06 * b0) continue;
+                        double f, b;
+                        time_dirs([&](int sign) {
+                            return launch_strided(p->len[axis], sign, a, kStridedGridCap, s, nullptr,
+                                                  x.variant, x.chunk);
+                        }, 2, f, b);
+                        if (f >= 0 && (x.fwd < 0 || f < x.fwd)) x.fwd = f;
+                        if (b >= 0 && (x.bwd < 0 || b < x.bwd)) x.bwd = b;
+                        if (sweep == 0 && f >= 0 && (f0 < 0 || f < f0)) f0 = f;
+                        if (sweep == 0 && b >= 0 && (b0 < 0 || b < b0)) b0 = b;
                     }
                 const TileChoice c = choose_tiles(
                     t, TileChoice{p->svar[axis], p->svar_b[axis], p->schunk[axis], -1.0, -1.0});
@@ -1024,7 +1050,7 @@ lf2_status autotune(lf2_plan p)
                 if (st != LF2_OK || b < 1) break;
                 const double us = time_both([&](int sign) {
                     return launch_gs(sign, a, sc, p->len[axis], b, kStridedGridCap, s, nullptr);
-                });
+                }, best);
                 if (p->tune_us[axis][0] < 0) p->tune_us[axis][0] = us;
                 if (us >= 0 && (best < 0 || us < 0.97 * best)) {
                     best = us;
@@ -1058,19 +1084,24 @@ lf2_status autotune(lf2_plan p)
                 if (!e) e = run_xy(p, bwd, 1, x_args(p, W, w2, false, true, real), W, s, p->plane);
                 return e == LF2_OK ? hipSuccess : hipErrorUnknown;
             };
-            auto pair = [&] { return time_it(one_pair, bytes < ((size_t)16 << 20) ? 20 : 4); };
+            auto pair = [&] {
+                return time_it(one_pair, bytes < ((size_t)16 << 20) ? 10 : bytes < ((size_t)256 << 20) ? 4
+                                                                              : 2);
+            };
             const bool was_quiet = prof::t_quiet;
             prof::t_quiet = true;
             p->plane = false;
+            bool same[3];
+            for (int i = 0; i < 3; ++i)
+                same[i] = tuned.svar[i] == def.svar[i] && tuned.svar_b[i] == def.svar_b[i] &&
+                          tuned.schunk[i] == def.schunk[i] && tuned.gen[i] == def.gen[i] &&
+                          tuned.nat[i] == def.nat[i] && (i > 0 || tuned.xx == def.xx) &&
+                          memcmp(&tuned.sched[i], &def.sched[i], sizeof(GSched)) == 0;
             for (int i = 0; i < 3; ++i) take(i, def);
-            double best = pair();
+            double best = same[0] && same[1] && same[2] && !def.plane ? -1.0 : pair();
             for (int i = 0; i < 3 && st == LF2_OK; ++i) {
+                if (same[i]) continue;
                 take(i, tuned);
-                const bool same = p->svar[i] == def.svar[i] && p->svar_b[i] == def.svar_b[i] &&
-                                  p->schunk[i] == def.schunk[i] && p->gen[i] == def.gen[i] &&
-                                  p->nat[i] == def.nat[i] && p->xx == (i == 0 ? def.xx : p->xx) &&
-                                  memcmp(&p->sched[i], &def.sched[i], sizeof(GSched)) == 0;
-                if (same) continue;
                 const double us = pair();
                 if (us >= 0 && us < 0.995 * best) {
                     best = us;
@@ -1094,6 +1125,7 @@ lf2_status autotune(lf2_plan p)
     if (s) (void)hipStreamSynchronize(s);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
+    if (e2) (void)hipEventDestroy(e2);
     if (s) (void)hipStreamDestroy(s);
     (void)hipFree(w);
     if (w2) (void)hipFree(w2);
